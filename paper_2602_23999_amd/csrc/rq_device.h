@@ -508,6 +508,46 @@ __device__ inline int wave_upper_cluster(const int32_t* __restrict__ off, int n,
   return base;
 }
 
+// ---------------------------------------------------------------------------------
+// Running sums over the lists of an index (pair offsets, work-item tables) by ONE workgroup of NT threads.
+// A thread takes SCAN_PER consecutive entries of a chunk, whose loads are independent of one another, so that a
+// chunk of 8192 lists costs one round of memory latency and two barriers; the sums of NV values travel together.
+// NT: 256 where one chunk of 2048 holds all lists (a launch of 1024 threads starts about 1 us later), 1024 otherwise.
+// excl[v] becomes the sum of all entries before this thread's, carry[v] the sum up to the end of the chunk.
+// ---------------------------------------------------------------------------------
+constexpr int SCAN_PER = 8, SCAN_SMALL = 256, SCAN_LARGE = 1024;
+
+template <int NT, int NV>
+__device__ inline void block_chunk_scan(const uint32_t (&sum)[NV], uint32_t (&excl)[NV], uint32_t (&carry)[NV],
+                                        uint32_t (*s_wave)[NT / 64]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t incl[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) incl[v] = sum[v];
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const uint32_t o = __shfl_up(incl[v], d, 64);
+      if (lane >= d) incl[v] += o;
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+    if (lane == 63) s_wave[v][wave] = incl[v];
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    // (lanes 0..15 hold the wavefronts' totals; every wavefront adds up those before it and all of them)
+    const uint32_t t = lane < NT / 64 ? s_wave[v][lane] : 0u;
+    const uint32_t before = wave_reduce_u32(lane < wave ? t : 0u, [](uint32_t a, uint32_t b) { return a + b; });
+    const uint32_t all = wave_reduce_u32(t, [](uint32_t a, uint32_t b) { return a + b; });
+    excl[v] = carry[v] + before + incl[v] - sum[v];
+    carry[v] += all;
+  }
+  __syncthreads();  // s_wave is free for the next chunk
+}
+
 __host__ __device__ inline int next_pow2(int v) {
   int p = 1;
   while (p < v) p <<= 1;

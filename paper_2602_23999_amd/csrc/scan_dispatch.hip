@@ -3,7 +3,7 @@
 #include <algorithm>
 #include <functional>
 
-#include "rq_internal.h"
+#include "rq_device.h"
 #include "rq_scan_args.h"
 #include "rq_small_batch.h"
 
@@ -19,58 +19,63 @@ __global__ void zero_i32_kernel(int32_t* p, int64_t n) {
 
 // item16 != nullptr (split search): also item16[c] = first work item of cluster c when an item is 16 pairs times one
 // segment, and mask_off[c] = first block of survivor bits of cluster c (a block per group of 16 pairs and tile).
-__global__ __launch_bounds__(256) void item_offsets_kernel(const int32_t* __restrict__ pair_off,
-                                                          const int32_t* __restrict__ tile_off,
-                                                          const int32_t* __restrict__ order, int n, int qw, int tseg,
-                                                          int segmax, int32_t* __restrict__ item_off,
-                                                          int32_t* __restrict__ item16, uint32_t* __restrict__ mask_off) {
-  __shared__ uint32_t part[3][256];
-  const int tid = threadIdx.x;
-  const int per = (n + 255) / 256;
-  const int s = tid * per, e = min(n, s + per);
-  // (entry i is about cluster i, or about the i-th longest cluster when an order is given)
-  auto counts = [&](int r, uint32_t& it, uint32_t& i16, uint32_t& mb) {
-    const int i = order ? order[r] : r;
-    const uint32_t pairs = (uint32_t)(pair_off[i + 1] - pair_off[i]), tiles = (uint32_t)(tile_off[i + 1] - tile_off[i]);
-    const uint32_t nseg = (uint32_t)seg_count((int)tiles, tseg, segmax), groups = (pairs + QM - 1) / QM;
-    it = ((pairs + qw - 1) / qw) * nseg;
-    i16 = groups * nseg;
-    mb = groups * tiles;
-  };
-  uint32_t sum[3] = {0, 0, 0};
-  for (int i = s; i < e; ++i) {
-    uint32_t a, b, c;
-    counts(i, a, b, c);
-    sum[0] += a; sum[1] += b; sum[2] += c;
-  }
-  const int nscan = item16 ? 3 : 1;
-  for (int v = 0; v < nscan; ++v) part[v][tid] = sum[v];
-  __syncthreads();
-  for (int d = 1; d < 256; d <<= 1) {
-    uint32_t o[3];
-    for (int v = 0; v < nscan; ++v) o[v] = (tid >= d) ? part[v][tid - d] : 0u;
-    __syncthreads();
-    for (int v = 0; v < nscan; ++v) part[v][tid] += o[v];
-    __syncthreads();
-  }
-  uint32_t run[3];
-  for (int v = 0; v < nscan; ++v) run[v] = part[v][tid] - sum[v];
-  for (int i = s; i < e; ++i) {
-    uint32_t a, b, c;
-    counts(i, a, b, c);
-    item_off[i] = (int32_t)run[0];
-    run[0] += a;
-    if (item16) {
-      item16[i] = (int32_t)run[1];
-      mask_off[i] = run[2];
-      run[1] += b; run[2] += c;
+// SPLIT is `item16 != nullptr`, ORDERED `order != nullptr`.  One workgroup whose time is its load latencies: a thread's
+// 8 entries are fetched together (8192 lists, split: 69 us when 256 threads walked 32 entries each; see SCAN_PER).
+template <int NT, bool SPLIT, bool ORDERED>
+__global__ __launch_bounds__(NT) void item_offsets_kernel(const int32_t* __restrict__ pair_off,
+                                                                   const int32_t* __restrict__ tile_off,
+                                                                   const int32_t* __restrict__ order, int n, int qw,
+                                                                   int tseg, int segmax, int32_t* __restrict__ item_off,
+                                                                   int32_t* __restrict__ item16,
+                                                                   uint32_t* __restrict__ mask_off) {
+  constexpr int NV = SPLIT ? 3 : 1;
+  __shared__ uint32_t s_wave[NV][NT / 64];
+  uint32_t carry[NV] = {0};
+  for (int base = 0; base < n; base += NT * SCAN_PER) {
+    const int s = base + (int)threadIdx.x * SCAN_PER;
+    // (entry i is about cluster i, or about the i-th longest cluster when an order is given; entries past the last
+    // are fetched as the last and count nothing)
+    uint32_t val[SCAN_PER][NV], sum[NV] = {0}, run[NV];
+    int po[SCAN_PER], pe[SCAN_PER], to[SCAN_PER], te[SCAN_PER];
+#pragma unroll
+    for (int e = 0; e < SCAN_PER; ++e) {
+      const int r = min(s + e, n - 1), c = ORDERED ? order[r] : r;
+      po[e] = pair_off[c]; pe[e] = pair_off[c + 1];
+      to[e] = tile_off[c]; te[e] = tile_off[c + 1];
+    }
+#pragma unroll
+    for (int e = 0; e < SCAN_PER; ++e) {
+      const bool in = s + e < n;
+      const uint32_t pairs = in ? (uint32_t)(pe[e] - po[e]) : 0u, tiles = (uint32_t)(te[e] - to[e]);
+      const uint32_t nseg = (uint32_t)seg_count((int)tiles, tseg, segmax);
+      val[e][0] = (qw == 1 ? pairs : (pairs + qw - 1) / (uint32_t)qw) * nseg;
+      if (SPLIT) {
+        const uint32_t groups = (pairs + QM - 1) / QM;
+        val[e][NV - 2] = groups * nseg;
+        val[e][NV - 1] = groups * tiles;
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) sum[v] += val[e][v];
+    }
+    block_chunk_scan<NT, NV>(sum, run, carry, s_wave);
+#pragma unroll
+    for (int e = 0; e < SCAN_PER; ++e) {
+      if (s + e < n) {
+        item_off[s + e] = (int32_t)run[0];
+        if (SPLIT) {
+          item16[s + e] = (int32_t)run[NV - 2];
+          mask_off[s + e] = run[NV - 1];
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) run[v] += val[e][v];
     }
   }
-  if (tid == 255) {
-    item_off[n] = (int32_t)part[0][255];
-    if (item16) {
-      item16[n] = (int32_t)part[1][255];
-      mask_off[n] = part[2][255];
+  if (threadIdx.x == 0) {
+    item_off[n] = (int32_t)carry[0];
+    if (SPLIT) {
+      item16[n] = (int32_t)carry[NV - 2];
+      mask_off[n] = carry[NV - 1];
     }
   }
 }
@@ -427,8 +432,15 @@ int launch_scan(const rabitq_index* ix, const rabitq_query_repr& repr, const flo
   // (one launch for the item table and, when the search is split, the two tables of its first half; a small batch's
   // list builder has written the item table already, with the same values)
   if (!ss.setup_done || split)
-    hipLaunchKernelGGL(item_offsets_kernel, dim3(1), dim3(256), 0, sst, pair_off, ix->tile_off, a.order, ix->nlist, qw,
-                       a.tseg, a.segmax, item_off, split ? item16 : nullptr, split ? mask_off : nullptr);
+  {
+    const bool small = ix->nlist <= SCAN_SMALL * SCAN_PER;
+    auto table = split ? (small ? item_offsets_kernel<SCAN_SMALL, true, false> : item_offsets_kernel<SCAN_LARGE, true, false>)
+                       : (small ? item_offsets_kernel<SCAN_SMALL, false, false> : item_offsets_kernel<SCAN_LARGE, false, false>);
+    if (a.order)  // (never together with the split search)
+      table = small ? item_offsets_kernel<SCAN_SMALL, false, true> : item_offsets_kernel<SCAN_LARGE, false, true>;
+    hipLaunchKernelGGL(table, dim3(1), dim3(small ? SCAN_SMALL : SCAN_LARGE), 0, sst, pair_off, ix->tile_off, a.order,
+                       ix->nlist, qw, a.tseg, a.segmax, item_off, item16, mask_off);
+  }
   if (!ss.setup_done && !ss.counters_clear) {
     if (int rc = launch_clear_counters(cand_cnt, nq * nprobe, sst)) return rc;
   }
