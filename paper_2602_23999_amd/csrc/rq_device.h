@@ -278,6 +278,89 @@ __device__ inline int wave_gather_selected(const uint64_t (&key)[R], uint64_t bo
 }
 
 // ---------------------------------------------------------------------------------
+// The same with 32-bit words (order-preserving float bits; all ones = absent) whose order of arrival, r then lane, is
+// the order of their positions, so that a tie goes to the earlier one.  Bisection of the value range; a step is one
+// compare per word on the vector unit and its bits counted on the scalar unit, and it ends as soon as a value splits
+// off exactly K words (about log2 of the word count steps, not 32).
+// Returns a bound with count(words <= bound) = *n_le >= K, where *n_le > K only if the bound is the K-th smallest
+// word itself and has equals.  At least K words must be present (1 <= K).
+// ---------------------------------------------------------------------------------
+template <int R>
+__device__ inline uint32_t wave_kth_ord(const uint32_t (&ord)[R], uint32_t K, uint32_t* n_le) {
+  uint32_t mn = 0xffffffffu, mx = 0u;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    mn = min(mn, ord[r]);
+    mx = max(mx, ord[r] == 0xffffffffu ? 0u : ord[r]);
+  }
+  uint32_t lo = wave_reduce_u32(mn, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+  uint32_t hi = wave_reduce_u32(mx, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+  auto count = [&](uint32_t v) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) c += (uint32_t)__popcll(__ballot(ord[r] <= v));
+    return c;
+  };
+  while (lo < hi) {
+    const uint32_t mid = lo + ((hi - lo) >> 1);
+    const uint32_t c = count(mid);
+    if (c == K) {
+      *n_le = K;
+      return mid;
+    }
+    if (c > K) hi = mid;
+    else lo = mid + 1;
+  }
+  *n_le = count(hi);
+  return hi;
+}
+
+// Value of the K-th smallest word (the bound above may lie between two words).
+template <int R>
+__device__ inline uint32_t wave_kth_value(const uint32_t (&ord)[R], uint32_t K) {
+  uint32_t n_le;
+  const uint32_t bound = wave_kth_ord<R>(ord, K, &n_le);
+  uint32_t mx = 0u;
+#pragma unroll
+  for (int r = 0; r < R; ++r) mx = max(mx, ord[r] <= bound ? ord[r] : 0u);
+  return wave_reduce_u32(mx, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+}
+
+// Appends the selected words and their positions to a list in LDS that this wavefront owns, keeping their order:
+// every word <= bound, or, where more than K words are (n_le > K), those below it and the first equals.  Returns K.
+// (the caller orders its own LDS accesses)
+template <int R>
+__device__ inline int wave_put_smallest(const uint32_t (&ord)[R], const uint32_t (&pos)[R], uint32_t bound, uint32_t n_le,
+                                        uint32_t K, uint32_t* s_ord, uint32_t* s_pos, int lane) {
+  uint32_t equals = 0xffffffffu;  // how many words equal to the bound may still be taken
+  if (n_le > K) {
+    uint32_t below = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) below += (uint32_t)__popcll(__ballot(ord[r] < bound));
+    equals = K - below;
+  }
+  const uint64_t lower = (1ull << lane) - 1ull;
+  uint32_t base = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    bool take = ord[r] <= bound;
+    if (n_le > K) {
+      const uint64_t eq = __ballot(ord[r] == bound);
+      if (ord[r] == bound) take = (uint32_t)__popcll(eq & lower) < equals;
+      equals -= min(equals, (uint32_t)__popcll(eq));
+    }
+    const uint64_t m = __ballot(take);
+    if (take) {
+      const uint32_t at = base + (uint32_t)__popcll(m & lower);
+      s_ord[at] = ord[r];
+      s_pos[at] = pos[r];
+    }
+    base += (uint32_t)__popcll(m);
+  }
+  return (int)base;
+}
+
+// ---------------------------------------------------------------------------------
 // Streaming selection of the K <= 64 smallest 64-bit keys by one wavefront, entirely in
 // registers: lane l holds the l-th smallest key seen so far.  The first 64 keys are sorted
 // across the lanes (bitonic network); afterwards a tile of 64 keys is compared with the
@@ -652,6 +735,28 @@ __device__ inline float refine_lane(const uint32_t* __restrict__ row, const floa
       const int w = w0 + i;
       if (w < LW) acc += dot_word<F>(row[w], qf + w * DPW);
     }
+  }
+  return acc;
+}
+
+// refine_lane's sum over words that refine_load fetched: the same products in the same grouping, bit for bit
+template <int F, int LW>
+__device__ inline float refine_lane_dot(const uint32_t (&w)[RefineShape<LW>::WPL], const float* qf, int t) {
+  constexpr int WPL = RefineShape<LW>::WPL, DPW = 32 / F;
+  const int w0 = t * WPL;
+  float acc = 0.f;
+  if (w0 >= LW) return 0.f;
+  if (WPL % 4 == 0 && LW % 4 == 0) {
+#pragma unroll
+    for (int c = 0; c < WPL / 4; ++c) {
+      const float* q = qf + (w0 + 4 * c) * DPW;
+      acc += dot_word<F>(w[4 * c], q) + dot_word<F>(w[4 * c + 1], q + DPW) + dot_word<F>(w[4 * c + 2], q + 2 * DPW) +
+             dot_word<F>(w[4 * c + 3], q + 3 * DPW);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < WPL; ++i)
+      if (w0 + i < LW) acc += dot_word<F>(w[i], qf + (w0 + i) * DPW);
   }
   return acc;
 }

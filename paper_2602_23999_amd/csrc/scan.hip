@@ -47,16 +47,16 @@ __device__ inline void stage_query(float* dst, const float* __restrict__ src, in
 }
 
 // ---------------------------------------------------------------------------------
-// Seeding: one workgroup (256 threads) per query.  In the nearest probed cluster with
+// Seeding of the lookup-table scan: one workgroup (256 threads) per query.  In the nearest probed cluster with
 // at least k vectors: the m = max(k, SEED_M) smallest (est1, position) -> refine -> tau = k-th
 // smallest refined estimate (B == 1: the k-th smallest est1).
 // ---------------------------------------------------------------------------------
 constexpr int SEED_CHUNK_TILES = 32;  // 2048 keys per selection round
 
-template <int W, int F, int M>  // M = 1: lookup-table inner product
+template <int W, int F>
 __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
   extern __shared__ unsigned char smem_raw[];
-  // layout: chunk keys [2048] u64 | best [kpad] u64 | out [kpad] u64 | qf [D] f32 | tables [8W][16] f16 (M = 1)
+  // layout: chunk keys [2048] u64 | best [kpad] u64 | out [kpad] u64 | qf [D] f32 | tables [8W][16] f16
   const int m = max(a.k, SEED_M);
   const int kpad = next_pow2(m);
   uint64_t* chunk = reinterpret_cast<uint64_t*>(smem_raw);
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
   }
   for (int i = tid; i < kpad; i += 256) best[i] = KEY_NONE;
   if (F > 0) stage_query(qf, a.q_stage + q * a.D, a.D, tid, 256);
-  if (M == 1) stage_lut(lut_s, a.lut + q * (int64_t)W * 128, W, tid, 256);
+  stage_lut(lut_s, a.lut + q * (int64_t)W * 128, W, tid, 256);
   __syncthreads();
   const int rank = s_rank;
   if (rank < 0) {
@@ -110,10 +110,7 @@ __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
     return;
   }
   const float G = s_G;
-  const float dl = a.delta[q];
-  const float be = 0.5f * dl * (float)a.sum_qhat[q];
   const float hsq = 0.5f * a.sum_q[q];
-  const_u32_ptr pl = (const_u32_ptr)(a.planes + q * 4 * W);
   const int t0 = s_t0, t1 = s_t1;
 
   for (int tb = t0; tb < t1; tb += SEED_CHUNK_TILES) {
@@ -125,8 +122,7 @@ __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
       for (int w = 0; w < W; ++w) cw[w] = a.short_codes[((int64_t)tile * W + w) * TILE + lane];
       const float fa = a.short_factors[((int64_t)tile * 3 + 0) * TILE + lane];
       const float fr = a.short_factors[((int64_t)tile * 3 + 1) * TILE + lane];
-      int I;
-      const float e1 = (M == 1) ? G + fa + fr * (ip_lut_of<W>(cw, lut_s) - hsq) : est1_of<W>(cw, pl, fa, fr, G, dl, be, &I);
+      const float e1 = G + fa + fr * (ip_lut_of<W>(cw, lut_s) - hsq);
       const bool real = a.ids[(int64_t)tile * TILE + lane] >= 0;
       chunk[tl * TILE + lane] = real ? make_key(e1, (uint32_t)((tile - t0) * TILE + lane)) : KEY_NONE;
     }
@@ -167,16 +163,30 @@ __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
 }
 
 // ---------------------------------------------------------------------------------
-// Seeding with one wavefront per query (k <= 64, popcount inner products): the same
-// selection and refinement as seed_kernel, but the m <= 64 smallest (est1, position) keys are
-// kept in registers while the cluster streams by, so there is no LDS and no barrier.
+// Seeding with one wavefront per query (popcount inner products, every k): in the nearest probed cluster with at
+// least k vectors the m = max(k, SEED_M) <= 128 smallest (est1, position) are refined and tau is the k-th smallest
+// refined estimate.  The m smallest are found by value: a bisection over the estimates of the first R tiles, held in
+// registers, gives a bound, and a later vector matters only if it is below it; those few are appended to a list in
+// LDS, cut back to m by another bisection when it is full.  (Keeping a sorted list in registers instead, one serial
+// insertion of ~25 instructions per vector that beats the current m-th, was what bound this kernel: 10^4 queries,
+// lists of ~1000 x 128-d, 4 bits: 62 us, now 57, what is
+// left being the reads of the lists; k = 100 needed a workgroup-wide radix select: 10^4 queries, lists of ~490
+// x 96-d, 3 bits: 217 us, now 70.)
+// SPLIT (few queries): the four wavefronts of a workgroup share one query; each takes a quarter of the cluster's tiles
+// and of the refinement, the first one the selections in between.
 // ---------------------------------------------------------------------------------
-// SPLIT (small batches): the four wavefronts of a workgroup share one query, each streaming a quarter of the
-// cluster; their sorted lists meet in LDS and the first wavefront finishes alone.
+constexpr int SEED_MAX = 128;       // seeds of a query at most: max(RABITQ_MAX_K, SEED_M)
+constexpr int SEED_LIST = 256;      // entries of a wavefront's list
+static_assert(RABITQ_MAX_K <= SEED_MAX && SEED_M <= SEED_MAX, "a list of seeds holds 128");
+struct SeedScratch {
+  uint32_t ord[4][SEED_LIST], pos[4][SEED_LIST];  // one list per wavefront of the workgroup, in order of position
+  int cnt[4];
+};
+
 // The work of one query (SPLIT: of the four wavefronts that share it; every one of them must call, and they meet
-// at one barrier unless no probed cluster has k vectors, which all four find alike).
+// at barriers unless no probed cluster has k vectors, which all four find alike).
 template <int W, int F, bool SPLIT>
-__device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, int wave, uint64_t* s_lists) {
+__device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, int wave, SeedScratch& sh) {
   // Lane j looks at probe j: everything the chosen probe contributes (cluster, coarse term, tile range) is fetched
   // for all probes at once and read from the chosen lane, so the walk to the first tile is two dependent loads deep.
   int rank = -1, t0 = 0, t1 = 0, n_c = 0;
@@ -193,7 +203,7 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
       const int l = __ffsll((unsigned long long)m) - 1;
       rank = b + l;
       G = __shfl(g, l, 64);
-      t0 = __shfl(to0, l, 64);  // positions in the keys are relative to the cluster's first tile
+      t0 = __shfl(to0, l, 64);  // positions are relative to the cluster's first tile
       t1 = __shfl(to1, l, 64);
       n_c = __shfl(sz, l, 64);
     }
@@ -216,11 +226,12 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
     tw0 = min(t0 + wave * per, t1);
     t1 = min(tw0 + per, t1);
   }
-  const int m = max(a.k, SEED_M);  // <= 64
-  WaveTopK top;
-  top.v = KEY_NONE;
+  const uint32_t m = (uint32_t)max(a.k, SEED_M);
+  uint32_t *lo = sh.ord[wave], *lp = sh.pos[wave];
+  int cnt = 0;
+  uint32_t limit = 0xfffffffeu;  // no vector above this can be among the m smallest
   // U tiles are requested together so that their load latencies overlap (tiles past the end
-  // re-read the last tile and contribute no key)
+  // re-read the last tile and contribute nothing)
   constexpr int U = (W <= 4) ? 4 : (W <= 8 ? 2 : 1);
   // est1 of U tiles starting at tb, as order-preserving words (all ones where there is no vector)
   auto estimate = [&](int tb, uint32_t (&ord)[U]) {
@@ -243,84 +254,139 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
       ord[u] = real[u] ? f2ord(e1) : 0xffffffffu;
     }
   };
-  // The first R tiles are estimated before anything is selected: the 64 per-lane minima (distinct vectors) start
-  // the sorted list, so its m-th key is small from the outset and few of the remaining keys have to be inserted.
+  // cuts the list to its m smallest
+  auto cut = [&]() {
+    constexpr int RL = SEED_LIST / 64;
+    uint32_t o[RL], p[RL];
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < RL; ++r) {
+      const int i = r * 64 + lane;
+      o[r] = i < cnt ? lo[i] : 0xffffffffu;
+      p[r] = i < cnt ? lp[i] : 0u;
+    }
+    wave_sync();
+    uint32_t n_le;
+    limit = wave_kth_ord<RL>(o, m, &n_le);
+    cnt = wave_put_smallest<RL>(o, p, limit, n_le, m, lo, lp, lane);
+  };
   constexpr int R = (W <= 4) ? 16 : (W <= 8 ? 8 : 4);
   if (tw0 < t1) {
-    const uint32_t pos0 = (uint32_t)(tw0 - t0) * TILE + lane;
-    uint32_t ord[R];
+    {
+      uint32_t ord[R], pos[R];
+      uint32_t present = 0;
 #pragma unroll
-    for (int c2 = 0; c2 < R; c2 += U) {
-      uint32_t o[U];
-      estimate(tw0 + c2, o);
+      for (int c2 = 0; c2 < R; c2 += U) {
+        uint32_t o[U];
+        if (tw0 + c2 < t1) {
+          estimate(tw0 + c2, o);
+        } else {
 #pragma unroll
-      for (int u = 0; u < U; ++u) ord[c2 + u] = (tw0 + c2 + u < t1) ? o[u] : 0xffffffffu;
-    }
-    uint32_t mo = ord[0];
-    int mr = 0;
+          for (int u = 0; u < U; ++u) o[u] = 0xffffffffu;
+        }
 #pragma unroll
-    for (int r = 1; r < R; ++r)
-      if (ord[r] < mo) { mo = ord[r]; mr = r; }  // ties keep the lower position, as the key order does
-    top.init_sorted(mo == 0xffffffffu ? KEY_NONE : (((uint64_t)mo << 32) | (pos0 + (uint32_t)(mr * TILE))), lane);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const bool take = r != mr && ord[r] != 0xffffffffu;
-      top.push_tile(take ? (((uint64_t)ord[r] << 32) | (pos0 + (uint32_t)(r * TILE))) : KEY_NONE, m, lane);
+        for (int u = 0; u < U; ++u) {
+          ord[c2 + u] = o[u];
+          pos[c2 + u] = (uint32_t)((tw0 + c2 + u - t0) * TILE + lane);
+          present += (uint32_t)__popcll(__ballot(o[u] != 0xffffffffu));
+        }
+      }
+      uint32_t n_le = present;
+      if (present > m) limit = wave_kth_ord<R>(ord, m, &n_le);
+      cnt = wave_put_smallest<R>(ord, pos, limit, n_le, min(m, present), lo, lp, lane);
     }
     for (int tb = tw0 + R; tb < t1; tb += U) {
       uint32_t o[U];
       estimate(tb, o);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const uint64_t key = o[u] != 0xffffffffu ? (((uint64_t)o[u] << 32) | (uint32_t)((tb + u - t0) * TILE + lane)) : KEY_NONE;
-        top.push_tile(key, m, lane);
+        uint64_t mk = __ballot(o[u] <= limit);
+        if (mk == 0ull) continue;
+        if (cnt + __popcll(mk) > SEED_LIST) {
+          cut();  // (m <= 128: a tile always fits afterwards)
+          mk = __ballot(o[u] <= limit);  // the cut has lowered the limit
+        }
+        if (o[u] <= limit) {
+          const int at = cnt + __popcll(mk & ((1ull << lane) - 1ull));
+          lo[at] = o[u];
+          lp[at] = (uint32_t)((tb + u - t0) * TILE + lane);
+        }
+        cnt += __popcll(mk);
       }
     }
+    if (cnt > (int)m) cut();
   }
-  if (SPLIT) {  // the other wavefronts hand their lists to the first and leave
-    if (wave > 0) s_lists[(wave - 1) * 64 + lane] = top.v;
+  if (SPLIT) {  // the first wavefront selects from the four lists, in order of position
+    if (lane == 0) sh.cnt[wave] = cnt;
     __syncthreads();
-    if (wave > 0) return;
+    if (wave == 0) {
+      constexpr int RL = SEED_MAX / 64;
+      uint32_t o[4 * RL], p[4 * RL], present = 0;
 #pragma unroll
-    for (int w2 = 0; w2 < 3; ++w2) top.push_tile(s_lists[w2 * 64 + lane], m, lane);
+      for (int w2 = 0; w2 < 4; ++w2) {
+        const int n = sh.cnt[w2];
+        present += (uint32_t)n;
+#pragma unroll
+        for (int r = 0; r < RL; ++r) {
+          const int i = r * 64 + lane;
+          o[w2 * RL + r] = i < n ? sh.ord[w2][i] : 0xffffffffu;
+          p[w2 * RL + r] = i < n ? sh.pos[w2][i] : 0u;
+        }
+      }
+      wave_sync();
+      uint32_t n_le = present, bound = 0xfffffffeu;
+      if (present > m) bound = wave_kth_ord<4 * RL>(o, m, &n_le);
+      cnt = wave_put_smallest<4 * RL>(o, p, bound, n_le, min(m, present), sh.ord[0], sh.pos[0], lane);
+      if (lane == 0) sh.cnt[0] = cnt;
+    }
+    __syncthreads();
+    cnt = __builtin_amdgcn_readfirstlane(sh.cnt[0]);
+    lo = sh.ord[0];
+    lp = sh.pos[0];
+  } else {
+    wave_sync();
   }
-  if (F == 0) {
-    const uint64_t kth = readlane_u64(top.v, a.k - 1);
-    if (lane == 0) a.tau_out[q] = ord2f((uint32_t)(kth >> 32));
-    return;
+  if (F > 0) {
+    // refine the seeds (fewer than m if the cluster is smaller), GL lanes per seed; a refined estimate takes the
+    // place of the seed's 1-bit estimate.  Nothing is fetched under a condition (an absent seed repeats the last
+    // one), and a round's words are requested before the previous round is worked on.
+    constexpr int FF = (F > 0 ? F : 8), LW = W * FF, GL = RefineShape<LW>::G, NS = RefineShape<LW>::NS;
+    const int grp = lane / GL, t = lane % GL, step = SPLIT ? 4 * NS : NS;
+    const float csq = a.cB * a.sum_q[q];
+    struct Seed {
+      uint32_t w[RefineShape<LW>::WPL];
+      float2 lf;
+    };
+    auto request = [&](int base, Seed& s) {
+      const int64_t slot = (int64_t)t0 * TILE + lp[min(base + grp, cnt - 1)];
+      refine_load<FF, LW>(a.long_codes + slot * LW, t, s.w);
+      s.lf = *reinterpret_cast<const float2*>(a.long_factors + 2 * slot);
+    };
+    Seed nxt;
+    const int first = SPLIT ? wave * NS : 0;
+    if (first < cnt) request(first, nxt);
+    for (int base = first; base < cnt; base += step) {
+      const Seed cur = nxt;
+      if (base + step < cnt) request(base + step, nxt);
+      const float ip = group_sum<GL>(refine_lane_dot<FF, LW>(cur.w, a.q_stage + q * a.D, t));
+      const float eB = G + cur.lf.x + cur.lf.y * (ip - csq);
+      if (t == 0 && base + grp < cnt) lo[base + grp] = f2ord(eB);
+    }
+    if (SPLIT) __syncthreads();
+    else wave_sync();
   }
-  // refine the m seeds (fewer if the cluster is smaller), GL lanes per seed; lane i ends up with the
-  // refined key of seed i, and the k-th smallest of those is tau
-  constexpr int FF = (F > 0 ? F : 8), LW = W * FF, GL = RefineShape<LW>::G, NS = RefineShape<LW>::NS;
-  const int grp = lane / GL, t = lane % GL;
-  const float csq = a.cB * a.sum_q[q];
-  uint64_t rkey = KEY_NONE;
-  for (int base = 0; base < m; base += NS) {
-    const int sidx = base + grp;
-    const uint64_t skey = shfl_u64(top.v, min(sidx, 63));
-    const bool valid = sidx < m && skey != KEY_NONE;
-    // nothing here is fetched under a condition (an absent seed reads the cluster's first slot instead), so the
-    // code words and the factors of a round are requested together
-    const int64_t slot = (int64_t)t0 * TILE + (valid ? (uint32_t)skey : 0u);
-    const float2 lf = *reinterpret_cast<const float2*>(a.long_factors + 2 * slot);
-    const float part = refine_lane<FF, LW>(a.long_codes + slot * LW, a.q_stage + q * a.D, t);
-    const float ip = group_sum<GL>(part);
-    const float eB = G + lf.x + lf.y * (ip - csq);
-    // seed base + g was refined by lanes g*GL ..; hand its estimate to lane base + g
-    const int g = (lane - base) & (NS - 1);
-    const float mine = __shfl(eB, g * GL, 64);
-    const bool mine_valid = __shfl((int)valid, g * GL, 64) != 0;
-    if (lane >= base && lane < base + NS && mine_valid) rkey = make_key(mine, (uint32_t)lane);
-  }
-  WaveTopK fin;
-  fin.init_sorted(rkey, lane);
-  const uint64_t kth = readlane_u64(fin.v, a.k - 1);
-  if (lane == 0) a.tau_out[q] = fminf(ord2f((uint32_t)(kth >> 32)), 3.402823466e+38f);
+  if (SPLIT && wave > 0) return;
+  constexpr int RK = SEED_MAX / 64;
+  uint32_t o[RK];
+#pragma unroll
+  for (int r = 0; r < RK; ++r) o[r] = r * 64 + lane < cnt ? lo[r * 64 + lane] : 0xffffffffu;
+  const float kth = ord2f(wave_kth_value<RK>(o, (uint32_t)a.k));
+  if (lane == 0) a.tau_out[q] = F == 0 ? kth : fminf(kth, 3.402823466e+38f);
 }
 
 template <int W, int F, bool SPLIT>
 __global__ __launch_bounds__(256) void seed_wave_kernel(ScanArgs a, int64_t nq) {
-  __shared__ uint64_t s_lists[SPLIT ? 3 * 64 : 1];
+  __shared__ SeedScratch s_seed;
   // (the wavefront index is the same in all lanes: saying so lets everything indexed by the query be fetched
   // through the scalar cache)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -331,7 +397,7 @@ __global__ __launch_bounds__(256) void seed_wave_kernel(ScanArgs a, int64_t nq) 
   const int blk = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
   const int64_t q = SPLIT ? (int64_t)blk : (int64_t)blk * 4 + wave;
   if (q >= nq) return;
-  seed_wave_body<W, F, SPLIT>(a, q, lane, wave, s_lists);
+  seed_wave_body<W, F, SPLIT>(a, q, lane, wave, s_seed);
 }
 
 // ---------------------------------------------------------------------------------
@@ -342,7 +408,7 @@ __global__ __launch_bounds__(256) void seed_wave_kernel(ScanArgs a, int64_t nq) 
 // ---------------------------------------------------------------------------------
 template <int W, int F>
 __global__ __launch_bounds__(256) void small_select_seed_kernel(ScanArgs a, SmallSelectArgs b) {
-  __shared__ uint64_t s_lists[3 * 64];
+  __shared__ SeedScratch s_seed;
   __shared__ uint32_t s_pairs[256], s_items[256];
   __shared__ int s_last;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
@@ -362,7 +428,7 @@ __global__ __launch_bounds__(256) void small_select_seed_kernel(ScanArgs a, Smal
   }
   __syncthreads();  // the probes are in memory for the other wavefronts of the workgroup
   if (b.do_seed) {
-    seed_wave_body<W, F, true>(a, q, lane, wave, s_lists);
+    seed_wave_body<W, F, true>(a, q, lane, wave, s_seed);
   } else if (tid == 0) {
     a.tau_out[q] = 3.402823466e+38f;
   }
@@ -1215,14 +1281,12 @@ static void launch_seed_wf(const ScanArgs& a, int impl, int64_t nq, hipStream_t 
   const int kpad = next_pow2(std::max(a.k, SEED_M));
   const size_t smem = (size_t)(SEED_CHUNK_TILES * TILE + 2 * kpad) * sizeof(uint64_t) + (size_t)a.D * sizeof(float);
   if (impl == 2)
-    hipLaunchKernelGGL((seed_kernel<W, F, 1>), dim3((unsigned)nq), dim3(256), smem + (size_t)W * 256, st, a);
-  else if (a.k <= 64 && nq <= 2048)  // few queries: four wavefronts per query
+    hipLaunchKernelGGL((seed_kernel<W, F>), dim3((unsigned)nq), dim3(256), smem + (size_t)W * 256, st, a);
+  else if (nq <= 2048)  // few queries: four wavefronts per query
     hipLaunchKernelGGL((seed_wave_kernel<W, F, true>), dim3((unsigned)((nq + 7) / 8 * 8)), dim3(256), 0, st, a, nq);
-  else if (a.k <= 64)
+  else
     hipLaunchKernelGGL((seed_wave_kernel<W, F, false>), dim3((unsigned)(((nq + 3) / 4 + 7) / 8 * 8)), dim3(256), 0, st, a,
                        nq);
-  else
-    hipLaunchKernelGGL((seed_kernel<W, F, 0>), dim3((unsigned)nq), dim3(256), smem, st, a);
 }
 
 template <int W, int F>
