@@ -255,28 +255,6 @@ __device__ inline uint64_t wave_kth_bound(const uint64_t (&key)[R], int K) {
   return prefix;
 }
 
-// Packs the keys <= bound of every lane into out[0..) in LDS (any order) and pads the rest
-// of out[0..Kpad) with KEY_NONE.  For a single-wavefront workgroup.  Returns the count.
-template <int R>
-__device__ inline int wave_gather_selected(const uint64_t (&key)[R], uint64_t bound, uint64_t* out, int Kpad) {
-  const int lane = threadIdx.x & 63;
-  for (int i = lane; i < Kpad; i += 64) out[i] = KEY_NONE;
-  __syncthreads();
-  int base = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const bool sel = key[r] <= bound && key[r] != KEY_NONE;
-    const uint64_t m = __ballot(sel);
-    if (sel) {
-      const int pos = base + __popcll(m & ((1ull << lane) - 1ull));
-      if (pos < Kpad) out[pos] = key[r];
-    }
-    base += __popcll(m);
-  }
-  __syncthreads();
-  return base;
-}
-
 // ---------------------------------------------------------------------------------
 // The same with 32-bit words (order-preserving float bits; all ones = absent) whose order of arrival, r then lane, is
 // the order of their positions, so that a tie goes to the earlier one.  Bisection of the value range; a step is one
@@ -326,12 +304,10 @@ __device__ inline uint32_t wave_kth_value(const uint32_t (&ord)[R], uint32_t K) 
   return wave_reduce_u32(mx, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
 }
 
-// Appends the selected words and their positions to a list in LDS that this wavefront owns, keeping their order:
-// every word <= bound, or, where more than K words are (n_le > K), those below it and the first equals.  Returns K.
-// (the caller orders its own LDS accesses)
-template <int R>
-__device__ inline int wave_put_smallest(const uint32_t (&ord)[R], const uint32_t (&pos)[R], uint32_t bound, uint32_t n_le,
-                                        uint32_t K, uint32_t* s_ord, uint32_t* s_pos, int lane) {
+// Hands the selected words out in their order, put(place, r) for every word <= bound, or, where more than K words are
+// (n_le > K), for those below it and the first equals.  Returns K.  (the caller orders its own LDS accesses)
+template <int R, typename Put>
+__device__ inline int wave_put_smallest(const uint32_t (&ord)[R], uint32_t bound, uint32_t n_le, uint32_t K, int lane, Put put) {
   uint32_t equals = 0xffffffffu;  // how many words equal to the bound may still be taken
   if (n_le > K) {
     uint32_t below = 0;
@@ -350,11 +326,7 @@ __device__ inline int wave_put_smallest(const uint32_t (&ord)[R], const uint32_t
       equals -= min(equals, (uint32_t)__popcll(eq));
     }
     const uint64_t m = __ballot(take);
-    if (take) {
-      const uint32_t at = base + (uint32_t)__popcll(m & lower);
-      s_ord[at] = ord[r];
-      s_pos[at] = pos[r];
-    }
+    if (take) put((int)(base + (uint32_t)__popcll(m & lower)), r);
     base += (uint32_t)__popcll(m);
   }
   return (int)base;

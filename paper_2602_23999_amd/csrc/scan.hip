@@ -268,12 +268,12 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
     wave_sync();
     uint32_t n_le;
     limit = wave_kth_ord<RL>(o, m, &n_le);
-    cnt = wave_put_smallest<RL>(o, p, limit, n_le, m, lo, lp, lane);
+    cnt = wave_put_smallest<RL>(o, limit, n_le, m, lane, [&](int at, int r) { lo[at] = o[r]; lp[at] = p[r]; });
   };
   constexpr int R = (W <= 4) ? 16 : (W <= 8 ? 8 : 4);
   if (tw0 < t1) {
     {
-      uint32_t ord[R], pos[R];
+      uint32_t ord[R];
       uint32_t present = 0;
 #pragma unroll
       for (int c2 = 0; c2 < R; c2 += U) {
@@ -287,13 +287,15 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           ord[c2 + u] = o[u];
-          pos[c2 + u] = (uint32_t)((tw0 + c2 + u - t0) * TILE + lane);
           present += (uint32_t)__popcll(__ballot(o[u] != 0xffffffffu));
         }
       }
       uint32_t n_le = present;
       if (present > m) limit = wave_kth_ord<R>(ord, m, &n_le);
-      cnt = wave_put_smallest<R>(ord, pos, limit, n_le, min(m, present), lo, lp, lane);
+      cnt = wave_put_smallest<R>(ord, limit, n_le, min(m, present), lane, [&](int at, int r) {
+        lo[at] = ord[r];
+        lp[at] = (uint32_t)((tw0 + r - t0) * TILE + lane);
+      });
     }
     for (int tb = tw0 + R; tb < t1; tb += U) {
       uint32_t o[U];
@@ -336,7 +338,10 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
       wave_sync();
       uint32_t n_le = present, bound = 0xfffffffeu;
       if (present > m) bound = wave_kth_ord<4 * RL>(o, m, &n_le);
-      cnt = wave_put_smallest<4 * RL>(o, p, bound, n_le, min(m, present), sh.ord[0], sh.pos[0], lane);
+      cnt = wave_put_smallest<4 * RL>(o, bound, n_le, min(m, present), lane, [&](int at, int r) {
+        sh.ord[0][at] = o[r];
+        sh.pos[0][at] = p[r];
+      });
       if (lane == 0) sh.cnt[0] = cnt;
     }
     __syncthreads();

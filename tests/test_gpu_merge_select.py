@@ -1,0 +1,39 @@
+"""The per-query merge around the edges of its two kernels: k up to 64 and above, fewer and more than 64 lists (one and
+several rounds of lists), empty lists, full ones, fewer candidates than k, and equal distances, which go to the lower id."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import build
+from paper_2602_23999_amd import rabitq
+
+from gpu_helpers import upload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("k", [1, 10, 64, 65, 100, 128])
+@pytest.mark.parametrize("nprobe,fill", [(1, "full"), (63, "some"), (64, "some"), (65, "full"), (130, "few"), (130, "full")])
+def test_merge_selects_the_k_smallest(k, nprobe, fill):
+    nq, nlist = 9, 130
+    rng = np.random.default_rng(1000 * k + nprobe)
+    C = rng.standard_normal((nlist, 32))
+    gi = upload(build.build_index((C + 0.1).astype(np.float32), nlist, 1, centroids=C))
+    cap = rabitq.load_library().rabitq_cand_capacity(k)
+    cnt = {"full": np.full((nq, nprobe), cap), "some": rng.integers(0, 40, (nq, nprobe)),
+           "few": (rng.random((nq, nprobe)) < 0.2).astype(int)}[fill].astype(np.int32)
+    cnt[0] = 0                                   # a query without candidates
+    d = rng.integers(0, 200, (nq, nprobe, cap)).astype(np.float32) - 20.0      # many equal distances
+    ids = np.stack([rng.permutation(nprobe * cap) for _ in range(nq)]).reshape(nq, nprobe, cap)
+    bits = d.view(np.uint32)
+    order = np.where(bits >> 31, ~bits, bits | np.uint32(1 << 31)).astype(np.uint64)
+    keys = (order << np.uint64(32)) | ids.astype(np.uint64)
+    got_i, got_d = gi.merge(torch.from_numpy(keys.view(np.int64)).cuda(), torch.from_numpy(cnt).cuda(), nq, k, nprobe)
+    got_i, got_d = got_i.cpu().numpy(), got_d.cpu().numpy()
+    for q in range(nq):
+        have = np.arange(cap)[None, :] < cnt[q][:, None]
+        best = np.lexsort((ids[q][have], d[q][have]))[:k]
+        n = len(best)
+        assert np.array_equal(got_i[q, :n], ids[q][have][best]) and np.array_equal(got_d[q, :n], d[q][have][best])
+        assert np.all(got_i[q, n:] == -1) and np.all(np.isinf(got_d[q, n:]))
+    gi.close()
