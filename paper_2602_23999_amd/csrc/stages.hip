@@ -302,6 +302,7 @@ int launch_build_lists(const int32_t* probe_ids, int64_t nq, int nprobe, int nli
 // key into a sorted register list 43.)
 // ---------------------------------------------------------------------------------
 constexpr int MERGE_BUF = 512;
+static_assert(RABITQ_MAX_K <= 128 && RABITQ_MAX_K + TILE <= MERGE_BUF, "k keys and a step of 64 fit the buffer; k are sorted in 128 places");
 
 __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__ cand_keys,
                                                    const int32_t* __restrict__ cand_cnt, int64_t nq, int k, int cap,
@@ -318,8 +319,9 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__
   const int32_t* counts = cand_cnt + q * nprobe;
   const uint64_t lower = (1ull << lane) - 1ull;
   int cnt = 0;
-  uint64_t limit = KEY_NONE - 1ull;  // no key above this can be among the k best
-  // cuts the buffer to its k best
+  uint64_t limit = KEY_NONE;  // only keys below this can be among the k best
+  // Cuts the buffer to its k best.  Keys may repeat (a caller of the stage may hand in what it likes): of several at the
+  // last place only as many stay as there is room for, and another copy of them is no better, so the limit excludes it.
   auto cut = [&]() {
     constexpr int RB = MERGE_BUF / 64;
     uint64_t key[RB];
@@ -333,18 +335,26 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__
     wave_sync();
     uint32_t n_le;
     const uint32_t bound = wave_kth_ord<RB>(ord, (uint32_t)k, &n_le);
-    limit = ((uint64_t)bound << 32) | 0xffffffffu;
+    uint64_t last = ((uint64_t)bound << 32) | 0xffffffffu;  // the k-th smallest key, or a value between it and the next
     // (equal distances at the last place: the lower ids)
-    if (n_le != (uint32_t)k) limit = wave_kth_bound<RB>(key, k);
-    limit = limit < KEY_NONE - 1ull ? limit : KEY_NONE - 1ull;
-    int base = 0;
+    if (n_le != (uint32_t)k) last = wave_kth_bound<RB>(key, k);
+    int at = 0;
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-      const uint64_t m = __ballot(key[r] <= limit);
-      if (key[r] <= limit) buf[base + __popcll(m & lower)] = key[r];
-      base += __popcll(m);
+      const uint64_t m = __ballot(key[r] < last);
+      if (key[r] < last) buf[at + __popcll(m & lower)] = key[r];
+      at += __popcll(m);
     }
-    cnt = base;
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const uint64_t m = __ballot(key[r] == last);
+      const int place = at + __popcll(m & lower);
+      if (key[r] == last && place < k) buf[place] = key[r];
+      at += __popcll(m);
+    }
+    const uint64_t next = at > k ? last : last + 1ull;
+    limit = next < limit ? next : limit;
+    cnt = min(at, k);
     wave_sync();
   };
   for (int jb = 0; jb < nprobe; jb += 64) {
@@ -376,13 +386,13 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__
       for (int u = 0; u < 4; ++u) {
         if (i0 + u * 64 >= total) break;
         if (i0 + u * 64 + lane >= total) kk[u] = KEY_NONE;
-        uint64_t m = __ballot(kk[u] <= limit);
+        uint64_t m = __ballot(kk[u] < limit);
         if (m == 0ull) continue;
         if (cnt + __popcll(m) > MERGE_BUF) {
-          cut();  // (k <= 128: a step of 64 keys always fits afterwards)
-          m = __ballot(kk[u] <= limit);
+          cut();  // (k keys are left: a step of 64 always fits)
+          m = __ballot(kk[u] < limit);
         }
-        if (kk[u] <= limit) buf[cnt + __popcll(m & lower)] = kk[u];
+        if (kk[u] < limit) buf[cnt + __popcll(m & lower)] = kk[u];
         cnt += __popcll(m);
       }
     }

@@ -37,3 +37,39 @@ def test_merge_selects_the_k_smallest(k, nprobe, fill):
         assert np.array_equal(got_i[q, :n], ids[q][have][best]) and np.array_equal(got_d[q, :n], d[q][have][best])
         assert np.all(got_i[q, n:] == -1) and np.all(np.isinf(got_d[q, n:]))
     gi.close()
+
+
+@pytest.mark.parametrize("k", [1, 10, 64, 65, 100, 128])
+@pytest.mark.parametrize("nprobe", [16, 64, 130])
+@pytest.mark.parametrize("kind", ["one", "smaller after copies", "copies at the last place"])
+def test_merge_of_repeated_keys(k, nprobe, kind):
+    # the stage takes whatever keys its caller hands it: copies of a key count like any other keys, also more of them
+    # than the kernel's buffer of 512 holds
+    nq, nlist = 5, 130
+    rng = np.random.default_rng(1000 * k + nprobe)
+    C = rng.standard_normal((nlist, 32))
+    gi = upload(build.build_index((C + 0.1).astype(np.float32), nlist, 1, centroids=C))
+    cap = rabitq.load_library().rabitq_cand_capacity(k)
+    total = nprobe * cap
+    val = np.full((nq, total), 7.0, np.float32)
+    ids = np.full((nq, total), 3)
+    if kind == "smaller after copies":
+        for q in range(nq):       # fewer better keys than k, all of them behind at least 600 copies
+            late = 600 + rng.permutation(total - 600)[:max(1, k - 1 - q)]
+            val[q, late], ids[q, late] = 1.0 + rng.random(len(late)), late
+    elif kind == "copies at the last place":
+        val[:] = 100.0 + rng.random((nq, total))
+        ids[:] = rng.permutation(total)[None]
+        for q in range(nq):       # k - 1 better keys, then many copies of the k-th, somewhere among worse ones
+            at = rng.permutation(total)
+            val[q, at[:k - 1]], (val[q, at[k - 1:k + 700]], ids[q, at[k - 1:k + 700]]) = rng.random(k - 1), (50.0, 11)
+    bits = val.view(np.uint32)
+    order = np.where(bits >> 31, ~bits, bits | np.uint32(1 << 31)).astype(np.uint64)
+    keys = (order << np.uint64(32)) | ids.astype(np.uint64)
+    cnt = torch.full((nq, nprobe), cap, dtype=torch.int32, device="cuda")
+    got_i, got_d = gi.merge(torch.from_numpy(keys.view(np.int64)).cuda(), cnt, nq, k, nprobe)
+    got_i, got_d = got_i.cpu().numpy(), got_d.cpu().numpy()
+    for q in range(nq):
+        best = np.lexsort((ids[q], val[q]))[:k]
+        assert np.array_equal(got_i[q], ids[q][best]) and np.array_equal(got_d[q], val[q][best]), q
+    gi.close()
