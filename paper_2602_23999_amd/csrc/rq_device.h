@@ -293,7 +293,8 @@ __device__ inline uint32_t wave_kth_ord(const uint32_t (&ord)[R], uint32_t K, ui
   return hi;
 }
 
-// Value of the K-th smallest word (the bound above may lie between two words).
+// Value of the K-th smallest word (the bound above may lie between two words); all ones if fewer than K are present
+// (an estimate that is a NaN of all ones reads as absent).
 template <int R>
 __device__ inline uint32_t wave_kth_value(const uint32_t (&ord)[R], uint32_t K) {
   uint32_t n_le;
@@ -301,7 +302,8 @@ __device__ inline uint32_t wave_kth_value(const uint32_t (&ord)[R], uint32_t K) 
   uint32_t mx = 0u;
 #pragma unroll
   for (int r = 0; r < R; ++r) mx = max(mx, ord[r] <= bound ? ord[r] : 0u);
-  return wave_reduce_u32(mx, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+  mx = wave_reduce_u32(mx, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+  return n_le < K ? 0xffffffffu : mx;
 }
 
 // Hands the selected words out in their order, put(place, r) for every word <= bound, or, where more than K words are

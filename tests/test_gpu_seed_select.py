@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from oracle import build, search
+from paper_2602_23999_amd import rabitq
 
 from gpu_helpers import key_scale, oracle_stages, to_dev, upload
 
@@ -37,4 +38,32 @@ def test_seeding_selects_what_the_oracle_selects(D, B, size):
         bad = np.abs(few.cpu().numpy() - want) > 1e-4 * (np.abs(want) + scale)
         # (another seed may be taken where two 1-bit estimates at the last rank are equal up to their rounding)
         assert bad.sum() <= 1, (k, few.cpu().numpy(), want)
+    gi.close()
+
+
+@pytest.mark.parametrize("payload", [0x7fc00000, 0x7fffffff])
+@pytest.mark.parametrize("B,good", [(4, 5), (4, 60), (1, 60)])
+def test_fewer_numbers_than_k_give_no_threshold(B, good, payload):
+    # factors that are NaN (of any payload) rank last among the seeds; where the k-th is one, nothing is filtered out
+    # (1-bit codes: the threshold is that NaN itself), whatever the smaller ones are
+    D, size, k = 64, 300, 64
+    rng = np.random.default_rng(good)
+    X = rng.standard_normal((size, D)).astype(np.float32)
+    ix = build.build_index(X, 1, B, centroids=X.mean(0, keepdims=True).astype(np.float64))
+    dev = build.pack_device_layout(ix)
+    nan = np.uint32(payload).view(np.float32)
+    if B == 1:
+        f = dev["short_factors"].reshape(-1, 3, 64)
+        for s in range(good, size):
+            f[s // 64, 0, s % 64] = nan
+    else:
+        dev["long_factors"].reshape(-1, 2)[good:size, 0] = nan
+    gi = rabitq.index_from_arrays(ix, dev)
+    q = torch.from_numpy(X[:7] + np.float32(0.1)).cuda()
+    for n in (7, 2100):
+        g = q.repeat(n // 7, 1)
+        q_rot = gi.rotate(g)
+        prep = gi.query_prep(q_rot)
+        tau = gi.seed_threshold(prep, gi.coarse_probe(q_rot, prep["sq_norm"], 1), k).cpu().numpy()
+        assert np.all(np.isnan(tau)) if B == 1 else np.all(tau == np.finfo(np.float32).max), tau[:7]
     gi.close()
