@@ -229,7 +229,11 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
   const uint32_t m = (uint32_t)max(a.k, SEED_M);
   uint32_t *lo = sh.ord[wave], *lp = sh.pos[wave];
   int cnt = 0;
-  uint32_t limit = 0xfffffffeu;  // no vector above this can be among the m smallest
+  // Only a vector below the limit can be among the m smallest.  Where the m-th smallest has equals the limit is that very
+  // value, because an equal that comes later loses by its position; otherwise (m vectors are <= bound) it is bound + 1.
+  // (Equals that were let in filled the list every few tiles: a list of 20000 x 64-d, 6 of 7 vectors equal, 3000 queries, k = 10:
+  // 92 us, 474 with the limit included.)
+  uint32_t limit = 0xffffffffu;
   // U tiles are requested together so that their load latencies overlap (tiles past the end
   // re-read the last tile and contribute nothing)
   constexpr int U = (W <= 4) ? 4 : (W <= 8 ? 2 : 1);
@@ -267,8 +271,9 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
     }
     wave_sync();
     uint32_t n_le;
-    limit = wave_kth_ord<RL>(o, m, &n_le);
-    cnt = wave_put_smallest<RL>(o, limit, n_le, m, lane, [&](int at, int r) { lo[at] = o[r]; lp[at] = p[r]; });
+    const uint32_t bound = wave_kth_ord<RL>(o, m, &n_le);
+    cnt = wave_put_smallest<RL>(o, bound, n_le, m, lane, [&](int at, int r) { lo[at] = o[r]; lp[at] = p[r]; });
+    limit = n_le > m ? bound : bound + 1u;
   };
   constexpr int R = (W <= 4) ? 16 : (W <= 8 ? 8 : 4);
   if (tw0 < t1) {
@@ -290,9 +295,12 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
           present += (uint32_t)__popcll(__ballot(o[u] != 0xffffffffu));
         }
       }
-      uint32_t n_le = present;
-      if (present > m) limit = wave_kth_ord<R>(ord, m, &n_le);
-      cnt = wave_put_smallest<R>(ord, limit, n_le, min(m, present), lane, [&](int at, int r) {
+      uint32_t n_le = present, bound = 0xfffffffeu;
+      if (present > m) {
+        bound = wave_kth_ord<R>(ord, m, &n_le);
+        limit = n_le > m ? bound : bound + 1u;
+      }
+      cnt = wave_put_smallest<R>(ord, bound, n_le, min(m, present), lane, [&](int at, int r) {
         lo[at] = ord[r];
         lp[at] = (uint32_t)((tw0 + r - t0) * TILE + lane);
       });
@@ -302,13 +310,13 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
       estimate(tb, o);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        uint64_t mk = __ballot(o[u] <= limit);
+        uint64_t mk = __ballot(o[u] < limit);
         if (mk == 0ull) continue;
         if (cnt + __popcll(mk) > SEED_LIST) {
           cut();  // (m <= 128: a tile always fits afterwards)
-          mk = __ballot(o[u] <= limit);  // the cut has lowered the limit
+          mk = __ballot(o[u] < limit);  // the cut has lowered the limit
         }
-        if (o[u] <= limit) {
+        if (o[u] < limit) {
           const int at = cnt + __popcll(mk & ((1ull << lane) - 1ull));
           lo[at] = o[u];
           lp[at] = (uint32_t)((tb + u - t0) * TILE + lane);

@@ -67,3 +67,37 @@ def test_fewer_numbers_than_k_give_no_threshold(B, good, payload):
         tau = gi.seed_threshold(prep, gi.coarse_probe(q_rot, prep["sq_norm"], 1), k).cpu().numpy()
         assert np.all(np.isnan(tau)) if B == 1 else np.all(tau == np.finfo(np.float32).max), tau[:7]
     gi.close()
+
+
+@pytest.mark.parametrize("size", [700, 5000])
+@pytest.mark.parametrize("k", [1, 10, 40, 64, 65, 128])
+def test_of_equal_estimates_the_lower_positions_are_seeds(k, size):
+    # most of the list has one 1-bit code and the same factors of it, but long codes of their own: the seeds, and with
+    # them the threshold, depend on which of the equals are taken
+    D, B, near = 64, 4, 9
+    rng = np.random.default_rng(size + k)
+    X = rng.standard_normal((size, D)).astype(np.float32)
+    ix = build.build_index(X, 1, B, centroids=X.mean(0, keepdims=True).astype(np.float64))
+    sign = 1 << (B - 1)
+    few = rng.permutation(size)[:size // 7]                   # the others: `near` below the equals, the rest above
+    same = np.setdiff1d(np.arange(size), few)
+    ix["u"][same] = (ix["u"][same[0]] & sign) | (ix["u"][same] & (sign - 1))
+    ix["short_factors"][same] = ix["short_factors"][same[0]]
+    ix["short_factors"][few[:near], 0] -= 1000.0
+    ix["short_factors"][few[near:], 0] += 1000.0
+    s, gi = search.Searcher(ix), upload(ix)
+    Q = X[same[:15]] + np.float32(0.1)
+    st = oracle_stages(s, Q, k, 1)
+    d = to_dev(st)
+    scale = key_scale(st["G"], st["E"], s.metric)
+    m = max(k, s.seed_m)
+    assert near < m < near + len(same)
+    other = [np.sort(s.refined(0, size, st["G"][i, 0], st["Qr"][i], np.concatenate([few[:near], same[-(m - near):]])))[k - 1]
+             for i in range(len(Q))]
+    tol = 1e-5 * (np.abs(st["tau"]) + scale)
+    assert np.any(np.abs(other - st["tau"]) > 2 * tol)          # another choice among the equals would show
+    for reps in (1, 140):
+        tau = gi.seed_threshold({n: t.repeat((reps,) + (1,) * (t.dim() - 1)) for n, t in d["prep"].items()},
+                                {n: t.repeat(reps, 1) for n, t in d["probes"].items()}, k).cpu().numpy()
+        assert np.all(np.abs(tau.reshape(reps, -1) - st["tau"]) <= tol), (reps, tau[:6], st["tau"])
+    gi.close()
