@@ -82,11 +82,12 @@ __global__ __launch_bounds__(64) void select_probes_wave_kernel(const float* __r
   for (int r = 0; r < R; ++r) sv[r] = pinned(sv[r]);
 #pragma unroll
   for (int r = 0; r < R; ++r) ord[r] = (r * 64 + lane < nlist) ? min(f2ord(sv[r]), 0xfffffffeu) : 0xffffffffu;
-  // (32-bit words bisected with ballots; 64-bit keys counted per lane and reduced at every step are slower:
-  // 3001 queries, 1024 lists, 128 probes: the kernel 19 us
-  // against 25)
-  uint32_t n_le;
-  const uint32_t bound = wave_kth_ord<R>(ord, (uint32_t)nprobe, &n_le);
+  // (32-bit words bisected with ballots; 64-bit keys counted per lane and reduced at every step are slower: 3001
+  // queries, 1024 lists, 128 probes: the kernel 19 us against 25.  Where every list is probed there is nothing to bisect:
+  // no value short of the largest splits off all words, so the search would go through the whole range: 10 us of 65 for the
+  // coarse stage of one query and 1024 lists.)
+  uint32_t n_le = (uint32_t)nlist, bound = 0xfffffffeu;
+  if (nprobe < nlist) bound = wave_kth_ord<R>(ord, (uint32_t)nprobe, &n_le);
   const int got = wave_put_smallest<R>(ord, bound, n_le, (uint32_t)nprobe, lane, [&](int at, int r) {
     sel_out[at] = ((uint64_t)ord[r] << 32) | (uint32_t)(r * 64 + lane);
   });

@@ -72,6 +72,22 @@ def test_probe_selection_kernels(nlist, nprobe, variant, metric):
     gi.close()
 
 
+@pytest.mark.parametrize("nlist,nprobe", [(65, 65), (66, 65), (500, 100), (512, 511), (512, 512), (1000, 100), (1023, 1023),
+                                          (1024, 1024), (1100, 128), (2047, 1024), (2048, 65)])
+def test_rows_in_registers_select_what_a_sort_of_the_scores_selects(nlist, nprobe):
+    # every centroid eight times over, so that equal scores straddle the last place: exact, on the library's own scores
+    D, nq = 32, 30
+    rng = np.random.default_rng(nlist + nprobe)
+    C = np.tile(rng.standard_normal((nlist // 8 + 1, D)), (8, 1))[rng.permutation(8 * (nlist // 8 + 1))[:nlist]]
+    gi = upload(build.build_index(rng.standard_normal((100, D)).astype(np.float32), nlist, 1, centroids=C))
+    q = torch.from_numpy(rng.standard_normal((nq, D)).astype(np.float32)).cuda()
+    out = gi.coarse_probe(q, (q * q).sum(1).contiguous(), nprobe)
+    ids, G, sc = (out[k].cpu().numpy() for k in ("probe_ids", "probe_G", "scores"))
+    want = np.lexsort((np.broadcast_to(np.arange(nlist), sc.shape), sc))[:, :nprobe]
+    assert np.array_equal(ids, want) and np.array_equal(G, np.take_along_axis(sc, want, 1))
+    gi.close()
+
+
 def test_every_selection_kernel_has_a_case():
     lib = rabitq.load_library()
     assert {lib.rabitq_probe_select_variant(nlist, nprobe) for nlist, nprobe, _, _ in CASES} == {0, 1, 2, 3, 4}
