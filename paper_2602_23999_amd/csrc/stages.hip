@@ -295,24 +295,28 @@ int launch_build_lists(const int32_t* probe_ids, int64_t nq, int nprobe, int nli
 }
 
 // ---------------------------------------------------------------------------------
-// Section 3.3.5: merge the nprobe cluster-local lists of one query into its top-k, one wavefront per query, any k.
+// Section 3.3.5: merge the nprobe cluster-local lists of one query into its top-k, any k.
 // The lists are short and ragged: 64 of them at a time are laid end to end (a scan of their lengths), so that every
 // lane fetches a key that exists, four at a time.  Keys that can still be among the k best go to a buffer in LDS,
 // which is cut to its k best by bisection when it is full; the k that are left are sorted.  (10^4 queries, 32 lists, k = 100:
 // 27 us, a workgroup per query with a radix select 87; 3001 queries, 128 lists, k = 50: 21 us, one serial insertion per
 // key into a sorted register list 43.)
+// SHARED: the four wavefronts of a workgroup take every fourth step of one query, each with its own buffer, and the first
+// one selects from what they kept; otherwise each has a query of its own.
 // ---------------------------------------------------------------------------------
 constexpr int MERGE_BUF = 512;
 static_assert(RABITQ_MAX_K <= 128 && RABITQ_MAX_K + TILE <= MERGE_BUF, "k keys and a step of 64 fit the buffer; k are sorted in 128 places");
 
+template <bool SHARED>
 __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__ cand_keys,
                                                    const int32_t* __restrict__ cand_cnt, int64_t nq, int k, int cap,
                                                    int nprobe, int metric, int64_t* __restrict__ out_ids,
                                                    float* __restrict__ out_dists) {
   __shared__ uint64_t s_buf[4][MERGE_BUF];
   __shared__ int s_off[4][64];
+  __shared__ int s_cnt[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t q = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t q = SHARED ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
   if (q >= nq) return;
   uint64_t* buf = s_buf[wave];
   int* off = s_off[wave];
@@ -321,20 +325,15 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__
   const uint64_t lower = (1ull << lane) - 1ull;
   int cnt = 0;
   uint64_t limit = KEY_NONE;  // only keys below this can be among the k best
-  // Cuts the buffer to its k best.  Keys may repeat (a caller of the stage may hand in what it likes): of several at the
-  // last place only as many stay as there is room for, and another copy of them is no better, so the limit excludes it.
-  auto cut = [&]() {
-    constexpr int RB = MERGE_BUF / 64;
-    uint64_t key[RB];
-    uint32_t ord[RB];
-    wave_sync();
+  constexpr int RB = MERGE_BUF / 64;
+  // Leaves the k best of more than k keys in the buffer.  Keys may repeat (a caller of the stage may hand in what it likes):
+  // of several at the last place only as many stay as there is room for, and another copy of them is no better, so
+  // the limit excludes it.
+  auto keep_best = [&](const uint64_t (&key)[RB]) {
+    uint32_t ord[RB], n_le;
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      key[r] = r * 64 + lane < cnt ? buf[r * 64 + lane] : KEY_NONE;
-      ord[r] = (uint32_t)(key[r] >> 32);
-    }
+    for (int r = 0; r < RB; ++r) ord[r] = (uint32_t)(key[r] >> 32);
     wave_sync();
-    uint32_t n_le;
     const uint32_t bound = wave_kth_ord<RB>(ord, (uint32_t)k, &n_le);
     uint64_t last = ((uint64_t)bound << 32) | 0xffffffffu;  // the k-th smallest key, or a value between it and the next
     // (equal distances at the last place: the lower ids)
@@ -358,6 +357,13 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__
     cnt = min(at, k);
     wave_sync();
   };
+  auto cut = [&]() {
+    uint64_t key[RB];
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < RB; ++r) key[r] = r * 64 + lane < cnt ? buf[r * 64 + lane] : KEY_NONE;
+    keep_best(key);
+  };
   for (int jb = 0; jb < nprobe; jb += 64) {
     const int n = jb + lane < nprobe ? min(counts[jb + lane], cap) : 0;
     int incl = n;
@@ -370,7 +376,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__
     wave_sync();
     off[lane] = incl - n;  // first place of list jb + lane
     wave_sync();
-    for (int i0 = 0; i0 < total; i0 += 256) {
+    for (int i0 = SHARED ? wave * 256 : 0; i0 < total; i0 += SHARED ? 1024 : 256) {
       uint64_t kk[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -398,7 +404,38 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__
       }
     }
   }
-  if (cnt > k) cut();
+  if (!SHARED) {
+    if (cnt > k) cut();
+  } else {
+    // the first wavefront takes the k best of the four buffers, which fit its registers as they are or cut to k each
+    if (lane == 0) s_cnt[wave] = cnt;
+    __syncthreads();
+    if (s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3] > MERGE_BUF) {  // (the same for all four)
+      if (cnt > k) cut();
+      __syncthreads();
+      if (lane == 0) s_cnt[wave] = cnt;
+      __syncthreads();
+    }
+    if (wave > 0) return;
+    const int e0 = s_cnt[0], e1 = e0 + s_cnt[1], e2 = e1 + s_cnt[2], e3 = e2 + s_cnt[3];
+    uint64_t key[RB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const int i = r * 64 + lane;
+      const int w = i < e0 ? 0 : (i < e1 ? 1 : (i < e2 ? 2 : 3));
+      const int first = w == 0 ? 0 : (w == 1 ? e0 : (w == 2 ? e1 : e2));
+      key[r] = i < e3 ? s_buf[w][i - first] : KEY_NONE;
+    }
+    if (e3 > k) {
+      keep_best(key);
+    } else {  // k <= 128 of them at most
+      wave_sync();
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        if (r * 64 + lane < e3) buf[r * 64 + lane] = key[r];
+      cnt = e3;
+    }
+  }
   wave_sync();
   auto put = [&](int r, uint64_t key) {
     int64_t id = -1;
@@ -423,7 +460,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__
   }
 }
 
-// The same merge for k <= 64 and few lists, one wavefront per query: the candidate lists stream through
+// The same merge for k <= 64 and few lists (or k < 4), one wavefront per query: the candidate lists stream through
 // a register-resident sorted list, G lanes per list, four entries per lane in flight.
 __global__ __launch_bounds__(256) void merge_wave_kernel(const uint64_t* __restrict__ cand_keys,
                                                         const int32_t* __restrict__ cand_cnt, int64_t nq, int k,
@@ -490,15 +527,24 @@ int launch_merge(const uint64_t* cand_keys, const int32_t* cand_cnt, int64_t nq,
                  int64_t* out_ids, float* out_dists, hipStream_t st) {
   if (nq <= 0) return RABITQ_OK;
   const int cap = next_pow2(k + TILE);
-  // Few lists and k <= 64: the first keys of all lists fill the sorted register list at once and few of the others have
-  // to be inserted (16 lists, k = 10, 10^4 queries: 13.0 us against 18.0; one query 5.5 against 6.6).  From 64 lists on, or for
-  // k > 64, the buffer and its bisection win (64 lists, k = 10, 2500 queries: 13.6 against 15.5 us; figures above).
-  if (k <= 64 && nprobe < 64)
+  // Few lists and k <= 64, or the very smallest k: the first keys of all lists fill the sorted register list at once and few
+  // of the others have to be inserted (16 lists, k = 10, 10^4 queries: 13.0 us against 18.0; one query 5.4 against 6.3;
+  // k = 1, 512 lists, one query 5.4 against 7.8).  From 64 lists on, or for k > 64, the buffer and its bisection win (64
+  // lists, k = 10, 2500 queries: 13.6 against 15.5 us; k = 4, 256 queries: 7.5 against 11.0; figures above).
+  // Where there are too few queries to fill the chip, a query is shared by four wavefronts (one query, k = 128, 16 lists:
+  // 15.4 us against 17.6 with one; 64 queries, k = 100, 128 lists: 19.0 against 28.9; unpruned lists, one query, k = 35, 512
+  // lists: 51 against 145).  1024 queries, k = 65, 16 lists: 18.5 against 24.1, but 2048: 21.6 against 15.9; with k <= 64 the
+  // two meet at 512 (64 lists, k = 35: 14.2 against 14.7, 1024: 15.8 against 15.0), and a k below 8 leaves too few
+  // keys to share (64 lists, k = 4, 8 queries: 7.5 against 6.9).
+  if (k <= 64 && (nprobe < 64 || k < 4))
     hipLaunchKernelGGL(merge_wave_kernel, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, cand_keys, cand_cnt, nq, k,
                        cap, nprobe, metric, out_ids, out_dists);
+  else if (k >= 8 && nq <= (k <= 64 ? 512 : 1024))
+    hipLaunchKernelGGL(merge_kernel<true>, dim3((unsigned)nq), dim3(256), 0, st, cand_keys, cand_cnt, nq, k, cap, nprobe,
+                       metric, out_ids, out_dists);
   else
-    hipLaunchKernelGGL(merge_kernel, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, cand_keys, cand_cnt, nq, k, cap,
-                       nprobe, metric, out_ids, out_dists);
+    hipLaunchKernelGGL(merge_kernel<false>, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, cand_keys, cand_cnt, nq, k,
+                       cap, nprobe, metric, out_ids, out_dists);
   RQ_HIP(hipGetLastError());
   return RABITQ_OK;
 }

@@ -73,3 +73,31 @@ def test_merge_of_repeated_keys(k, nprobe, kind):
         best = np.lexsort((ids[q], val[q]))[:k]
         assert np.array_equal(got_i[q], ids[q][best]) and np.array_equal(got_d[q], val[q][best]), q
     gi.close()
+
+
+@pytest.mark.parametrize("k", [3, 4, 7, 8, 64, 65, 128])
+@pytest.mark.parametrize("nprobe", [16, 63, 64, 130])
+def test_few_and_many_queries_merge_alike(k, nprobe):
+    # a query is merged by four wavefronts where there are few queries and by one where there are many, with kept keys that
+    # fit the final selection as they are and with more of them
+    nq, nlist = 8, 130
+    rng = np.random.default_rng(1000 * k + nprobe)
+    C = rng.standard_normal((nlist, 32))
+    gi = upload(build.build_index((C + 0.1).astype(np.float32), nlist, 1, centroids=C))
+    cap = rabitq.load_library().rabitq_cand_capacity(k)
+    cnt = np.minimum(rng.integers(0, cap + 1, (nq, nprobe)), np.array([cap, cap, 20, 5, 5, 1, 2 * k // nprobe + 1, cap])[:, None])
+    d = np.sort(rng.integers(0, 500, (nq, nprobe * cap)), 1).reshape(nq, nprobe, cap)[:, ::-1, ::-1].astype(np.float32)
+    d[1::2] = rng.integers(0, 500, (nq // 2, nprobe, cap))       # (even rows: better and better keys, the limit keeps falling)
+    ids = rng.integers(0, nprobe * cap // 2, (nq, nprobe, cap))
+    order = d.view(np.uint32).astype(np.uint64) | np.uint64(1 << 31)
+    keys = torch.from_numpy(((order << np.uint64(32)) | ids.astype(np.uint64)).view(np.int64)).cuda()
+    cnt_d = torch.from_numpy(cnt.astype(np.int32)).cuda()
+    for reps in (1, 64, 65, 128, 129):                            # 8, 512, 520, 1024, 1032 queries
+        got_i, got_d = gi.merge(keys.repeat(reps, 1, 1), cnt_d.repeat(reps, 1), nq * reps, k, nprobe)
+        got_i, got_d = got_i.cpu().numpy().reshape(reps, nq, k), got_d.cpu().numpy().reshape(reps, nq, k)
+        for q in range(nq):
+            have = np.arange(cap)[None, :] < cnt[q][:, None]
+            best = np.lexsort((ids[q][have], d[q][have]))[:k]
+            assert np.all(got_i[:, q, :len(best)] == ids[q][have][best]) and np.all(got_d[:, q, :len(best)] == d[q][have][best])
+            assert np.all(got_i[:, q, len(best):] == -1)
+    gi.close()
