@@ -691,55 +691,9 @@ struct RefineShape {
   static constexpr int NS = 64 / G;                     // candidates per wavefront round
 };
 
-// partial <u, q'> of lane t (0..G-1) of a candidate whose long-code row starts at `row`
-template <int F, int LW>
-__device__ inline float refine_lane(const uint32_t* __restrict__ row, const float* qf, int t) {
-  constexpr int WPL = RefineShape<LW>::WPL, DPW = 32 / F;
-  float acc = 0.f;
-  const int w0 = t * WPL;
-  if (w0 >= LW) return 0.f;
-  if (WPL % 4 == 0 && LW % 4 == 0) {
-#pragma unroll
-    for (int c = 0; c < WPL / 4; ++c) {
-      const uint4 v = *reinterpret_cast<const uint4*>(row + w0 + 4 * c);
-      const float* q = qf + (w0 + 4 * c) * DPW;
-      acc += dot_word<F>(v.x, q) + dot_word<F>(v.y, q + DPW) + dot_word<F>(v.z, q + 2 * DPW) +
-             dot_word<F>(v.w, q + 3 * DPW);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < WPL; ++i) {
-      const int w = w0 + i;
-      if (w < LW) acc += dot_word<F>(row[w], qf + w * DPW);
-    }
-  }
-  return acc;
-}
-
-// refine_lane's sum over words that refine_load fetched: the same products in the same grouping, bit for bit
-template <int F, int LW>
-__device__ inline float refine_lane_dot(const uint32_t (&w)[RefineShape<LW>::WPL], const float* qf, int t) {
-  constexpr int WPL = RefineShape<LW>::WPL, DPW = 32 / F;
-  const int w0 = t * WPL;
-  float acc = 0.f;
-  if (w0 >= LW) return 0.f;
-  if (WPL % 4 == 0 && LW % 4 == 0) {
-#pragma unroll
-    for (int c = 0; c < WPL / 4; ++c) {
-      const float* q = qf + (w0 + 4 * c) * DPW;
-      acc += dot_word<F>(w[4 * c], q) + dot_word<F>(w[4 * c + 1], q + DPW) + dot_word<F>(w[4 * c + 2], q + 2 * DPW) +
-             dot_word<F>(w[4 * c + 3], q + 3 * DPW);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < WPL; ++i)
-      if (w0 + i < LW) acc += dot_word<F>(w[i], qf + (w0 + i) * DPW);
-  }
-  return acc;
-}
-
-// The same in two steps, so that the words of the next candidate can be requested before the current one is
-// worked on: refine_load only issues loads (every address is inside the row, whatever t), refine_dot consumes them.
+// Partial <u, q'> of lane t (0..G-1) of a candidate whose long-code row starts at `row`, in two steps, so that the words of
+// the next candidate can be requested before the current one is worked on: refine_load only issues loads (every address
+// is inside the row, whatever t), refine_dot consumes them.
 template <int F, int LW>
 __device__ inline void refine_load(const uint32_t* __restrict__ row, int t, uint32_t (&w)[RefineShape<LW>::WPL]) {
   constexpr int WPL = RefineShape<LW>::WPL;
@@ -764,6 +718,28 @@ __device__ inline float refine_dot(const uint32_t (&w)[RefineShape<LW>::WPL], co
 #pragma unroll
   for (int i = 0; i < WPL; ++i)
     if (w0 + i < LW) acc += dot_word<F>(w[i], qf + (w0 + i) * DPW);
+  return acc;
+}
+
+// The same partial sum in the grouping of the threshold seeding, four words at a time: the thresholds' bits depend on it.
+template <int F, int LW>
+__device__ inline float refine_lane_dot(const uint32_t (&w)[RefineShape<LW>::WPL], const float* qf, int t) {
+  constexpr int WPL = RefineShape<LW>::WPL, DPW = 32 / F;
+  const int w0 = t * WPL;
+  float acc = 0.f;
+  if (w0 >= LW) return 0.f;
+  if (WPL % 4 == 0 && LW % 4 == 0) {
+#pragma unroll
+    for (int c = 0; c < WPL / 4; ++c) {
+      const float* q = qf + (w0 + 4 * c) * DPW;
+      acc += dot_word<F>(w[4 * c], q) + dot_word<F>(w[4 * c + 1], q + DPW) + dot_word<F>(w[4 * c + 2], q + 2 * DPW) +
+             dot_word<F>(w[4 * c + 3], q + 3 * DPW);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < WPL; ++i)
+      if (w0 + i < LW) acc += dot_word<F>(w[i], qf + (w0 + i) * DPW);
+  }
   return acc;
 }
 

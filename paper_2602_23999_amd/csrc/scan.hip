@@ -149,7 +149,9 @@ __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
     int64_t slot = 0;
     if (valid) {
       slot = (int64_t)t0 * TILE + (uint32_t)best[sidx];
-      part = refine_lane<FF, LW>(a.long_codes + slot * LW, qf, t);
+      uint32_t w[RefineShape<LW>::WPL];
+      refine_load<FF, LW>(a.long_codes + slot * LW, t, w);
+      part = refine_lane_dot<FF, LW>(w, qf, t);
     }
     const float ip = group_sum<GL>(part);
     if (valid && t == 0) {
