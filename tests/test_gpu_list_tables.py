@@ -37,3 +37,30 @@ def test_tables_at_the_edges_of_a_chunk(nlist):
     for ids, d in got[1:]:
         assert np.array_equal(ids, got[0][0]) and np.array_equal(d, got[0][1])
     gi.close()
+
+
+@pytest.mark.parametrize("nlist", [2047, 2049, 8192, 8193])
+def test_lists_of_several_segments_on_both_sides_of_a_chunk(nlist):
+    # a few hundred vectors in some lists around the edges of a thread's 8 lists and of a chunk, scanned in segments of two
+    # tiles: a list's items and survivor blocks are products of its pairs, segments and tiles.  The reference is the
+    # search in batches of 50 queries, whose tables come from the small-batch builder.
+    D, nprobe, k = 64, 5, 3
+    rng = np.random.default_rng(nlist)
+    C = rng.standard_normal((nlist, D))
+    long = np.unique([c for c in (0, 7, 8, 1000, 2039, 2040, 2046, 2047, 2048, 2049, 5000, 8183, 8184, 8190, 8191, 8192) if c < nlist])
+    which = np.concatenate([np.repeat(long, rng.integers(150, 500, len(long))), rng.integers(0, nlist, 2000)])
+    X = (C[which] + 0.1 * rng.standard_normal((len(which), D))).astype(np.float32)
+    gi = upload(build.build_index(X, nlist, 4, centroids=C))
+    gi.set_option("scan_segment_tiles", 2)
+    gi.set_option("split_min_pairs", 0)
+    nq = 4 * nlist // nprobe + 100                        # just above four pairs per list: not the prefetching scan
+    Q = torch.from_numpy((C[rng.choice(long, nq)] + 0.3 * rng.standard_normal((nq, D))).astype(np.float32)).cuda()
+    want_i, want_d = (torch.cat(t) for t in zip(*[gi.search(Q[i:i + 50].contiguous(), k, nprobe) for i in range(0, nq, 50)]))
+    for impl, n, split, stream in ((0, nq, 0, 0), (0, nq - 200, 0, 1), (4, nq, 1, 0), (4, nq - 200, 1, 0)):
+        for longest in (1, 0):
+            gi.set_option("scan_impl", impl)
+            gi.set_option("longest_first", longest)
+            ids, d = gi.search(Q[:n].contiguous(), k, nprobe)
+            assert (gi.index_info("last_scan_split"), gi.index_info("last_scan_stream")) == (split, stream)
+            assert torch.equal(ids, want_i[:n]) and torch.equal(d, want_d[:n]), (impl, n, longest)
+    gi.close()
