@@ -323,7 +323,7 @@ int rabitq_scan(rabitq_index_t index, const rabitq_query_repr* repr, const float
                 int32_t nprobe, uint64_t* cand_keys, int32_t* cand_cnt, int32_t* dbg_ip, const int64_t* dbg_off,
                 void* stream);
 
-/* Section 3.3.5: per-query merge of the nprobe local lists into the final top-k. */
+/* Section 3.3.5: per-query merge of the nprobe local lists into the final top-k.  Keys may repeat; every copy counts. */
 int rabitq_merge(rabitq_index_t index, const uint64_t* cand_keys, const int32_t* cand_cnt, int64_t nq, int32_t k,
                  int32_t nprobe, int64_t* out_ids, float* out_dists, void* stream);
 

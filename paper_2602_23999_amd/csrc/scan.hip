@@ -171,9 +171,10 @@ __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
 // registers, gives a bound, and a later vector matters only if it is below it; those few are appended to a list in
 // LDS, cut back to m by another bisection when it is full.  (Keeping a sorted list in registers instead, one serial
 // insertion of ~25 instructions per vector that beats the current m-th, was what bound this kernel: 10^4 queries,
-// lists of ~1000 x 128-d, 4 bits: 62 us, now 57, what is
-// left being the reads of the lists; k = 100 needed a workgroup-wide radix select: 10^4 queries, lists of ~490
-// x 96-d, 3 bits: 217 us, now 70.)
+// lists of ~1000 x 128-d, 4 bits: 62 us, now 57, what is left being the reads of the lists; k = 100 needed a
+// workgroup-wide radix select: 10^4 queries, lists of ~490 x 96-d, 3 bits: 217 us, now 70.)
+// A refined estimate is formed as the scan forms it, (2^B-1)/2 * sum(q') rounded before it is subtracted, so that a
+// threshold and the keys it is compared with have the same rounding.
 // SPLIT (few queries): the four wavefronts of a workgroup share one query; each takes a quarter of the cluster's tiles
 // and of the refinement, the first one the selections in between.
 // ---------------------------------------------------------------------------------

@@ -17,10 +17,10 @@ __global__ void zero_i32_kernel(int32_t* p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0;
 }
 
-// item16 != nullptr (split search): also item16[c] = first work item of cluster c when an item is 16 pairs times one
-// segment, and mask_off[c] = first block of survivor bits of cluster c (a block per group of 16 pairs and tile).
-// SPLIT is `item16 != nullptr`, ORDERED `order != nullptr`.  One workgroup whose time is its load latencies: a thread's
-// 8 entries are fetched together (8192 lists, split: 69 us when 256 threads walked 32 entries each; see SCAN_PER).
+// SPLIT (split search): also item16[c] = first work item of cluster c when an item is 16 pairs times one segment, and
+// mask_off[c] = first block of survivor bits of cluster c (a block per group of 16 pairs and tile); not written otherwise.
+// ORDERED: entry i is about cluster order[i].  One workgroup whose time is its load latencies: a thread's 8 entries are
+// fetched together (8192 lists, split: 69 us when 256 threads walked 32 entries each; see SCAN_PER).
 template <int NT, bool SPLIT, bool ORDERED>
 __global__ __launch_bounds__(NT) void item_offsets_kernel(const int32_t* __restrict__ pair_off,
                                                                    const int32_t* __restrict__ tile_off,
