@@ -17,7 +17,7 @@ UNITS = [("api.hip", [], "api.o"), ("gemm.hip", [], "gemm.o"), ("stages.hip", []
          ("scan_dispatch.hip", [], "scan_dispatch.o"), ("build.hip", [], "build.o"),
          ("scan.hip", ["-DRQ_PART=0"], "scan0.o"), ("scan.hip", ["-DRQ_PART=1"], "scan1.o"),
          ("scan.hip", ["-DRQ_PART=2"], "scan2.o"),
-         ("estimate_mfma.hip", [], "estimate_mfma.o")]
+         ("scan_group.hip", [], "scan_group.o"), ("estimate_mfma.hip", [], "estimate_mfma.o")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument",

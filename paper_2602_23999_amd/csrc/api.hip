@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "rq_internal.h"
+#include "rq_scan_args.h"
 
 namespace rq {
 
@@ -205,6 +206,10 @@ static int init_streams(rabitq_index* ix) {
     for (size_t c = 0; c < order.size(); ++c) order[c] = (int32_t)c;
     std::stable_sort(order.begin(), order.end(),
                      [&](int32_t x, int32_t y) { return ix->host_tiles[x] > ix->host_tiles[y]; });
+    // list r of that order belongs to XCD r % 8
+    const int nlist = (int)order.size();
+    order.resize(2 * (size_t)nlist);
+    for (int r = 0; r < nlist; ++r) order[nlist + xcd_first(nlist, r & 7) + (r >> 3)] = order[r];
     if (int rc = dev_alloc(&ix->cluster_order, (int64_t)order.size())) return rc;
     if (!order.empty())
       RQ_HIP(hipMemcpy(ix->cluster_order, order.data(), order.size() * sizeof(int32_t), hipMemcpyHostToDevice));
@@ -518,7 +523,7 @@ int rabitq_query_prep(rabitq_index_t ix, const float* q_rot, int64_t nq, const r
   if (rc) return rc;
   if (nq == 0) return RABITQ_OK;
   if (!q_rot || !repr_ok(out)) { set_error("query_prep: null pointer"); return RABITQ_EINVAL; }
-  return launch_query_prep(q_rot, nq, ix->dim, ix->F, *out, (hipStream_t)stream);
+  return launch_query_prep(q_rot, nq, ix->dim, ix->F, *out, 0, (hipStream_t)stream);
 }
 
 int rabitq_coarse_probe(rabitq_index_t ix, const float* q_rot, const float* sq_norm, int64_t nq, int32_t nprobe,
@@ -572,7 +577,7 @@ int rabitq_seed_threshold(rabitq_index_t ix, const rabitq_query_repr* repr, cons
   if ((rc = check_k_nprobe(ix, k, nprobe, "seed_threshold"))) return rc;
   if (nq == 0) return RABITQ_OK;
   if (!repr_ok(repr) || !probe_ids || !probe_G || !probe_E || !tau) { set_error("seed_threshold: null pointer"); return RABITQ_EINVAL; }
-  return launch_seed(ix, *repr, probe_ids, probe_G, probe_E, nq, k, nprobe, tau, (hipStream_t)stream);
+  return launch_seed(ix, *repr, 0, probe_ids, probe_G, probe_E, nq, k, nprobe, tau, (hipStream_t)stream);
 }
 
 int rabitq_scan(rabitq_index_t ix, const rabitq_query_repr* repr, const float* probe_G, const float* probe_E,
@@ -588,12 +593,11 @@ int rabitq_scan(rabitq_index_t ix, const rabitq_query_repr* repr, const float* p
     set_error("scan: null pointer"); return RABITQ_EINVAL;
   }
   if (nq * nprobe > 0x7fffffff) { set_error("scan: nq*nprobe exceeds 2^31-1"); return RABITQ_EINVAL; }
-  if (split_wanted(ix, nq, nprobe))
-    if ((rc = ensure_split_buffers(ix, nq, nprobe, k))) return rc;
+  if ((rc = ensure_split_buffers(ix, nq, nprobe, k))) return rc;
   if ((rc = ensure_stream_buffers(ix, nq, nprobe, k))) return rc;
   ScanStreams ss;
   ss.main = ss.setup = (hipStream_t)stream;
-  rc = launch_scan(ix, *repr, probe_G, probe_E, pair_off, pair_ids, tau, nq, k, nprobe, cand_keys, cand_cnt, dbg_ip,
+  rc = launch_scan(ix, *repr, 0, probe_G, probe_E, pair_off, pair_ids, tau, nq, k, nprobe, cand_keys, cand_cnt, dbg_ip,
                    dbg_off, ss);
   ix->last_scan_split = ss.split ? 1 : 0;
   ix->last_scan_stream = ss.streamed ? 1 : 0;
@@ -644,15 +648,16 @@ static int search_batch_body(rabitq_index* ix, Workspace& w, const float* querie
     if ((rc = launch_clear_list_bitmap(nq, ix->nlist, w.list_scratch, ix->side)) != RABITQ_OK) return rc;
     if ((rc = launch_clear_counters(w.cand_cnt, nq * nprobe, ix->side)) != RABITQ_OK) return rc;
   }
+  const int form = query_form(scan_route(ix, nq, nprobe, k));
   rabitq_query_repr repr = w.repr;
   if (ix->scan_impl != 2) repr.lut = nullptr;  // tables are only built for the scan that reads them
   // a small batch is bound by the number of dependent launches (Section 4.2.2): it takes fused kernels
   const bool small = ix->small_batch && nq <= SMALL_BATCH_MAX;
   if (small) {
-    RQ_STAGE(0, st, launch_small_front(ix, queries, nq, w.q_rot, repr, w.scores, st));
+    RQ_STAGE(0, st, launch_small_front(ix, queries, nq, w.q_rot, repr, form, w.scores, st));
   } else {
     RQ_STAGE(0, st, launch_rotate(ix, queries, w.q_rot, nq, st));
-    RQ_STAGE(1, st, launch_query_prep(w.q_rot, nq, ix->dim, ix->F, repr, st));
+    RQ_STAGE(1, st, launch_query_prep(w.q_rot, nq, ix->dim, ix->F, repr, form, st));
     RQ_STAGE(2, st, launch_gemm(w.q_rot, ix->centroids_t, w.scores, nq, ix->nlist, ix->dim,
                                 ix->metric == RABITQ_L2 ? 1 : 2, w.repr.sq_norm, ix->centroid_sq, st));
   }
@@ -689,7 +694,7 @@ static int search_batch_body(rabitq_index* ix, Workspace& w, const float* querie
   const bool seed = ix->prune && !(nprobe == 1 && ix->total_bits == 1);
   if (small_fused) {
   } else if (seed) {
-    RQ_STAGE(5, st, launch_seed(ix, w.repr, w.probe_ids, w.probe_G, w.probe_E, nq, k, nprobe, w.tau, st));
+    RQ_STAGE(5, st, launch_seed(ix, w.repr, form, w.probe_ids, w.probe_G, w.probe_E, nq, k, nprobe, w.tau, st));
   } else {
     RQ_STAGE(5, st, launch_fill_f32(w.tau, nq, 3.402823466e+38f, st));
   }
@@ -701,10 +706,10 @@ static int search_batch_body(rabitq_index* ix, Workspace& w, const float* querie
   if (ev && ((ix->prof_mask >> 6) & 1u)) { ss.setup_b = ev->b[6]; ss.setup_e = ev->e[6]; ev->rec |= 1u << 6; }
   if (ev && ((ix->prof_mask >> 7) & 1u)) { ss.scan_b = ev->b[7]; ss.scan_e = ev->e[7]; ev->rec |= 1u << 7; }
   if (ev && ((ix->prof_mask >> 9) & 1u)) { ss.est_b = ev->b[9]; ss.est_e = ev->e[9]; }
-  if ((rc = launch_scan(ix, w.repr, w.probe_G, w.probe_E, w.pair_off, w.pair_ids, w.tau, nq, k, nprobe, w.cand_keys,
+  if ((rc = launch_scan(ix, w.repr, form, w.probe_G, w.probe_E, w.pair_off, w.pair_ids, w.tau, nq, k, nprobe, w.cand_keys,
                         w.cand_cnt, nullptr, nullptr, ss)) != RABITQ_OK)
     return rc;
-  if (ss.est_b && ss.split) ev->rec |= 1u << 9;
+  if (ss.est_b && ss.estimated) ev->rec |= 1u << 9;
   ix->last_scan_split = ss.split ? 1 : 0;
   ix->last_scan_stream = ss.streamed ? 1 : 0;
   RQ_STAGE(8, st, launch_merge(w.cand_keys, w.cand_cnt, nq, k, nprobe, ix->metric, out_ids, out_dists, st));
@@ -740,8 +745,7 @@ int rabitq_search(rabitq_index_t ix, const float* queries, int64_t nq, int32_t k
   // consecutive sub-batches through one workspace; the results do not depend on the split.
   const int64_t step = std::min(nq, search_batch_limit(ix, k, nprobe));
   if ((rc = ensure_workspace(ix, step, nprobe, k))) return rc;
-  if (split_wanted(ix, step, nprobe))
-    if ((rc = ensure_split_buffers(ix, step, nprobe, k))) return rc;
+  if ((rc = ensure_split_buffers(ix, step, nprobe, k))) return rc;
   if ((rc = ensure_stream_buffers(ix, step, nprobe, k))) return rc;
   for (int64_t s0 = 0; s0 < nq; s0 += step) {
     const int64_t m = std::min(step, nq - s0);

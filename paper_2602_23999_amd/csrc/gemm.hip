@@ -132,7 +132,7 @@ __global__ __launch_bounds__(256) void small_front_kernel(const float* __restric
                                                           const float* __restrict__ P, const float* __restrict__ mean_rot,
                                                           const float* __restrict__ ct, const float* __restrict__ csq,
                                                           int metric, float* __restrict__ q_rot, rabitq_query_repr o,
-                                                          float* __restrict__ scores) {
+                                                          int form, float* __restrict__ scores) {
   extern __shared__ float qs[];  // [32][D + 1] rotated queries, then [32] squared norms
   const int ld = D + 1;
   float* s_sq = qs + 32 * ld;
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256) void small_front_kernel(const float* __restric
     if (lane == 0) s_sq[row] = s2;
   }
   for (int row = (int)blockIdx.x + (int)gridDim.x * wave; row < nrows; row += (int)gridDim.x * 4)
-    query_prep_row<F>(qs + row * ld, m0 + row, D, o, lane);
+    query_prep_row<F>(qs + row * ld, m0 + row, D, o, lane, form);
   __syncthreads();
   // coarse scores: this wavefront's 32 lists
   {
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(256) void small_front_kernel(const float* __restric
 }
 
 int launch_small_front(const rabitq_index* ix, const float* queries, int64_t nq, float* q_rot, const rabitq_query_repr& o,
-                       float* scores, hipStream_t st) {
+                       int form, float* scores, hipStream_t st) {
   if (nq <= 0) return RABITQ_OK;
   const int D = ix->dim;
   const size_t smem = (size_t)(32 * (D + 1) + 32) * sizeof(float);
@@ -258,7 +258,7 @@ int launch_small_front(const rabitq_index* ix, const float* queries, int64_t nq,
     if (smem > 64 * 1024) RQ_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(small_front_kernel<F_>),             \
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));            \
     hipLaunchKernelGGL(small_front_kernel<F_>, grid, dim3(256), smem, st, queries, (int)nq, D, ix->nlist, ix->rotation,  \
-                       ix->mean_rot, ix->centroids_t, ix->centroid_sq, ix->metric, q_rot, o, scores);                    \
+                       ix->mean_rot, ix->centroids_t, ix->centroid_sq, ix->metric, q_rot, o, form, scores);                    \
   }
   switch (ix->F) {
     case 0: RQ_SF(0) break;

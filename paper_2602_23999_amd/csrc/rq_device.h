@@ -6,6 +6,10 @@ namespace rq {
 
 constexpr uint64_t KEY_NONE = ~0ull;
 
+// (by value: a conditional on variables selects among their addresses, which puts them into memory)
+template <typename T>
+__device__ inline T one_of(int i, T a, T b, T c, T d) { return i == 0 ? a : (i == 1 ? b : (i == 2 ? c : d)); }
+
 __device__ inline uint64_t make_key(float v, uint32_t lo) { return ((uint64_t)f2ord(v) << 32) | lo; }
 
 // ---------------------------------------------------------------------------------
@@ -337,6 +341,38 @@ __device__ inline int wave_put_smallest(const uint32_t (&ord)[R], uint32_t bound
   return (int)base;
 }
 
+// The k best of more than k keys in registers (KEY_NONE = absent), put(place, key) for places 0 .. k - 1 in any order, by one
+// wavefront.  Keys may repeat: of several at the last place only as many are kept as there is room for.  *cnt = k; returns a
+// limit that only keys at or below it can be among the k best: the k-th key, or a value between it and the next one up.
+// (the caller orders its own memory accesses)
+template <int R, typename Put>
+__device__ __forceinline__ uint64_t wave_keep_best(const uint64_t (&key)[R], int k, int lane, int* cnt, Put put) {
+  uint32_t ord[R], n_le;
+#pragma unroll
+  for (int r = 0; r < R; ++r) ord[r] = (uint32_t)(key[r] >> 32);
+  const uint32_t bound = wave_kth_ord<R>(ord, (uint32_t)k, &n_le);
+  uint64_t last = ((uint64_t)bound << 32) | 0xffffffffu;
+  // (equal distances at the last place: the lower ids)
+  if (n_le != (uint32_t)k) last = wave_kth_bound<R>(key, k);
+  const uint64_t lower = (1ull << lane) - 1ull;
+  int at = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint64_t m = __ballot(key[r] < last);
+    if (key[r] < last) put(at + __popcll(m & lower), key[r]);
+    at += __popcll(m);
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint64_t m = __ballot(key[r] == last);
+    const int place = at + __popcll(m & lower);
+    if (key[r] == last && place < k) put(place, key[r]);
+    at += __popcll(m);
+  }
+  *cnt = min(at, k);
+  return at > k ? last - 1ull : last;
+}
+
 // ---------------------------------------------------------------------------------
 // Streaming selection of the K <= 64 smallest 64-bit keys by one wavefront, entirely in
 // registers: lane l holds the l-th smallest key seen so far.  The first 64 keys are sorted
@@ -412,6 +448,8 @@ struct WaveTopK {
 
 template <int F>
 __host__ __device__ inline int stage_index(int d);  // position of dimension d in the refinement's query order (below)
+__device__ inline float digit_factor(float delta);
+__device__ inline uint4 digit_quad(float4 q, float factor);
 
 // Position of dimension d in the qhat8 array (the matrix-core scan's query operand).  Within every chunk of 64
 // dimensions, dimension r = 32 w + 8 b + 4 h + i (w: word of the chunk, b = 0..3, h = 0..1, i = 0..3) sits at byte
@@ -419,6 +457,19 @@ __host__ __device__ inline int stage_index(int d);  // position of dimension d i
 __host__ __device__ inline int qhat_mfma_pos(int d) {
   const int c = d >> 6, r = d & 63, w = r >> 5, x = r & 31;
   return 64 * c + 16 * (2 * w + ((x >> 2) & 1)) + 4 * (x & 3) + (x >> 3);
+}
+
+// The same digit in the group scan's operand, an 8-bit float (e4m3) of qhat times the 2, 1, 0.5 or 2 that undoes the 0.5, 1,
+// 2 or 0.5 a sign bit in place s of a nibble stands for, and its byte (codes of up to 128 dimensions).
+__device__ inline uint32_t qhat_fp8(int qh, int s) {
+  const uint32_t m = (uint32_t)abs(qh);
+  const uint32_t lo = s == 1 ? 0x44403800u : (s == 2 ? 0x3c383000u : 0x4c484000u);  // for |qhat| = 0..3
+  const uint32_t hi = s == 1 ? 0x4e4c4a48u : (s == 2 ? 0x46444240u : 0x56545250u);  // 4..7
+  return (((m < 4 ? lo : hi) >> (8 * (m & 3))) & 255u) | (qh < 0 ? 128u : 0u);
+}
+__host__ __device__ inline int qhat_fp8_pos(int d) {
+  const int w = d >> 5, n = (d & 31) >> 2, s = d & 3;
+  return 64 * (w >> 1) + 16 * (2 * (w & 1) + (s >> 1)) + 8 * (s & 1) + n;
 }
 
 // ---------------------------------------------------------------------------------
@@ -444,14 +495,27 @@ __device__ inline void prep_reduce(const float* x, int D, int lane, float& amax,
   }
 }
 
+// form (QueryForm): what a search's own scans read, in the same space: the refinement's digits (below) instead of q' in
+// q_stage, the group scan's operand instead of bytes in qhat8.
 template <int F>
-__device__ inline void query_prep_row(const float* x, int64_t q, int D, const rabitq_query_repr& o, int lane) {
+__device__ inline void query_prep_row(const float* x, int64_t q, int D, const rabitq_query_repr& o, int lane, int form) {
   const int W = D >> 5;
   const int Dp = (D + 63) / 64 * 64;
   float amax, s1, s2;
   prep_reduce(x, D, lane, amax, s1, s2);
-  for (int i = lane; i < D; i += 64) o.q_stage[q * D + (F == 0 ? i : stage_index<(F == 0 ? 8 : F)>(i))] = x[i];
   const float dl = (amax == 0.f) ? 1.0f : __fdiv_rn(amax, 7.0f);
+  if ((form & QUERY_DIGITS) != 0 && F > 0) {
+    constexpr int FF = F == 0 ? 8 : F, DPW = 32 / FF, SPB = 8 / FF;
+    const float factor = digit_factor(dl);
+    uint32_t* out = reinterpret_cast<uint32_t*>(o.q_stage) + q * D;
+    for (int i = lane; i < D / 4; i += 64) {  // positions 4i .. 4i+3 of the refinement order
+      const float* src = x + i / SPB * DPW + i % SPB;
+      const uint4 d = digit_quad(make_float4(src[0], src[SPB], src[2 * SPB], src[3 * SPB]), factor);
+      out[i] = d.x; out[D / 4 + i] = d.y; out[D / 2 + i] = d.z; out[3 * (D / 4) + i] = d.w;
+    }
+  } else {
+    for (int i = lane; i < D; i += 64) o.q_stage[q * D + (F == 0 ? i : stage_index<(F == 0 ? 8 : F)>(i))] = x[i];
+  }
   int S = 0;
   uint32_t* pl = o.planes + q * 4 * W;
   for (int base = 0; base < Dp; base += 64) {
@@ -462,7 +526,8 @@ __device__ inline void query_prep_row(const float* x, int64_t q, int D, const ra
       qh = (int)fminf(fmaxf(t, -7.f), 7.f);
     }
     S += qh;
-    o.qhat8[q * Dp + qhat_mfma_pos(i)] = (int8_t)qh;
+    if ((form & QUERY_FP8) != 0) o.qhat8[q * Dp + qhat_fp8_pos(i)] = (int8_t)qhat_fp8(qh, i & 3);
+    else o.qhat8[q * Dp + qhat_mfma_pos(i)] = (int8_t)qh;
     const uint32_t tc = (uint32_t)qh & 15u;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -651,14 +716,21 @@ __device__ inline int ip_bitplanes(const uint32_t (&cw)[W], const_u32_ptr pl) {
 // ---------------------------------------------------------------------------------
 // Refinement (Section 3.4.2: lanes cooperate on one candidate).  The long code holds the
 // whole B-bit code of every dimension in F-bit fields (F = 2, 4, 8), LW = D*F/32 words per
-// vector.  G lanes share one candidate; lane t takes the words [t*WPL, (t+1)*WPL).
+// vector.  <u, q'> of 16 candidates against 4 queries is one chain of v_mfma_i32_16x16x64_i8: the fields u are bytes
+// as they come (masked out of a word four at a time), and q' is a 30-bit fixed-point number cut into four signed bytes
+// ("digits"), so that the 16 rows of the left operand are 4 queries x 4 digits and a lane's four results are the four
+// digit sums of ONE query, exact integers, whatever the order of the sum.  Lane (lj, g) = (lane % 16, lane / 16) feeds
+// part g of candidate lj and receives candidate lj against query g.
+// What bounds it: nothing in the arithmetic (2 matrix and ~50 vector instructions per 16 candidates of 128 x 4 bits,
+// about 190 when each of 4 lanes converted and multiplied 32 fields in fp32 and the partial sums were added across lanes).
 //
-// A word is decoded byte-lane-wise: for each of the 8/F field positions s inside a byte,
-// (word >> s*F) & mask leaves one field in each of the four bytes, and a byte converts to
-// float in one instruction.  Byte b, position s of word w is dimension
-// w*(32/F) + b*(8/F) + s; the query is staged in LDS in that order (stage_index) so that
-// the four floats matching one masked word are one 16-byte read.
+// Digits.  With 2^x <= delta < 2^(x+1) (delta = max|q'|/7, so |q'| < 2^(x+4)), Q = rint(q' * 2^(26-x)) < 2^30, an error of
+// at most 2^(x-27) <= max|q'| * 2^-29.8 per dimension, below the rounding of the 32-bit sum it replaces;
+// Q = d0 + 2^8 d1 + 2^16 d2 + 2^24 d3 with -128 <= d <= 127.  Stored [query][digit][D/4] dwords, four consecutive
+// positions of the refinement order (stage_index) per dword.
 // ---------------------------------------------------------------------------------
+typedef int v4i __attribute__((ext_vector_type(4)));
+
 template <int F>
 __host__ __device__ inline int stage_index(int d) {
   constexpr int DPW = 32 / F, SPB = 8 / F;
@@ -666,105 +738,218 @@ __host__ __device__ inline int stage_index(int d) {
   return w * DPW + (r % SPB) * 4 + (r / SPB);
 }
 
-template <int F>
-__device__ inline float dot_word(uint32_t word, const float* qw) {
-  constexpr int SPB = 8 / F;
-  constexpr uint32_t MASK = (F == 8) ? 0xffffffffu : (((1u << F) - 1u) * 0x01010101u);
-  float acc = 0.f;
-#pragma unroll
-  for (int s = 0; s < SPB; ++s) {
-    uint32_t m = (word >> (s * F)) & MASK;
-    // (kept opaque: otherwise the compiler undoes the shared mask and extracts every field on its own, two
-    // instructions per dimension instead of one byte-to-float conversion)
-    if (F < 8) asm volatile("" : "+v"(m));
-    const float4 q = *reinterpret_cast<const float4*>(qw + 4 * s);
-    acc += (float)(m & 255u) * q.x + (float)((m >> 8) & 255u) * q.y + (float)((m >> 16) & 255u) * q.z +
-           (float)(m >> 24) * q.w;
-  }
-  return acc;
+// biased exponent of delta, kept where both powers of two below are normal numbers
+__device__ inline uint32_t digit_exponent(float delta) { return min(max((__float_as_uint(delta) >> 23) & 255u, 27u), 253u); }
+__device__ inline float digit_factor(float delta) { return __uint_as_float((280u - digit_exponent(delta)) << 23); }  // 2^(26-x)
+__device__ inline float digit_unit(float delta) { return __uint_as_float((digit_exponent(delta) - 26u) << 23); }     // 2^(x-26)
+
+// the four digits of one value, a byte each (the largest byte sum is 0x7f7f7f7f)
+__device__ inline uint32_t digits_of(float q, float factor) {
+  const float v = fminf(fmaxf(rintf(q * factor), -2139062016.f), 2139062016.f);
+  return ((uint32_t)(int)v + 0x80808080u) ^ 0x80808080u;
 }
 
-template <int LW>
+__device__ inline float4 four_floats(const float* p) { return make_float4(p[0], p[1], p[2], p[3]); }  // (any alignment)
+
+// four values -> a dword per digit, value i in byte i
+__device__ inline uint4 digit_quad(float4 q, float factor) {
+  const uint32_t a = digits_of(q.x, factor), b = digits_of(q.y, factor), c = digits_of(q.z, factor), d = digits_of(q.w, factor);
+  const uint32_t ab = __builtin_amdgcn_perm(b, a, 0x05010400u), cd = __builtin_amdgcn_perm(d, c, 0x05010400u);
+  const uint32_t ab2 = __builtin_amdgcn_perm(b, a, 0x07030602u), cd2 = __builtin_amdgcn_perm(d, c, 0x07030602u);
+  return make_uint4(__builtin_amdgcn_perm(cd, ab, 0x05040100u), __builtin_amdgcn_perm(cd, ab, 0x07060302u),
+                    __builtin_amdgcn_perm(cd2, ab2, 0x05040100u), __builtin_amdgcn_perm(cd2, ab2, 0x07060302u));
+}
+
+// one digit of them, from memory
+__device__ inline uint32_t digit_of_quad(const float* p, float factor, int digit) {
+  const uint4 d = digit_quad(four_floats(p), factor);
+  uint32_t v = digit == 0 ? d.x : (digit == 1 ? d.y : (digit == 2 ? d.z : d.w));
+  asm volatile("" : "+v"(v)::"memory");  // (one after the other: many of them in flight would cost every kernel registers)
+  return v;
+}
+
+// How the words of a long-code row are dealt to the four lanes of a candidate: 16 words at a time, four consecutive ones
+// per lane (so that the four lanes read 64 contiguous bytes), and the last LW % 16 in four runs of RW.
+template <int F, int LW>
 struct RefineShape {
-  static constexpr int G = (LW > 32) ? 16 : 4;          // lanes per candidate
-  static constexpr int WPL = (LW + G - 1) / G;          // words per lane
-  static constexpr int NS = 64 / G;                     // candidates per wavefront round
+  static constexpr int UNITS = LW / 16, RW = (LW % 16 + 3) / 4;
+  static constexpr int WPL = 4 * UNITS + RW;      // words per lane
+  static constexpr int QPW = 8 / F;               // operand dwords a word expands to
+  static constexpr int DW = WPL * QPW;            // operand dwords per lane
+  static constexpr int KC = (DW + 3) / 4;         // matrix instructions per 16 candidates
+  static constexpr int NS = 16;                   // candidates per round
+  static constexpr bool EVEN = 16 * UNITS + 4 * RW == LW;  // the last part's runs end with the row
+  static constexpr bool IN_REGS = KC <= 4;        // the query operand of a work item lives in registers (else in LDS)
+  static constexpr int ROW = LW * QPW + 4;        // ... dwords of a digit row there (padded: rows start in other banks)
+  static constexpr int LDS_WORDS = IN_REGS ? 0 : 4 * ROW;  // ... dwords per query
+  __device__ static inline int word(int i, int g) { return i < 4 * UNITS ? 16 * (i / 4) + 4 * g + i % 4 : 16 * UNITS + RW * g + i - 4 * UNITS; }
 };
 
-// Partial <u, q'> of lane t (0..G-1) of a candidate whose long-code row starts at `row`, in two steps, so that the words of
-// the next candidate can be requested before the current one is worked on: refine_load only issues loads (every address
-// is inside the row, whatever t), refine_dot consumes them.
+// the words of one candidate this lane feeds (every address is inside the row)
 template <int F, int LW>
-__device__ inline void refine_load(const uint32_t* __restrict__ row, int t, uint32_t (&w)[RefineShape<LW>::WPL]) {
-  constexpr int WPL = RefineShape<LW>::WPL;
-  const int w0 = t * WPL;
-  if (WPL % 4 == 0 && LW % 4 == 0) {
+__device__ inline void refine_load(const uint32_t* __restrict__ row, int g, uint32_t (&w)[RefineShape<F, LW>::WPL]) {
+  using S = RefineShape<F, LW>;
 #pragma unroll
-    for (int c = 0; c < WPL / 4; ++c) {
-      const uint4 v = *reinterpret_cast<const uint4*>(row + min(w0 + 4 * c, LW - 4));
-      w[4 * c] = v.x; w[4 * c + 1] = v.y; w[4 * c + 2] = v.z; w[4 * c + 3] = v.w;
+  for (int u = 0; u < S::UNITS; ++u) {
+    if (LW % 4 == 0) {  // rows start at multiples of 16 bytes
+      const uint4 v = *reinterpret_cast<const uint4*>(row + 16 * u + 4 * g);
+      w[4 * u] = v.x; w[4 * u + 1] = v.y; w[4 * u + 2] = v.z; w[4 * u + 3] = v.w;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[4 * u + i] = row[16 * u + 4 * g + i];
     }
-  } else {
+  }
 #pragma unroll
-    for (int i = 0; i < WPL; ++i) w[i] = row[min(w0 + i, LW - 1)];
+  for (int i = 0; i < S::RW; ++i) {
+    const int at = 16 * S::UNITS + S::RW * g + i;
+    w[4 * S::UNITS + i] = row[S::EVEN ? at : min(at, LW - 1)];
   }
 }
 
+// dword c of the candidate operand.  (8-bit codes: flip turns 0..255 into -128..127; it is 0 for shorter codes)
+template <int F>
+__device__ inline uint32_t refine_field(uint32_t word, int s, uint32_t flip) {
+  if (F == 8) return word ^ flip;
+  return (word >> (F * s)) & (((1u << F) - 1u) * 0x01010101u);
+}
+
+// dword c of the query operand of lane (., g), whose left row of digits is at `row`
 template <int F, int LW>
-__device__ inline float refine_dot(const uint32_t (&w)[RefineShape<LW>::WPL], const float* qf, int t) {
-  constexpr int WPL = RefineShape<LW>::WPL, DPW = 32 / F;
-  const int w0 = t * WPL;
-  float acc = 0.f;
+__device__ __forceinline__ uint32_t query_operand(const uint32_t* row, int c, int g) {
+  using S = RefineShape<F, LW>;
+  const int w = S::word(c / S::QPW, g);
+  const bool whole = c / S::QPW < 4 * S::UNITS;  // (a word of the last, incomplete part may lie past the row)
+  const uint32_t v = row[(whole ? w : min(w, LW - 1)) * S::QPW + c % S::QPW];
+  return whole || w < LW ? v : 0u;
+}
+// the whole of it in registers
+template <int F, int LW>
+__device__ __forceinline__ void load_query_operand(const uint32_t* row, int g, v4i (&qa)[RefineShape<F, LW>::KC]) {
+  using S = RefineShape<F, LW>;
 #pragma unroll
-  for (int i = 0; i < WPL; ++i)
-    if (w0 + i < LW) acc += dot_word<F>(w[i], qf + (w0 + i) * DPW);
+  for (int kc = 0; kc < S::KC; ++kc) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) qa[kc][i] = 4 * kc + i < S::DW ? (int)query_operand<F, LW>(row, 4 * kc + i, g) : 0;
+  }
+}
+// The four digit rows of one query, `stride` dwords apart, written by one wavefront: copied from the digits, or made from
+// q' (the stage entry points, whose callers hand in q' and no digits).
+template <int D>
+__device__ __forceinline__ void stage_digits(uint32_t* dst, int stride, const uint32_t* digits, const float* q_stage, float factor, int64_t q, int lane) {
+  constexpr int NQ = D / 4;
+  if (digits != nullptr) {
+#pragma unroll
+    for (int i0 = 0; i0 < NQ; i0 += 64) {
+      const int i = i0 + lane;
+      if (i < NQ) {
+        const uint32_t* src = digits + q * D + i;
+        dst[i] = src[0]; dst[stride + i] = src[NQ]; dst[2 * stride + i] = src[2 * NQ]; dst[3 * stride + i] = src[3 * NQ];
+      }
+    }
+  } else {
+#pragma unroll 1
+    for (int i = lane; i < NQ; i += 64) {
+      const uint4 d = digit_quad(four_floats(q_stage + q * D + 4 * i), factor);
+      dst[i] = d.x; dst[stride + i] = d.y; dst[2 * stride + i] = d.z; dst[3 * stride + i] = d.w;
+    }
+  }
+}
+
+// digit sums of candidate lane % 16 against query lane / 16; operand(kc) gives the query operand of step kc
+template <int F, int LW, typename Operand>
+__device__ __forceinline__ v4i refine_mfma(const uint32_t (&w)[RefineShape<F, LW>::WPL], uint32_t flip, Operand operand) {
+  using S = RefineShape<F, LW>;
+  v4i acc = v4i{0, 0, 0, 0};
+#pragma unroll
+  for (int kc = 0; kc < S::KC; ++kc) {
+    v4i x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int c = 4 * kc + i;
+      x[i] = c < S::DW ? (int)refine_field<F>(w[c < S::DW ? c / S::QPW : 0], c % S::QPW, flip) : 0;
+    }
+    acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(operand(kc), x, acc, 0, 0, 0);
+  }
   return acc;
 }
 
-// The same partial sum in the grouping of the threshold seeding, four words at a time: the thresholds' bits depend on it.
-template <int F, int LW>
-__device__ inline float refine_lane_dot(const uint32_t (&w)[RefineShape<LW>::WPL], const float* qf, int t) {
-  constexpr int WPL = RefineShape<LW>::WPL, DPW = 32 / F;
-  const int w0 = t * WPL;
-  float acc = 0.f;
-  if (w0 >= LW) return 0.f;
-  if (WPL % 4 == 0 && LW % 4 == 0) {
+// The same sums with both operands read where they are needed: for kernels that refine little and have better uses for their
+// registers meanwhile (seeding, the matrix-core scans' lists of wide codes), U units of both in flight.  `row`: this lane's candidate; its left row is
+// (q, digit).
+template <int F, int LW, int U = 16>
+__device__ __forceinline__ v4i refine_mfma_from_memory(const uint32_t* __restrict__ row, const uint32_t* digits, const float* q_stage,
+                                              float factor, int64_t q, int digit, int g, uint32_t flip) {
+  using S = RefineShape<F, LW>;
+  constexpr int NQ = LW * S::QPW;
+  v4i acc = v4i{0, 0, 0, 0};
+  auto unit = [&](int u) __attribute__((always_inline)) {
+    uint32_t w[4];
+    if (LW % 4 == 0) {
+      const uint4 v = *reinterpret_cast<const uint4*>(row + 16 * u + 4 * g);
+      w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+    } else {
 #pragma unroll
-    for (int c = 0; c < WPL / 4; ++c) {
-      const float* q = qf + (w0 + 4 * c) * DPW;
-      acc += dot_word<F>(w[4 * c], q) + dot_word<F>(w[4 * c + 1], q + DPW) + dot_word<F>(w[4 * c + 2], q + 2 * DPW) +
-             dot_word<F>(w[4 * c + 3], q + 3 * DPW);
+      for (int i = 0; i < 4; ++i) w[i] = row[16 * u + 4 * g + i];
     }
-  } else {
 #pragma unroll
-    for (int i = 0; i < WPL; ++i)
-      if (w0 + i < LW) acc += dot_word<F>(w[i], qf + (w0 + i) * DPW);
+    for (int h = 0; h < S::QPW; ++h) {  // 4 / QPW words per instruction
+      const int at = (16 * u + 4 * g) * S::QPW + 4 * h;
+      v4i qa, x;
+      if (digits != nullptr) {
+        qa = *reinterpret_cast<const v4i*>(digits + (q * 4 + digit) * NQ + at);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          qa[i] = (int)digit_of_quad(q_stage + (q * NQ + at + i) * 4, factor, digit);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = (int)refine_field<F>(w[(4 * h + i) / S::QPW], (4 * h + i) % S::QPW, flip);
+      acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(qa, x, acc, 0, 0, 0);
+    }
+  };
+  if (S::UNITS <= U) {
+#pragma unroll
+    for (int u = 0; u < S::UNITS; ++u) unit(u);
+  } else {
+    constexpr int STEP = S::UNITS % 5 == 0 ? 5 : (S::UNITS % 4 == 0 ? 4 : (S::UNITS % 3 == 0 ? 3 : 1));
+#pragma unroll 1
+    for (int u0 = 0; u0 < S::UNITS; u0 += STEP) {
+#pragma unroll
+      for (int u = 0; u < STEP; ++u) unit(u0 + u);
+    }
+  }
+  if (S::RW > 0) {
+    constexpr int W0 = 4 * S::UNITS, RD = S::RW * S::QPW;  // words before the last part, its operand dwords
+    uint32_t w[S::RW > 0 ? S::RW : 1];
+#pragma unroll
+    for (int i = 0; i < S::RW; ++i) w[i] = row[min(16 * S::UNITS + S::RW * g + i, LW - 1)];
+#pragma unroll
+    for (int kc = 0; kc < (RD + 3) / 4; ++kc) {
+      v4i qa, x;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int c = 4 * kc + i;
+        const int at = min(16 * S::UNITS + S::RW * g + (c < RD ? c / S::QPW : 0), LW - 1) * S::QPW + c % S::QPW;
+        uint32_t v = 0u;
+        if (c < RD) v = digits != nullptr ? digits[(q * 4 + digit) * NQ + at] : digit_of_quad(q_stage + (q * NQ + at) * 4, factor, digit);
+        qa[i] = 16 * S::UNITS + S::RW * g + (c < RD ? c / S::QPW : 0) < LW ? (int)v : 0;
+        x[i] = c < RD ? (int)refine_field<F>(w[c < RD ? c / S::QPW : 0], c % S::QPW, flip) : 0;
+      }
+      acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(qa, x, acc, 0, 0, 0);
+    }
   }
   return acc;
 }
 
-// sum over the G = 4 or 16 adjacent lanes of a candidate, in every one of them; data-parallel moves inside a row of
-// 16 lanes (rotate by 8 and by 4, then the quad permutations [2,3,0,1] and [1,0,3,2]), no LDS round trips
-template <int CTRL>
-__device__ inline float dpp_move(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
-template <int G>
-__device__ inline float group_sum(float v) {
-  if (G >= 16) {
-    v += dpp_move<0x128>(v);
-    v += dpp_move<0x124>(v);
-  }
-  v += dpp_move<0x4E>(v);
-  v += dpp_move<0xB1>(v);
-  return v;
+// <u, q'> (u: fields as the operand has them) from the four digit sums, none larger than 2^24
+__device__ inline float digit_sum(v4i d, float unit) {
+  return unit * fmaf(256.f, fmaf(256.f, fmaf(256.f, (float)d[3], (float)d[2]), (float)d[1]), (float)d[0]);
 }
 
 // ---------------------------------------------------------------------------------
 // Shared by the matrix-core variants of the scan.
 // ---------------------------------------------------------------------------------
-typedef int v4i __attribute__((ext_vector_type(4)));
-
 // 16 sign bits of a code word -> 16 bytes of 0/1 for the matrix instruction's B operand, at two instructions per
 // four bytes: (word >> s) & 0x01010101 leaves bits s, s+8, s+16, s+24 of the word in the four bytes.  The lane
 // group with half h (0 / 1) of a word takes the shifts s = 4h .. 4h+3, so byte b of its i-th operand word is dimension

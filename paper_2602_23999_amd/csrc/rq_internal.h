@@ -57,6 +57,7 @@ struct rabitq_index {
                                     // | [nlist+1] work items of 16 pairs | [nlist+1] first survivor block (split search)
   int32_t* cluster_size = nullptr;  // [nlist]
   int32_t* cluster_order = nullptr; // [nlist] clusters by descending tile count, equal counts by ascending id
+                                    // | [nlist] the same dealt to the XCDs (xcd_first)
   uint32_t* short_codes = nullptr;
   float* short_factors = nullptr;
   uint32_t* long_codes = nullptr;
@@ -78,7 +79,7 @@ struct rabitq_index {
   int split_min_pairs = 32;  // pairs per list, on average, from which scan_impl 3 / 4 split the search
   uint64_t* surv_mask = nullptr;
   int64_t surv_mask_blocks = 0;
-  rq::ItemDesc* item_desc = nullptr;  // descriptors of the refinement kernel's work items (split search), grown with the bits
+  rq::ItemDesc* item_desc = nullptr;  // descriptors of work items (split search, group scan, streaming scan), grown on demand
   int64_t item_desc_cap = 0;
   std::vector<int64_t> tiles_prefix;  // [i] = tiles of the i largest lists (host; filled on first use)
   int overlap = 1;  // list building and scan set-up run beside the seeding on `side`
@@ -139,8 +140,12 @@ int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int 
 // small batches: Q' = (Q - mean) P, the queries' representation and the coarse scores [nq][nlist] from one launch,
 // bit-identical to launch_rotate + launch_query_prep + launch_gemm (mode 1 / 2)
 int launch_small_front(const rabitq_index* ix, const float* queries, int64_t nq, float* q_rot, const rabitq_query_repr& o,
-                       float* scores, hipStream_t st);
-int launch_query_prep(const float* q_rot, int64_t nq, int D, int F, const rabitq_query_repr& out, hipStream_t st);
+                       int form, float* scores, hipStream_t st);
+// form: what the members hold (query_form).  The stage entry points hand out and take what the header says (0); a search hands
+// its scans what they would otherwise make of it themselves, in the same space: the refinement's digits of q' in
+// q_stage, the group scan's operand in qhat8 (rq_device.h).  Same numbers either way.
+enum QueryForm { QUERY_DIGITS = 1, QUERY_FP8 = 2 };
+int launch_query_prep(const float* q_rot, int64_t nq, int D, int F, const rabitq_query_repr& out, int form, hipStream_t st);
 int launch_select_probes(const float* scores, const float* sq_norm, const float* centroid_sq, int64_t nq, int nlist,
                          int nprobe, int metric, int32_t* probe_ids, float* probe_G, float* probe_E, hipStream_t st);
 int probe_select_variant(int nlist, int nprobe);  // which selection kernel launch_select_probes takes (see stages.hip)
@@ -148,7 +153,7 @@ int64_t probe_list_scratch_words(int32_t nlist, int64_t nq);
 int launch_clear_list_bitmap(int64_t nq, int nlist, uint32_t* scratch, hipStream_t st);
 int launch_build_lists(const int32_t* probe_ids, int64_t nq, int nprobe, int nlist, int32_t* pair_off,
                        int32_t* pair_ids, uint32_t* scratch, hipStream_t st, bool bitmap_is_clear = false);
-int launch_seed(const rabitq_index* ix, const rabitq_query_repr& repr, const int32_t* probe_ids, const float* probe_G,
+int launch_seed(const rabitq_index* ix, const rabitq_query_repr& repr, int form, const int32_t* probe_ids, const float* probe_G,
                 const float* probe_E, int64_t nq, int k, int nprobe, float* tau, hipStream_t st);
 // Streams and events of one scan launch: the set-up kernels (work-item offsets, counter clearing) run on `setup`
 // and the scan kernel on `main`; when the two differ, `join` is recorded on `setup` and awaited on `main`.  The
@@ -158,7 +163,8 @@ struct ScanStreams {
   hipEvent_t join = nullptr;
   hipEvent_t setup_b = nullptr, setup_e = nullptr, scan_b = nullptr, scan_e = nullptr;
   hipEvent_t est_b = nullptr, est_e = nullptr;  // around the estimate kernel of a split search
-  mutable bool split = false;                  // out: the search was split
+  mutable bool split = false;                  // out: the estimates ran on the matrix cores (group scan or split search)
+  mutable bool estimated = false;              // out: ... as a kernel of their own, between est_b and est_e
   mutable bool streamed = false;               // out: the prefetching variant of the popcount kernel ran
   bool counters_clear = false;  // cand_cnt was already zeroed by launch_clear_counters
   bool desc_done = false;       // ... and so were the descriptors of the prefetching scan's work items (launch_small_select_seed)
@@ -174,16 +180,31 @@ constexpr int SMALL_BATCH_MAX = 64;
 constexpr int TICKET_WORDS = 4;  // words behind the two offset arrays of rabitq_index::tile_off (zero between launches)
 inline int64_t tile_off_words(int nlist) { return 4 * (int64_t)(nlist + 1) + TICKET_WORDS; }
 // Split search (scan_impl 4): the first stage runs on the matrix cores for groups of 16 pairs and hands one survivor
-// bit per (pair, vector) to the popcount kernel.  Built for every code with a long part (B > 1); taken on request (4) and,
-// by default (3), below D = 960 (there the four-wavefront matrix-core kernel is faster) from split_min_pairs pairs per
-// list on average.  split_mask_blocks bounds the blocks of survivor bits a search of
-// (nq, nprobe) can need: sum_c ceil(cnt_c / 16) tiles_c <= (nq * tiles of the nprobe largest lists) / 16 + all tiles,
-// because every query probes nprobe distinct lists.
+// bit per (pair, vector) to the popcount kernel.  Built for every code with a long part (B > 1) of less than 960 dimensions and
+// taken, where the group scan below is not, from split_min_pairs pairs per list on average.  split_mask_blocks bounds the
+// blocks of survivor bits a search of (nq, nprobe) can need: sum_c ceil(cnt_c / 16) tiles_c <= (nq * tiles of the nprobe
+// largest lists) / 16 + all tiles, because every query probes nprobe distinct lists.
 inline bool split_built(const rabitq_index* ix) { return ix->total_bits > 1; }
 inline bool split_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
-  return (ix->scan_impl == 4 || (ix->scan_impl == 3 && ix->W < 30)) && split_built(ix) &&
+  return (ix->scan_impl == 4 || ix->scan_impl == 3) && split_built(ix) && ix->W < 30 &&
          nq * nprobe >= (int64_t)ix->split_min_pairs * ix->nlist;
 }
+// ... as one kernel, the group scan (scan_group.hip says why these widths).  For codes of up to 256 dimensions it does not cut
+// lists into segments, so the longest list must not outlast the launch: one wavefront works on it, while the chip's about
+// 3072 share the rest.  From D = 960 on it takes the place of the four-wavefront matrix-core kernel from 8 pairs per list on.
+inline bool group_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
+  if (!split_built(ix) || (ix->scan_impl != 3 && ix->scan_impl != 4)) return false;
+  const int64_t pairs = nq * nprobe;
+  if (ix->W >= 30) return pairs >= (int64_t)(ix->split_min_pairs < 8 ? ix->split_min_pairs : 8) * ix->nlist;
+  if (ix->W > 8 || pairs < (int64_t)ix->split_min_pairs * ix->nlist) return false;
+  const int64_t share = (pairs / QM + ix->nlist) * (ix->n_tiles / (ix->nlist > 0 ? ix->nlist : 1) + 1) / 3072;
+  return ix->max_tiles <= (share > 32 ? 2 * share : 64);
+}
+// Which scan a search of this shape gets, given the handle's buffers: SINGLE stands for the kernels of scan_impl 0, 1 and 2.
+enum ScanRoute { ROUTE_SINGLE, ROUTE_SPLIT, ROUTE_GROUP };
+ScanRoute scan_route(rabitq_index* ix, int64_t nq, int nprobe, int k);
+// the form a search's queries take for it
+inline int query_form(ScanRoute route) { return QUERY_DIGITS | (route != ROUTE_SINGLE ? QUERY_FP8 : 0); }
 int64_t split_mask_blocks(rabitq_index* ix, int64_t nq, int nprobe);
 // makes the handle's survivor-bit buffer large enough for (nq, nprobe); may allocate (then it synchronises the device)
 int ensure_split_buffers(rabitq_index* ix, int64_t nq, int nprobe, int k);
@@ -199,7 +220,7 @@ int launch_small_select_seed(const rabitq_index* ix, const rabitq_query_repr& re
 int launch_small_batch_lists(const rabitq_index* ix, const int32_t* probe_ids, int64_t nq, int nprobe, int k,
                              int32_t* pair_off, int32_t* pair_ids, uint32_t* scratch, int32_t* cand_cnt, hipStream_t st);
 int launch_clear_counters(int32_t* cand_cnt, int64_t n, hipStream_t st);
-int launch_scan(const rabitq_index* ix, const rabitq_query_repr& repr, const float* probe_G, const float* probe_E,
+int launch_scan(rabitq_index* ix, const rabitq_query_repr& repr, int form, const float* probe_G, const float* probe_E,
                 const int32_t* pair_off, const int32_t* pair_ids, const float* tau, int64_t nq, int k, int nprobe,
                 uint64_t* cand_keys, int32_t* cand_cnt, int32_t* dbg_ip, const int64_t* dbg_off, const ScanStreams& ss);
 int launch_merge(const uint64_t* cand_keys, const int32_t* cand_cnt, int64_t nq, int k, int nprobe, int metric,

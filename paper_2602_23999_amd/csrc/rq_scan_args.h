@@ -46,14 +46,17 @@ struct ScanArgs {
   const int32_t* tile_off;
   const int32_t* cluster_size;
   int D, B, LW, nlist;
-  float cB;  // (2^B - 1) / 2
+  float cB;  // (2^B - 1) / 2, less what `flip` takes off every field
+  uint32_t flip;  // 0x80808080 for 8-bit codes, whose fields become signed bytes by it (u - 128), else 0
   // The 1-bit bound of a 4-bit query multiplies f_err by sqrt(E^2 + qerr * delta^2) instead of E = ||q'-c'||: the
   // query's rounding errors add variance (D-1) delta^2 / (12 (1-a^2)) in the units of the code's own error, with
   // a^2 = 2/pi for 1-bit codes; qerr = (D-1) / (12 (1 - 2/pi)), 0 for the lookup-table scheme (no rounded query).
   float qerr;
   // per query
-  const float* q_stage;   // [nq][D] rotated query in refinement order
+  const uint32_t* q_digits;  // [nq][4][D/4] rotated query in refinement order as digits; nullptr: made from q_stage
+  const float* q_stage;      // [nq][D] the rotated query itself, in that order (stage entry points only)
   const int8_t* qhat8;    // [nq][Dp] 4-bit query as bytes (matrix-core scan)
+  bool qhat_fp8;          // ... as 8-bit floats in the group scan's order instead
   int Dp;
   const uint32_t* planes;
   const uint16_t* lut;    // [nq][D/4][16] binary16 lookup tables (lookup-table scan only)
@@ -105,6 +108,10 @@ __host__ __device__ inline int pair_query(const ScanArgs& a, int pair) {
   return (int)(((uint64_t)(uint32_t)pair * a.nprobe_mul) >> a.nprobe_shift);
 }
 
+// the group scan's order of the lists: entry of the first one of XCD x, 0 <= x <= 8 (list r by descending length belongs to
+// XCD r % 8, and the lists of an XCD are consecutive entries)
+__host__ __device__ inline int xcd_first(int nlist, int x) { return x * (nlist >> 3) + ((nlist & 7) < x ? nlist & 7 : x); }
+
 // number of segments a cluster of `tiles` tiles is split into
 __host__ __device__ inline int seg_count(int tiles, int tseg, int segmax) {
   const int n = (tiles + tseg - 1) / tseg;
@@ -114,6 +121,13 @@ __host__ __device__ inline int seg_count(int tiles, int tseg, int segmax) {
 // impl 4: the estimates of QM pairs per wavefront on the matrix cores, leaving survivor bits for the popcount kernel;
 // false for a width it is not built for
 bool estimate_mfma(const ScanArgs& a, int W, unsigned grid, bool dbg, hipStream_t st);
+
+// the group scan (QM pairs per wavefront, estimates and refinement on the matrix cores); false for a width it is not
+// built for.  group_narrow: the form of it that keeps the digits in LDS and does not cut lists into segments; group_pool: keys of a
+// pair's pool in the other
+bool scan_group(const ScanArgs& a, int W, int F, unsigned grid, bool dbg, hipStream_t st);
+__host__ __device__ constexpr bool group_narrow(int W) { return W <= 8; }
+int group_pool(int k);
 
 // impl 0: popcount kernel (QW pairs per wavefront); impl 1: matrix-core kernel (QM pairs; seeds by popcount);
 // impl 2: lookup-table kernel (QW pairs)

@@ -41,11 +41,6 @@ __device__ inline void stage_lut(_Float16* dst, const uint16_t* __restrict__ src
   for (int i = tid; i < W * 64; i += nt) d32[i] = s32[i];
 }
 
-// copy one rotated query (already in refinement order) into LDS
-__device__ inline void stage_query(float* dst, const float* __restrict__ src, int D, int tid, int nt) {
-  for (int i = tid; i < D; i += nt) dst[i] = src[i];
-}
-
 // ---------------------------------------------------------------------------------
 // Seeding of the lookup-table scan: one workgroup (256 threads) per query.  In the nearest probed cluster with
 // at least k vectors: the m = max(k, SEED_M) smallest (est1, position) -> refine -> tau = k-th
@@ -53,17 +48,29 @@ __device__ inline void stage_query(float* dst, const float* __restrict__ src, in
 // ---------------------------------------------------------------------------------
 constexpr int SEED_CHUNK_TILES = 32;  // 2048 keys per selection round
 
+// Refined estimate of the vector at `slot` for query q, 16 of them per wavefront: lane (lj, g) names the slot of
+// candidate lj (the same in its four lanes) and gets its estimate.
+template <int W, int F>
+__device__ __forceinline__ float seed_estimate(const ScanArgs& a, int64_t q, int64_t slot, float G, int lj, int g) {
+  constexpr int FF = (F > 0 ? F : 8), LW = W * FF;
+  const float2 lf = *reinterpret_cast<const float2*>(a.long_factors + 2 * slot);
+  const float dl = a.delta[q];
+  // (one query: its four digits repeat in the 16 rows, so that all four lanes of a candidate get the same sums)
+  const float ip = digit_sum(refine_mfma_from_memory<FF, LW>(a.long_codes + slot * LW, a.q_digits, a.q_stage, digit_factor(dl),
+                                                             q, lj & 3, g, a.flip), digit_unit(dl));
+  return G + lf.x + lf.y * (ip - a.cB * a.sum_q[q]);
+}
+
 template <int W, int F>
 __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
   extern __shared__ unsigned char smem_raw[];
-  // layout: chunk keys [2048] u64 | best [kpad] u64 | out [kpad] u64 | qf [D] f32 | tables [8W][16] f16
+  // layout: chunk keys [2048] u64 | best [kpad] u64 | out [kpad] u64 | tables [8W][16] f16
   const int m = max(a.k, SEED_M);
   const int kpad = next_pow2(m);
   uint64_t* chunk = reinterpret_cast<uint64_t*>(smem_raw);
   uint64_t* best = chunk + SEED_CHUNK_TILES * TILE;
   uint64_t* out = best + kpad;
-  float* qf = reinterpret_cast<float*>(out + kpad);
-  _Float16* lut_s = reinterpret_cast<_Float16*>(qf + a.D);
+  _Float16* lut_s = reinterpret_cast<_Float16*>(out + kpad);
   __shared__ SelectScratch sh;
   __shared__ int s_rank, s_t0, s_t1;
   __shared__ float s_G;
@@ -101,7 +108,6 @@ __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
     }
   }
   for (int i = tid; i < kpad; i += 256) best[i] = KEY_NONE;
-  if (F > 0) stage_query(qf, a.q_stage + q * a.D, a.D, tid, 256);
   stage_lut(lut_s, a.lut + q * (int64_t)W * 128, W, tid, 256);
   __syncthreads();
   const int rank = s_rank;
@@ -137,27 +143,16 @@ __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
     if (tid == 0) a.tau_out[q] = ord2f((uint32_t)(best[a.k - 1] >> 32));
     return;
   }
-  // refine the m seeds (fewer if the cluster is smaller), GL lanes per seed; their keys replace `out`
-  constexpr int FF = (F > 0 ? F : 8), LW = W * FF, GL = RefineShape<LW>::G;
-  const int grp = tid / GL, t = tid % GL;
+  // refine the m seeds (fewer if the cluster is smaller), 16 per wavefront and round; their keys replace `out`
   for (int i = tid; i < kpad; i += 256) out[i] = KEY_NONE;
   __syncthreads();
-  for (int base = 0; base < m; base += 256 / GL) {
-    const int sidx = base + grp;
+  const int lj = lane & 15, g = lane >> 4;
+  for (int base = 16 * wave; base < m; base += 64) {
+    const int sidx = base + lj;
     const bool valid = sidx < m && best[min(sidx, kpad - 1)] != KEY_NONE;
-    float part = 0.f;
-    int64_t slot = 0;
-    if (valid) {
-      slot = (int64_t)t0 * TILE + (uint32_t)best[sidx];
-      uint32_t w[RefineShape<LW>::WPL];
-      refine_load<FF, LW>(a.long_codes + slot * LW, t, w);
-      part = refine_lane_dot<FF, LW>(w, qf, t);
-    }
-    const float ip = group_sum<GL>(part);
-    if (valid && t == 0) {
-      const float eB = G + a.long_factors[2 * slot] + a.long_factors[2 * slot + 1] * (ip - a.cB * a.sum_q[q]);
-      out[sidx] = make_key(eB, (uint32_t)sidx);
-    }
+    const int64_t slot = (int64_t)t0 * TILE + (valid ? (uint32_t)best[min(sidx, kpad - 1)] : 0u);
+    const float eB = seed_estimate<W, F>(a, q, slot, G, lj, g);
+    if (valid && g == 0) out[sidx] = make_key(eB, (uint32_t)sidx);
   }
   __syncthreads();
   block_bitonic_sort(out, kpad);
@@ -363,30 +358,13 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
     wave_sync();
   }
   if (F > 0) {
-    // refine the seeds (fewer than m if the cluster is smaller), GL lanes per seed; a refined estimate takes the
-    // place of the seed's 1-bit estimate.  Nothing is fetched under a condition (an absent seed repeats the last
-    // one), and a round's words are requested before the previous round is worked on.
-    constexpr int FF = (F > 0 ? F : 8), LW = W * FF, GL = RefineShape<LW>::G, NS = RefineShape<LW>::NS;
-    const int grp = lane / GL, t = lane % GL, step = SPLIT ? 4 * NS : NS;
-    const float csq = a.cB * a.sum_q[q];
-    struct Seed {
-      uint32_t w[RefineShape<LW>::WPL];
-      float2 lf;
-    };
-    auto request = [&](int base, Seed& s) {
-      const int64_t slot = (int64_t)t0 * TILE + lp[min(base + grp, cnt - 1)];
-      refine_load<FF, LW>(a.long_codes + slot * LW, t, s.w);
-      s.lf = *reinterpret_cast<const float2*>(a.long_factors + 2 * slot);
-    };
-    Seed nxt;
-    const int first = SPLIT ? wave * NS : 0;
-    if (first < cnt) request(first, nxt);
-    for (int base = first; base < cnt; base += step) {
-      const Seed cur = nxt;
-      if (base + step < cnt) request(base + step, nxt);
-      const float ip = group_sum<GL>(refine_lane_dot<FF, LW>(cur.w, a.q_stage + q * a.D, t));
-      const float eB = G + cur.lf.x + cur.lf.y * (ip - csq);
-      if (t == 0 && base + grp < cnt) lo[base + grp] = f2ord(eB);
+    // refine the seeds (fewer than m if the cluster is smaller), 16 per round; a refined estimate takes the place of the
+    // seed's 1-bit estimate.  Nothing is fetched under a condition: an absent seed repeats the last one.
+    const int lj = lane & 15, g = lane >> 4, step = SPLIT ? 64 : 16;
+    for (int base = SPLIT ? wave * 16 : 0; base < cnt; base += step) {
+      const int64_t slot = (int64_t)t0 * TILE + lp[min(base + lj, cnt - 1)];
+      const float eB = seed_estimate<W, F>(a, q, slot, G, lj, g);
+      if (g == 0 && base + lj < cnt) lo[base + lj] = f2ord(eB);
     }
     if (SPLIT) __syncthreads();
     else wave_sync();
@@ -474,7 +452,9 @@ constexpr int LIST_CAP = 512;
 // MASKED: MASK_BATCH words of survivor bits are turned into list entries at a time, at most 16 each
 constexpr int MASK_BATCH = 32;
 constexpr int LIST_CAP_MASKED = 256 + 16 * MASK_BATCH;
-constexpr int REFINE_AHEAD_MASKED = 2;  // refinement rounds whose loads are in flight (1 in the fused kernel)
+// refinement rounds whose loads are in flight: two where the kernel only refines and a candidate's words are few (1 in the
+// fused kernel)
+__host__ __device__ constexpr int refine_ahead(bool masked, int words_per_lane) { return masked && words_per_lane <= 16 ? 2 : 1; }
 
 #ifdef RQ_TIMELINE  // development: when each work item of the popcount kernel started, began to scan and ended
 __device__ unsigned long long g_timeline[1 << 16][4];
@@ -506,21 +486,18 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int item) {
   // with a quarter of the scalar state, which is what lets eight wavefronts share a SIMD)
   constexpr int QN = PFD > 0 ? 1 : QW;
   constexpr int FF = (F > 0 ? F : 8), LW = W * FF;
-  constexpr int G = RefineShape<LW>::G, NS = RefineShape<LW>::NS;
-  extern __shared__ unsigned char smem_raw[];
+  using RS = RefineShape<FF, LW>;
+  constexpr int NS = RS::NS;
+  // (wide codes: every step's four operand dwords are consecutive and inside the row)
+  static_assert(!RS::IN_REGS || 4 * QN * 8 * W <= 2 * 64 * QN + LIST_CAP, "the digits of the queries fit the pools and the list");
+  static_assert(RS::IN_REGS || (LW % 4 == 0 && RS::RW * RS::QPW % 4 == 0 && 16 * RS::UNITS + 4 * RS::RW == LW), "layout");
+  extern __shared__ __align__(16) unsigned char smem_raw[];
   uint64_t* pools = reinterpret_cast<uint64_t*>(smem_raw);             // [QN][pool]
-  uint64_t* pool_kth = pools + (size_t)QN * a.pool;                    // [QN] k-th best key so far
-  float* qs = reinterpret_cast<float*>(pool_kth + QN);                 // [QN][2]: G, cB*sum(q')
-  int* pool_cnt = reinterpret_cast<int*>(qs + 2 * QN);                 // [QN]
-  constexpr int LCAP = MASKED ? LIST_CAP_MASKED : LIST_CAP, AHEAD = MASKED ? REFINE_AHEAD_MASKED : 1;
-  uint32_t* list = reinterpret_cast<uint32_t*>(pool_cnt + QN);         // [LCAP] (F > 0)
-  // The queries in LDS, padded: a lane of the refinement reads a chunk of QCH = D / G consecutive floats, 16 bytes at
-  // a time, and the chunks of one row (and the rows) would all start in the same banks; QPAD floats after every
-  // chunk spread them over the banks.  Element e of row j sits at j * QROW + e + QPAD * (e / QCH).
-  constexpr int QCH = RefineShape<LW>::WPL * (32 / FF), QPAD = 4, QROW = 32 * W + QPAD * G;
-  float* qf = reinterpret_cast<float*>(list + (F > 0 ? LCAP : 0));     // [QN][QROW] (F > 0)
-  _Float16* lut_s = reinterpret_cast<_Float16*>(qf + (F > 0 ? QN * QROW : 0));  // [QN][8W][16] (M = 1)
-  const int lane = threadIdx.x;
+  constexpr int LCAP = MASKED ? LIST_CAP_MASKED : LIST_CAP, AHEAD = refine_ahead(MASKED, RS::WPL);
+  uint32_t* list = reinterpret_cast<uint32_t*>(pools + (size_t)QN * a.pool);  // [LCAP] (F > 0)
+  uint32_t* qdig = list + (F > 0 ? LCAP : 0);                          // [QN][4][ROW] digits of the queries (F > 0, wide codes)
+  _Float16* lut_s = reinterpret_cast<_Float16*>(qdig + (F > 0 ? QN * RS::LDS_WORDS : 0));  // [QN][8W][16] (M = 1)
+  const int lane = threadIdx.x, lj = lane & 15, lg = lane >> 4;
 
   RQ_TL(item, 0, wall_clock64());
   int t0, nseg, ts, te, pbeg, np;
@@ -592,7 +569,7 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int item) {
   }
 
   int pj[QN], Sj[QN], cnt[QN];
-  float Gj[QN], Ej[QN], dlj[QN], bej[QN], tauj[QN], hsqj[QN];
+  float Gj[QN], Ej[QN], dlj[QN], bej[QN], tauj[QN], hsqj[QN], sumqj[QN];
   int64_t qj[QN];
 #pragma unroll
   for (int j = 0; j < QN; ++j) {
@@ -618,12 +595,7 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int item) {
     const float tau_q = PFD > 0 ? *(const_f32_sptr)(a.tau + q) : a.tau[q];
     tauj[j] = (j < np) ? tau_q : -3.402823466e+38f;  // an absent pair lets nothing through
     cnt[j] = 0;
-    if (lane == 0) {
-      pool_kth[j] = KEY_NONE;
-      pool_cnt[j] = 0;
-      qs[2 * j] = Gj[j];
-      qs[2 * j + 1] = a.cB * sumq;
-    }
+    sumqj[j] = sumq;
   }
   if (M == 1) {
     // the lookup tables of the QN queries (W * 64 dwords each) go to LDS, all words of a batch requested before the
@@ -645,26 +617,34 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int item) {
         for (int u = 0; u < W; ++u) d32[(j0 + jj) * W * 64 + u * 64 + lane] = tv[jj][u];
     }
   }
+  // The refinement's share of a lane: row lane % 16 of the query operand is digit lane % 4 of pair (lane % 16) / 4 (the
+  // rows of absent pairs repeat the others'), and the sums that arrive are those of pair lane / 16, whose scalars and pool
+  // state (entries, k-th best key so far) the 16 lanes hold alike.
+#define RQ_OF_PAIR(v, j) one_of(j, v[0], v[QN > 1 ? 1 : 0], v[QN > 2 ? 2 : 0], v[QN > 3 ? 3 : 0])
+  v4i qa[RS::KC];
+  const int jg = QN > 1 ? lg : 0;
+  const float G_g = RQ_OF_PAIR(Gj, jg), csq_g = a.cB * RQ_OF_PAIR(sumqj, jg), unit_g = digit_unit(RQ_OF_PAIR(dlj, jg));
+  uint64_t kth_g = KEY_NONE;
+  int cnt_g = 0;
   if (F > 0) {
-    // the rotated queries go to LDS for the refinement: every word is requested before the first one is stored
-    // (copied one after the other, each word would wait for its own round trip, 2 QN of them for D = 128)
-    constexpr int DD = 32 * W, PER = (DD + 63) / 64, JB = (PER * QN <= 16) ? QN : 1;
+    constexpr int D = 32 * W;
+    if (RS::IN_REGS) {
+      if (a.q_digits != nullptr) {
+        const int jr = QN > 1 ? lj >> 2 : 0;
+        load_query_operand<FF, LW>(a.q_digits + RQ_OF_PAIR(qj, jr) * D + (lj & 3) * (D / 4), lg, qa);
+      } else {  // through the pools' and the list's memory, which is not in use yet
+        uint32_t* dst = reinterpret_cast<uint32_t*>(smem_raw);
 #pragma unroll
-    for (int j0 = 0; j0 < QN; j0 += JB) {
-      float sv[JB][PER];
+        for (int j = 0; j < QN; ++j) stage_digits<D>(dst + j * D, D / 4, nullptr, a.q_stage, digit_factor(dlj[j]), qj[j], lane);
+        __syncthreads();
+        load_query_operand<FF, LW>(dst + (lj & (4 * QN - 1)) * (D / 4), lg, qa);
+        __syncthreads();
+      }
+    } else {
+      // (wide codes: the operand, up to 64 registers, stays in LDS; from there it is read once per 16 candidates)
 #pragma unroll
-      for (int jj = 0; jj < JB; ++jj)
-#pragma unroll
-        for (int u = 0; u < PER; ++u) sv[jj][u] = a.q_stage[qj[j0 + jj] * DD + min(u * 64 + lane, DD - 1)];
-#pragma unroll
-      for (int jj = 0; jj < JB; ++jj)
-#pragma unroll
-        for (int u = 0; u < PER; ++u) sv[jj][u] = pinned(sv[jj][u]);
-#pragma unroll
-      for (int jj = 0; jj < JB; ++jj)
-#pragma unroll
-        for (int u = 0; u < PER; ++u)
-          if (u * 64 + lane < DD) qf[(j0 + jj) * QROW + (u * 64 + lane) + QPAD * ((u * 64 + lane) / QCH)] = sv[jj][u];
+      for (int j = 0; j < QN; ++j)
+        stage_digits<D>(qdig + j * RS::LDS_WORDS, RS::ROW, a.q_digits, a.q_stage, digit_factor(dlj[j]), qj[j], lane);
     }
   }
   __syncthreads();
@@ -689,20 +669,24 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int item) {
   // condition: a lane without a candidate repeats the list's last one, so a round's code words, factors and id are
   // requested together, and the next round's are requested before the current round is worked on.
   struct Cand {
-    uint32_t w[RefineShape<LW>::WPL];
+    uint32_t w[RS::WPL];
     float2 lf;
-    int id, j;
-    bool valid;
+    int id;
+    bool mine;  // a candidate of the pair whose sums this lane receives
   };
   auto request = [&](int base, Cand& c_) {
-    const int idx = base + lane / G;
-    c_.valid = idx < list_cnt;
+    const int idx = base + lj;
     const uint32_t e = list[min(idx, list_cnt - 1)];
-    c_.j = (int)(e >> 30);
+    c_.mine = idx < list_cnt && (int)(e >> 30) == lg;
     const int64_t slot = (int64_t)t0 * TILE + (e & 0x3fffffffu);
-    refine_load<FF, LW>(a.long_codes + slot * LW, lane % G, c_.w);
+    refine_load<FF, LW>(a.long_codes + slot * LW, lg, c_.w);
     c_.lf = *reinterpret_cast<const float2*>(a.long_factors + 2 * slot);
     c_.id = a.ids[slot];
+  };
+  auto operand = [&](int kc) -> v4i {
+    if (RS::IN_REGS) return qa[kc];
+    const uint32_t* row = qdig + ((lj & (4 * QN - 1)) >> 2) * RS::LDS_WORDS + (lj & 3) * RS::ROW;
+    return *reinterpret_cast<const v4i*>(row + RS::word(4 * kc / RS::QPW, lg) * RS::QPW);
   };
   auto flush = [&]() {
     __syncthreads();
@@ -722,32 +706,30 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int item) {
         RQ_STAT(1, 1);
         const Cand cur = ring[d];
         if (rb + AHEAD * NS < list_cnt) request(rb + AHEAD * NS, ring[d]);
-        const int t = lane % G, j = cur.j;
-        const float ip = group_sum<G>(refine_dot<FF, LW>(cur.w, qf + j * QROW + t * QPAD, t));
-        if (cur.valid && t == 0) {
-          const float eB = qs[2 * j] + cur.lf.x + cur.lf.y * (ip - qs[2 * j + 1]);
-          const uint64_t key = make_key(eB, (uint32_t)cur.id);
-          if (key <= pool_kth[j]) {
-            const int pos = atomicAdd(&pool_cnt[j], 1);
-            pools[(size_t)j * a.pool + pos] = key;
-          }
-        }
+        const float ip = digit_sum(refine_mfma<FF, LW>(cur.w, a.flip, operand), unit_g);
+        const float eB = G_g + cur.lf.x + cur.lf.y * (ip - csq_g);
+        const uint64_t key = make_key(eB, (uint32_t)cur.id);
+        const bool take = cur.mine && key <= kth_g;
+        const uint32_t m = (uint32_t)(__ballot(take) >> (16 * lg)) & 0xffffu;  // of this lane's pair
+        if (take) pools[(size_t)jg * a.pool + cnt_g + __popc(m & ((1u << lj) - 1u))] = key;
+        cnt_g += __popc(m);
       }
       // a pool that could not take the keys of another AHEAD rounds is cut to its k best (pool >= k + 64 >= k + AHEAD * NS)
-      __syncthreads();
-#pragma unroll
-      for (int jj = 0; jj < QN; ++jj) {
-        const int cj = pool_cnt[jj];
-        if (cj + AHEAD * NS > a.pool) {
-          RQ_STAT(2, 1);
-          uint64_t* pool = pools + (size_t)jj * a.pool;
-          const int nc = pool_compact(pool, a.pool, cj, a.k);
-          if (lane == 0) {
-            pool_cnt[jj] = nc;
-            if (nc >= a.k) pool_kth[jj] = pool[a.k - 1];
+      if (__ballot(cnt_g + AHEAD * NS > a.pool) != 0ull) {
+#pragma unroll 1
+        for (int jj = 0; jj < QN; ++jj) {
+          const int cj = __builtin_amdgcn_readlane(cnt_g, 16 * jj);
+          if (cj + AHEAD * NS > a.pool) {
+            RQ_STAT(2, 1);
+            uint64_t* pool = pools + (size_t)jj * a.pool;
+            const int nc = pool_compact(pool, a.pool, cj, a.k);
+            if (jg == jj) {
+              cnt_g = nc;
+              if (nc >= a.k) kth_g = pool[a.k - 1];
+            }
           }
-          __syncthreads();
         }
+        __syncthreads();
       }
     }
     list_cnt = 0;
@@ -755,7 +737,7 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int item) {
 
   if (MASKED) {
     // The first stage is done: the survivor bits of MASK_BATCH / 16 tiles are turned into list entries at a time.  A
-    // block holds, for each of the 4 groups of 4 pairs and each lj = 0..15, a 16-bit word about vectors 16 cb + lj and
+    // block holds, for each of the 4 groups of 4 pairs and each lj = 0..15, a 16-bit word about vectors 4 lj + cb and
     // pairs r of the group: bit 4 cb + r set = does not survive.  Lane l < MASK_BATCH takes word (tile wb / 16 + l / 16,
     // this item's group mg, lj = l % 16).
     const int nwords = (te - ts) * 16;
@@ -780,10 +762,10 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int item) {
       const int total = __builtin_amdgcn_readlane(incl, MASK_BATCH - 1);
       if (list_cnt + total > LCAP) flush();
       int pos = list_cnt + incl - mine_n;
-      const uint32_t pos0 = (uint32_t)((ts - t0 + (wi >> 4)) * TILE + (wi & 15));
+      const uint32_t pos0 = (uint32_t)((ts - t0 + (wi >> 4)) * TILE + 4 * (wi & 15));
       while (field != 0u) {
         const int b = __ffs(field) - 1;  // bit 4 cb + r
-        list[pos++] = ((uint32_t)(b & 3) << 30) | (pos0 + 16u * (uint32_t)(b >> 2));
+        list[pos++] = ((uint32_t)(b & 3) << 30) | (pos0 + (uint32_t)(b >> 2));
         field &= field - 1u;
       }
       list_cnt += total;
@@ -887,8 +869,9 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int item) {
   }
   if (F > 0) {
     flush();
+    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < QN; ++j) cnt[j] = pool_cnt[j];
+    for (int j = 0; j < QN; ++j) cnt[j] = __builtin_amdgcn_readlane(cnt_g, 16 * j);
   }
   // every key still in a pool goes out, unsorted; the per-query merge selects among them.
   // The segments of a split cluster share the pair's region (cand_cnt starts at 0 and is
@@ -937,7 +920,7 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int item) {
 }
 
 template <int W, int F, bool DBG, int M, int PFD = 0, bool MASKED = false>
-__global__ __launch_bounds__(64) void scan_kernel(ScanArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W <= 4 && M == 0 ? (F == 8 ? 6 : 7) : 1))) void scan_kernel(ScanArgs a) {
   // XCD-aware order: workgroups are dealt round-robin to the 8 XCDs, so give each XCD a
   // contiguous range of work items; items of one cluster then share one L2.
   // (the grid is an upper bound of the number of work items; the ranges are cut from the true count)
@@ -971,7 +954,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void sc
   scan_stream_items<W, 0, DBG>(a);
 }
 template <int W, int F, bool DBG>
-__global__ __launch_bounds__(64) void scan_stream_long_kernel(ScanArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W <= 4 ? 5 : 1))) void scan_stream_long_kernel(ScanArgs a) {
   scan_stream_items<W, F, DBG>(a);
 }
 
@@ -991,9 +974,12 @@ __global__ __launch_bounds__(64) void scan_stream_long_kernel(ScanArgs a) {
 // wide ones, where a tile keeps a wavefront busy for longer and the barrier after every round of tiles weighs more
 // (D = 960: 0.97 ms with four, 0.86 ms with two, 0.86 ms with one; D = 128: 0.32 / 0.38 / 0.45 ms)
 __host__ __device__ constexpr int mfma_waves(int W) { return W >= 16 ? 2 : 4; }
-constexpr int MLIST_FLUSH = 128;              // an owner list longer than this is refined before the next tiles
-// + what one round of tiles can add: every wavefront a tile, 64 vectors x QM / n queries per owner
-__host__ __device__ constexpr int mlist_cap(int n) { return MLIST_FLUSH + n * TILE * (QM / n); }
+// Survivor lists, one per 4 queries (the refinement takes 16 candidates of 4 queries at a time): list l holds those of
+// queries 4 i + l and belongs to wavefront l % n.
+constexpr int MLISTS = 4;
+constexpr int MLIST_FLUSH = 128;              // a list longer than this is refined before the next tiles
+// + what one round of tiles can add: every wavefront a tile, 64 vectors x 4 queries per list
+__host__ __device__ constexpr int mlist_cap(int n) { return MLIST_FLUSH + n * TILE * (QM / MLISTS); }
 
 // A decision every wavefront of the workgroup must take alike, although each of them computes it from LDS counters
 // that faster wavefronts may already be advancing: the first wavefront to arrive fixes the value in `slot` (which
@@ -1017,24 +1003,24 @@ __device__ inline int block_pool_compact(uint64_t* pool, int pool_n, int cnt, in
 }
 
 // Work split inside the workgroup of n = mfma_waves(W) wavefronts: every wavefront scans every n-th tile for all 16
-// queries, but survivors are filed by OWNER: query j belongs to wavefront j % n, which alone
+// queries, but survivors are filed by OWNER: query j is in list j % 4 of wavefront (j % 4) % n, which alone
 // refines them and keeps that query's pool.  Refinement therefore needs no workgroup
 // barrier; the wavefronts only meet once per round of tiles.
 template <int W, int F, bool DBG>
 __global__ __launch_bounds__(64 * mfma_waves(W)) void scan_mfma_kernel(ScanArgs a) {
   constexpr int FF = (F > 0 ? F : 8), LW = W * FF, KC = (W + 1) / 2;
   constexpr int MWAVES = mfma_waves(W), MLIST_CAP = mlist_cap(MWAVES);
-  constexpr int G = RefineShape<LW>::G, NS = RefineShape<LW>::NS;
+  constexpr int NS = RefineShape<FF, LW>::NS;
   extern __shared__ unsigned char smem_raw[];
   uint64_t* pools = reinterpret_cast<uint64_t*>(smem_raw);          // [QM][pool]
   uint64_t* pool_kth = pools + (size_t)QM * a.pool;                 // [QM]
-  float* qs = reinterpret_cast<float*>(pool_kth + QM);              // [QM][2]: G, cB*sum(q')
-  int* pool_cnt = reinterpret_cast<int*>(qs + 2 * QM);              // [QM]
+  float* qs = reinterpret_cast<float*>(pool_kth + QM);              // [QM][3]: G, cB*sum(q'), delta
+  int* pool_cnt = reinterpret_cast<int*>(qs + 3 * QM);              // [QM]
   int* qidx = pool_cnt + QM;                                        // [QM] query of each pair
-  int* s_list_cnt = qidx + QM;                                      // [MWAVES] entries in each owner list
-  int* s_out = s_list_cnt + MWAVES;                                 // [QM] first output slot of each pair
+  int* s_list_cnt = qidx + QM;                                      // [MLISTS] entries in each list
+  int* s_out = s_list_cnt + MLISTS;                                 // [QM] first output slot of each pair
   uint32_t* s_agree = reinterpret_cast<uint32_t*>(s_out + QM);      // [2] per-round decisions (wave_agree), by round parity
-  uint32_t* lists = s_agree + 2;                                    // [MWAVES][MLIST_CAP] (F > 0)
+  uint32_t* lists = s_agree + 2;                                    // [MLISTS][MLIST_CAP] (F > 0)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lj = lane & 15, g = lane >> 4;
 
   const int n_items = a.item_off[a.nlist];
@@ -1065,12 +1051,13 @@ __global__ __launch_bounds__(64 * mfma_waves(W)) void scan_mfma_kernel(ScanArgs 
     }
     if (tid < QM) {  // one thread per pair fills the shared per-pair state
       qidx[lj] = (int)q;
-      qs[2 * lj] = a.probe_G[pp];
-      qs[2 * lj + 1] = a.cB * a.sum_q[q];
+      qs[3 * lj] = a.probe_G[pp];
+      qs[3 * lj + 1] = a.cB * a.sum_q[q];
+      qs[3 * lj + 2] = a.delta[q];
       pool_kth[lj] = KEY_NONE;
       pool_cnt[lj] = 0;
     }
-    if (tid < MWAVES) s_list_cnt[tid] = 0;
+    if (tid < MLISTS) s_list_cnt[tid] = 0;
     if (tid < 2) s_agree[tid] = AGREE_UNSET;
   }
   // scalars of this lane's four queries (rows 4g .. 4g+3; query 4g+r is owned by wavefront r)
@@ -1110,62 +1097,57 @@ __global__ __launch_bounds__(64 * mfma_waves(W)) void scan_mfma_kernel(ScanArgs 
     }
   };
 
-  // F > 0: this wavefront refines its own list (queries j with j % MWAVES == wave) into its own pools
-  // (nothing is fetched under a condition: a lane without a candidate repeats the list's last one, so a round's code
-  // words, factors and id are requested together, and the next round's before the current round is worked on)
-  struct Cand {
-    uint32_t w[RefineShape<LW>::WPL];
-    float2 lf;
-    int id, j;
-    bool valid;
-  };
+  // F > 0: this wavefront refines its lists, 16 candidates at a time: the sums of query 4 i + l arrive in lanes 16 i .. 16 i + 15,
+  // which hold that query's scalars and pool state meanwhile
   auto flush_own = [&]() {
-    uint32_t* list = lists + (size_t)wave * MLIST_CAP;
-    const int list_cnt = s_list_cnt[wave];
-    auto request = [&](int base, Cand& c_) {
-      const int idx = base + lane / G;
-      c_.valid = idx < list_cnt;
-      const uint32_t e = list[min(idx, list_cnt - 1)];
-      c_.j = (int)(e >> 28);
-      const int64_t slot = (int64_t)t0 * TILE + (e & 0x0fffffffu);
-      refine_load<FF, LW>(a.long_codes + slot * LW, lane % G, c_.w);
-      c_.lf = *reinterpret_cast<const float2*>(a.long_factors + 2 * slot);
-      c_.id = a.ids[slot];
-    };
-    Cand nxt;
-    if (list_cnt > 0) request(0, nxt);
-    for (int base = 0; base < list_cnt; base += NS) {
-      const Cand cur = nxt;
-      if (base + NS < list_cnt) request(base + NS, nxt);
-      const int t = lane % G, j = cur.j;
-      const float* qrow = a.q_stage + (int64_t)qidx[j] * a.D;
-      const float ip = group_sum<G>(refine_dot<FF, LW>(cur.w, qrow, t));
-      if (cur.valid && t == 0) {
-        const float eB = qs[2 * j] + cur.lf.x + cur.lf.y * (ip - qs[2 * j + 1]);
-        const uint64_t key = make_key(eB, (uint32_t)cur.id);
-        if (key <= pool_kth[j]) {
-          const int pos = atomicAdd(&pool_cnt[j], 1);
-          pools[(size_t)j * a.pool + pos] = key;
+    for (int l = wave; l < MLISTS; l += MWAVES) {
+      const uint32_t* list = lists + (size_t)l * MLIST_CAP;
+      const int list_cnt = s_list_cnt[l];
+      if (list_cnt == 0) continue;
+      const int jq = 4 * g + l, jr = 4 * (lj >> 2) + l;  // the query whose sums arrive here, the one this lane's left row is of
+      const int64_t qr = qidx[jr];
+      const float G_q = qs[3 * jq], csq_q = qs[3 * jq + 1], unit_q = digit_unit(qs[3 * jq + 2]), factor_r = digit_factor(qs[3 * jr + 2]);
+      uint64_t* pool = pools + (size_t)jq * a.pool;
+      uint64_t kth = pool_kth[jq];
+      int cnt = pool_cnt[jq];
+      for (int base = 0; base < list_cnt; base += NS) {
+        const int idx = base + lj;
+        const uint32_t e = list[min(idx, list_cnt - 1)];
+        const int64_t slot = (int64_t)t0 * TILE + (e & 0x0fffffffu);
+        const float2 lf = *reinterpret_cast<const float2*>(a.long_factors + 2 * slot);
+        const int id = a.ids[slot];
+        const float ip = digit_sum(refine_mfma_from_memory<FF, LW>(a.long_codes + slot * LW, a.q_digits, a.q_stage, factor_r, qr,
+                                                                   lj & 3, g, a.flip), unit_q);
+        const float eB = G_q + lf.x + lf.y * (ip - csq_q);
+        const uint64_t key = make_key(eB, (uint32_t)id);
+        const bool take = idx < list_cnt && (int)(e >> 28) == g && key <= kth;
+        const uint32_t m = (uint32_t)(__ballot(take) >> (16 * g)) & 0xffffu;
+        if (take) pool[cnt + __popc(m & ((1u << lj) - 1u))] = key;
+        cnt += __popc(m);
+        if (__ballot(cnt + NS > a.pool) != 0ull) {
+#pragma unroll 1
+          for (int i = 0; i < 4; ++i) {
+            const int cj = __builtin_amdgcn_readlane(cnt, 16 * i);
+            if (cj + NS > a.pool) {
+              uint64_t* full = pools + (size_t)(4 * i + l) * a.pool;
+              const int nc = wave_pool_compact(full, a.pool, cj, a.k, lane);
+              if (g == i) {
+                cnt = nc;
+                if (nc >= a.k) kth = full[a.k - 1];
+              }
+              wave_sync();
+            }
+          }
         }
       }
       wave_sync();
-#pragma unroll
-      for (int rr = 0; rr < QM / MWAVES; ++rr) {  // the pools this wavefront owns
-        const int jj = MWAVES * rr + wave;
-        const int cj = pool_cnt[jj];
-        if (cj + NS > a.pool) {
-          uint64_t* pool = pools + (size_t)jj * a.pool;
-          const int nc = wave_pool_compact(pool, a.pool, cj, a.k, lane);
-          if (lane == 0) {
-            pool_cnt[jj] = nc;
-            if (nc >= a.k) pool_kth[jj] = pool[a.k - 1];
-          }
-          wave_sync();
-        }
+      if (lj == 0) {
+        pool_cnt[jq] = cnt;
+        pool_kth[jq] = kth;
       }
+      if (lane == 0) s_list_cnt[l] = 0;
     }
     wave_sync();
-    if (lane == 0) s_list_cnt[wave] = 0;
   };
 
   // pools that could not take `room` more keys (lane jj looks at pool jj); wave-uniform
@@ -1181,7 +1163,7 @@ __global__ __launch_bounds__(64 * mfma_waves(W)) void scan_mfma_kernel(ScanArgs 
     if (tid == 0) s_agree[round ^ 1] = AGREE_UNSET;
     if (F > 0) {
       int longest = 0;
-      for (int ww = 0; ww < MWAVES; ++ww) longest = max(longest, s_list_cnt[ww]);
+      for (int ww = 0; ww < MLISTS; ++ww) longest = max(longest, s_list_cnt[ww]);
       if (wave_agree(&s_agree[round], longest > MLIST_FLUSH ? 1u : 0u, lane)) {
         flush_own();
         __syncthreads();
@@ -1240,9 +1222,9 @@ __global__ __launch_bounds__(64 * mfma_waves(W)) void scan_mfma_kernel(ScanArgs 
             if (F == 0) {  // B == 1: the 1-bit estimate is the final key
               const uint64_t key = make_key(e1, (uint32_t)a.ids[(int64_t)tile * TILE + v]);
               if (key <= pool_kth[j]) pools[(size_t)j * a.pool + atomicAdd(&pool_cnt[j], 1)] = key;
-            } else {       // file the survivor with the owner of query j (= wavefront r % MWAVES)
-              const int pos = atomicAdd(&s_list_cnt[r % MWAVES], 1);
-              lists[(size_t)(r % MWAVES) * MLIST_CAP + pos] = ((uint32_t)j << 28) | (uint32_t)((tile - t0) * TILE + v);
+            } else {       // file the survivor in the list of query j
+              const int pos = atomicAdd(&s_list_cnt[r], 1);
+              lists[(size_t)r * MLIST_CAP + pos] = ((uint32_t)g << 28) | (uint32_t)((tile - t0) * TILE + v);
             }
           }
         }
@@ -1295,7 +1277,7 @@ __global__ __launch_bounds__(64 * mfma_waves(W)) void scan_mfma_kernel(ScanArgs 
 template <int W, int F>
 static void launch_seed_wf(const ScanArgs& a, int impl, int64_t nq, hipStream_t st) {
   const int kpad = next_pow2(std::max(a.k, SEED_M));
-  const size_t smem = (size_t)(SEED_CHUNK_TILES * TILE + 2 * kpad) * sizeof(uint64_t) + (size_t)a.D * sizeof(float);
+  const size_t smem = (size_t)(SEED_CHUNK_TILES * TILE + 2 * kpad) * sizeof(uint64_t);
   if (impl == 2)
     hipLaunchKernelGGL((seed_kernel<W, F>), dim3((unsigned)nq), dim3(256), smem + (size_t)W * 256, st, a);
   else if (nq <= 2048)  // few queries: four wavefronts per query
@@ -1309,8 +1291,8 @@ template <int W, int F>
 static void launch_scan_mfma_wf(const ScanArgs& a, unsigned grid, bool dbg, hipStream_t st) {
   constexpr int MWAVES = mfma_waves(W), MLIST_CAP = mlist_cap(MWAVES);
   const size_t smem = (size_t)QM * a.pool * sizeof(uint64_t) +
-                      QM * (sizeof(uint64_t) + 2 * sizeof(float) + 2 * sizeof(int)) + (MWAVES + QM + 2) * sizeof(int) +
-                      (F > 0 ? (size_t)MWAVES * MLIST_CAP * sizeof(uint32_t) : 0);
+                      QM * (sizeof(uint64_t) + 3 * sizeof(float) + 2 * sizeof(int)) + (MLISTS + QM + 2) * sizeof(int) +
+                      (F > 0 ? (size_t)MLISTS * MLIST_CAP * sizeof(uint32_t) : 0);
   if (dbg)
     hipLaunchKernelGGL((scan_mfma_kernel<W, F, true>), dim3(grid), dim3(64 * MWAVES), smem, st, a);
   else
@@ -1322,9 +1304,10 @@ static void launch_scan_wf(const ScanArgs& a, unsigned grid, bool dbg, hipStream
   const bool masked = M == 0 && F > 0 && a.surv_mask != nullptr;  // second half of the split search
   const bool stream = M == 0 && a.streaming && !masked;
   const int qn = stream ? 1 : QW;  // pairs per work item
-  const size_t smem = (size_t)qn * a.pool * sizeof(uint64_t) + qn * (sizeof(uint64_t) + 2 * sizeof(float) + sizeof(int)) +
-                      (F > 0 ? (masked ? LIST_CAP_MASKED : LIST_CAP) * sizeof(uint32_t) +
-                                   (size_t)qn * (a.D + 4 * RefineShape<W * (F > 0 ? F : 8)>::G) * sizeof(float) : 0) +
+  constexpr int FF = F > 0 ? F : 8;
+  const size_t smem = (size_t)qn * a.pool * sizeof(uint64_t) +
+                      (F > 0 ? ((masked ? LIST_CAP_MASKED : LIST_CAP) + (size_t)qn * RefineShape<FF, W * FF>::LDS_WORDS) * sizeof(uint32_t)
+                             : 0) +
                       (M == 1 ? (size_t)qn * W * 256 : 0);
   if (masked)  // (estimate_mfma_kernel ran)
     hipLaunchKernelGGL((scan_kernel<W, F, false, M, 0, (M == 0 && F > 0)>), dim3(grid), dim3(64), smem, st, a);

@@ -80,23 +80,24 @@ __global__ __launch_bounds__(NT) void item_offsets_kernel(const int32_t* __restr
   }
 }
 
-// One wavefront per cluster writes the descriptors of its work items of QW pairs (split search).
+// One wavefront per cluster writes the descriptors of its work items of qw pairs: 4 of the split search (with their first block
+// of survivor bits), 16 of the group scan (mask_off == nullptr).
 __global__ __launch_bounds__(64) void item_desc_kernel(const int32_t* __restrict__ pair_off, const int32_t* __restrict__ tile_off,
                                                       const int32_t* __restrict__ item_off, const uint32_t* __restrict__ mask_off,
-                                                      int tseg, int segmax, ItemDesc* __restrict__ desc) {
-  const int c = blockIdx.x;
-  const int i0 = item_off[c], n = item_off[c + 1] - i0;
+                                                      const int32_t* __restrict__ order, int qw, int tseg, int segmax, ItemDesc* __restrict__ desc) {
+  const int i0 = item_off[blockIdx.x], n = item_off[blockIdx.x + 1] - i0;
   if (n <= 0) return;
+  const int c = order != nullptr ? order[blockIdx.x] : (int)blockIdx.x;
   const int t0 = tile_off[c], tiles = tile_off[c + 1] - t0;
   const int p0 = pair_off[c], cnt = pair_off[c + 1] - p0;
   const int nseg = seg_count(tiles, tseg, segmax);
   const int seglen = (tiles + nseg - 1) / nseg;
-  const uint32_t m0 = mask_off[c];
+  const uint32_t m0 = mask_off != nullptr ? mask_off[c] : 0u;
   for (int it = threadIdx.x; it < n; it += 64) {
     const int grp = it / nseg, sidx = it - grp * nseg;
     ItemDesc d;
-    d.pbeg = p0 + grp * QW;
-    d.np_mg = min(QW, cnt - grp * QW) | ((grp & 3) << 8);
+    d.pbeg = p0 + grp * qw;
+    d.np_mg = min(qw, cnt - grp * qw) | ((grp & 3) << 8);
     d.t0 = t0;
     d.ts = t0 + sidx * seglen;
     d.te = min(t0 + tiles, d.ts + seglen);
@@ -178,7 +179,8 @@ int64_t split_mask_blocks(rabitq_index* ix, int64_t nq, int nprobe) {
 static bool stream_shape(const rabitq_index* ix, int64_t nq, int nprobe) {
   return effective_impl(ix) == 0 && nq * nprobe <= 4 * (int64_t)ix->nlist && !split_wanted(ix, nq, nprobe);
 }
-static ScanPlan plan_for(const rabitq_index* ix, int64_t nq, int nprobe, int k, bool streaming);
+static ScanPlan plan_for(const rabitq_index* ix, int64_t nq, int nprobe, int k, bool streaming, bool group = false);
+static ScanPlan group_plan(const rabitq_index* ix, int64_t nq, int nprobe, int k) { return plan_for(ix, nq, nprobe, k, false, true); }
 // descriptor slots (of sizeof(ItemDesc)) the prefetching variant needs for (nq, nprobe, k)
 // work items of one pair: a pair has as many as its list has segments, at most those of the longest list
 static int64_t stream_item_bound(const rabitq_index* ix, int64_t nq, int nprobe, const ScanPlan& plan) {
@@ -203,11 +205,28 @@ int ensure_stream_buffers(rabitq_index* ix, int64_t nq, int nprobe, int k) {
   return RABITQ_OK;
 }
 
+ScanRoute scan_route(rabitq_index* ix, int64_t nq, int nprobe, int k) {
+  if (ix->item_desc == nullptr) return ROUTE_SINGLE;
+  if (group_wanted(ix, nq, nprobe)) {
+    const ScanPlan plan = group_plan(ix, nq, nprobe, k);
+    update_seg_cache(ix, plan.tseg, plan.segmax);
+    if (item_bound(ix, nq, nprobe, plan.qw) <= ix->item_desc_cap) return ROUTE_GROUP;
+  } else if (split_wanted(ix, nq, nprobe) && ix->surv_mask != nullptr) {
+    const ScanPlan plan = plan_for(ix, nq, nprobe, k, false);
+    update_seg_cache(ix, plan.tseg, plan.segmax);
+    if (split_mask_blocks(ix, nq, nprobe) <= ix->surv_mask_blocks && item_bound(ix, nq, nprobe, plan.qw) <= ix->item_desc_cap)
+      return ROUTE_SPLIT;
+  }
+  return ROUTE_SINGLE;
+}
+
 int ensure_split_buffers(rabitq_index* ix, int64_t nq, int nprobe, int k) {
-  const int64_t need = split_mask_blocks(ix, nq, nprobe);
-  const ScanPlan plan = scan_plan(ix, nq, nprobe, k);
+  if (!group_wanted(ix, nq, nprobe) && !split_wanted(ix, nq, nprobe)) return RABITQ_OK;
+  const bool group = group_wanted(ix, nq, nprobe);  // (keeps its survivors to itself)
+  const int64_t need = group ? 0 : split_mask_blocks(ix, nq, nprobe);
+  const ScanPlan plan = plan_for(ix, nq, nprobe, k, false, group);
   update_seg_cache(ix, plan.tseg, plan.segmax);
-  const int64_t items = item_bound(ix, nq, nprobe, QW);
+  const int64_t items = item_bound(ix, nq, nprobe, plan.qw);
   if (need <= ix->surv_mask_blocks && items <= ix->item_desc_cap) return RABITQ_OK;
   if (need >= ((int64_t)1 << 32) || items > 0x7fffffff) return RABITQ_OK;  // beyond 32-bit offsets: the search is not split
   RQ_HIP(hipDeviceSynchronize());
@@ -259,7 +278,8 @@ static ScanArgs base_args(const rabitq_index* ix) {
   a.B = ix->total_bits;
   a.LW = ix->LW;
   a.nlist = ix->nlist;
-  a.cB = (float)(((1 << ix->total_bits) - 1) * 0.5);
+  a.flip = ix->total_bits == 8 ? 0x80808080u : 0u;
+  a.cB = (float)(((1 << ix->total_bits) - 1) * 0.5 - (a.flip ? 128.0 : 0.0));
   a.qerr = effective_impl(ix) == 2 ? 0.f : (float)((ix->dim - 1.0) / (12.0 * (1.0 - 2.0 / 3.14159265358979323846)));
   return a;
 }
@@ -269,8 +289,12 @@ static int bad_width() {
   return RABITQ_EINVAL;
 }
 
-static void set_repr(ScanArgs& a, const rabitq_index* ix, const rabitq_query_repr& r) {
-  a.q_stage = r.q_stage; a.qhat8 = r.qhat8; a.Dp = qhat_stride(ix->dim);
+static void set_repr(ScanArgs& a, const rabitq_index* ix, const rabitq_query_repr& r, int form) {
+  const bool digits = (form & QUERY_DIGITS) != 0;
+  a.qhat_fp8 = (form & QUERY_FP8) != 0;
+  a.q_stage = digits ? nullptr : r.q_stage;
+  a.q_digits = digits ? reinterpret_cast<const uint32_t*>(r.q_stage) : nullptr;
+  a.qhat8 = r.qhat8; a.Dp = qhat_stride(ix->dim);
   a.planes = r.planes; a.delta = r.delta; a.sum_qhat = r.sum_qhat; a.sum_q = r.sum_q; a.lut = r.lut;
 }
 
@@ -289,12 +313,12 @@ int launch_clear_counters(int32_t* cand_cnt, int64_t n, hipStream_t st) {
   return RABITQ_OK;
 }
 
-int launch_seed(const rabitq_index* ix, const rabitq_query_repr& repr, const int32_t* probe_ids, const float* probe_G,
+int launch_seed(const rabitq_index* ix, const rabitq_query_repr& repr, int form, const int32_t* probe_ids, const float* probe_G,
                 const float* probe_E, int64_t nq, int k, int nprobe, float* tau, hipStream_t st) {
   if (nq <= 0) return RABITQ_OK;
   if (int rc = need_lut(ix, repr)) return rc;
   ScanArgs a = base_args(ix);
-  set_repr(a, ix, repr);
+  set_repr(a, ix, repr, form);
   a.probe_ids = probe_ids; a.probe_G = probe_G; a.probe_E = probe_E;
   set_nprobe(a, nprobe); a.k = k; a.tau_out = tau;
   const int W = ix->W, F = field_bits(ix->total_bits);
@@ -309,16 +333,17 @@ int launch_seed(const rabitq_index* ix, const rabitq_query_repr& repr, const int
 // contributes at most k keys to the pair's region of cand_stride keys (cand_cnt is advanced atomically).  The segment
 // length adapts to the batch: a large batch has more work items than the chip has wavefront slots and keeps long
 // segments (32 tiles); a small batch is cut finer, down to 2 tiles, so that about 4096 items exist.
-static ScanPlan plan_for(const rabitq_index* ix, int64_t nq, int nprobe, int k, bool streaming) {
+static ScanPlan plan_for(const rabitq_index* ix, int64_t nq, int nprobe, int k, bool streaming, bool group) {
   ScanPlan p;
   p.streaming = streaming;
-  p.qw = effective_impl(ix) == 1 ? QM : (p.streaming ? 1 : QW);
+  p.qw = group || effective_impl(ix) == 1 ? QM : (p.streaming ? 1 : QW);
   const int64_t np_all = nq * nprobe;
   const int64_t est_items = std::min<int64_t>(np_all, (np_all + p.qw - 1) / p.qw + ix->nlist);
   const int64_t avg_tiles = std::max<int64_t>(1, ix->n_tiles / std::max(1, ix->nlist));
   p.tseg = (int)std::min<int64_t>(32, std::max<int64_t>(2, est_items * avg_tiles / 4096));
   if (ix->seg_tiles > 0) p.tseg = ix->seg_tiles;
   p.segmax = std::max(1, next_pow2_host(k + TILE) / k);
+  if (group && group_narrow(ix->W)) p.segmax = 1;  // (a wavefront owns its pairs' candidate regions)
   return p;
 }
 
@@ -362,7 +387,7 @@ int launch_small_select_seed(const rabitq_index* ix, const rabitq_query_repr& re
     return RABITQ_EINVAL;
   }
   ScanArgs a = base_args(ix);
-  set_repr(a, ix, repr);
+  set_repr(a, ix, repr, QUERY_DIGITS);  // (qhat8 is not read)
   a.probe_ids = probe_ids; a.probe_G = probe_G; a.probe_E = probe_E;
   set_nprobe(a, nprobe); a.k = k; a.tau_out = tau;
   SmallSelectArgs b{};
@@ -384,16 +409,20 @@ int launch_small_select_seed(const rabitq_index* ix, const rabitq_query_repr& re
   return RABITQ_OK;
 }
 
-int launch_scan(const rabitq_index* ix, const rabitq_query_repr& repr, const float* probe_G, const float* probe_E,
+int launch_scan(rabitq_index* ix, const rabitq_query_repr& repr, int form, const float* probe_G, const float* probe_E,
                 const int32_t* pair_off, const int32_t* pair_ids, const float* tau, int64_t nq, int k, int nprobe,
                 uint64_t* cand_keys, int32_t* cand_cnt, int32_t* dbg_ip, const int64_t* dbg_off, const ScanStreams& ss) {
   if (nq <= 0) return RABITQ_OK;
   const hipStream_t st = ss.main, sst = ss.setup;
   if (int rc = need_lut(ix, repr)) return rc;
   ScanArgs a = base_args(ix);
-  set_repr(a, ix, repr);
+  set_repr(a, ix, repr, form);
   const int impl = effective_impl(ix);
-  const ScanPlan plan = scan_plan(ix, nq, nprobe, k);
+  // Many pairs per list: groups of 16 pairs, estimates on the matrix cores (group scan or split search), where the handle's
+  // buffers are large enough (ensure_split_buffers, called by the entry points that may allocate).
+  const ScanRoute route = scan_route(ix, nq, nprobe, k);
+  const bool group = route == ROUTE_GROUP, split = route == ROUTE_SPLIT;
+  const ScanPlan plan = route == ROUTE_SINGLE ? scan_plan(ix, nq, nprobe, k) : plan_for(ix, nq, nprobe, k, false, group);
   const int qw = plan.qw;
   a.probe_G = probe_G; a.probe_E = probe_E; a.pair_off = pair_off; a.pair_ids = pair_ids; a.tau = tau;
   set_nprobe(a, nprobe); a.k = k;
@@ -416,27 +445,23 @@ int launch_scan(const rabitq_index* ix, const rabitq_query_repr& repr, const flo
   // ones for the end (the popcount kernel's own item table only: the small-batch builder and the split search keep
   // cluster order, where items of one cluster share a cache).
   if (a.streaming && !ss.setup_done && ix->longest_first && ix->cluster_order != nullptr) a.order = ix->cluster_order;
-  // Split search: the estimates of groups of 16 pairs on the matrix cores, then this kernel's refinement only.
-  // Chosen when asked for (scan_impl 4), built for the index, worth it for the batch, and the handle's buffer of
-  // survivor bits is large enough (ensure_split_buffers, called by the entry points that may allocate).
+  if (group) a.order = ix->cluster_order + ix->nlist;  // (dealt to the XCDs)
   if (!a.streaming) update_seg_cache(ix, a.tseg, a.segmax);
   const int64_t max_items = a.streaming ? stream_item_bound(ix, nq, nprobe, plan) : item_bound(ix, nq, nprobe, qw);
-  const bool split = split_wanted(ix, nq, nprobe) && ix->surv_mask != nullptr && ix->item_desc != nullptr &&
-                     split_mask_blocks(const_cast<rabitq_index*>(ix), nq, nprobe) <= ix->surv_mask_blocks &&
-                     max_items <= ix->item_desc_cap;
-  ss.split = split;
+  ss.split = split || group;
+  ss.estimated = split;
   ss.streamed = a.streaming != 0;
   int32_t* item16 = ix->tile_off + 2 * (ix->nlist + 1) + TICKET_WORDS;
   uint32_t* mask_off = reinterpret_cast<uint32_t*>(item16 + (ix->nlist + 1));
   if (ss.setup_b) RQ_HIP(hipEventRecord(ss.setup_b, sst));
   // (one launch for the item table and, when the search is split, the two tables of its first half; a small batch's
   // list builder has written the item table already, with the same values)
-  if (!ss.setup_done || split)
+  if (!ss.setup_done || split || group)
   {
     const bool small = ix->nlist <= SCAN_SMALL * SCAN_PER;
     auto table = split ? (small ? item_offsets_kernel<SCAN_SMALL, true, false> : item_offsets_kernel<SCAN_LARGE, true, false>)
                        : (small ? item_offsets_kernel<SCAN_SMALL, false, false> : item_offsets_kernel<SCAN_LARGE, false, false>);
-    if (a.order)  // (never together with the split search)
+    if (a.order)  // (streaming and group scan, never the split search)
       table = small ? item_offsets_kernel<SCAN_SMALL, false, true> : item_offsets_kernel<SCAN_LARGE, false, true>;
     hipLaunchKernelGGL(table, dim3(1), dim3(small ? SCAN_SMALL : SCAN_LARGE), 0, sst, pair_off, ix->tile_off, a.order,
                        ix->nlist, qw, a.tseg, a.segmax, item_off, item16, mask_off);
@@ -449,13 +474,16 @@ int launch_scan(const rabitq_index* ix, const rabitq_query_repr& repr, const flo
     hipLaunchKernelGGL(stream_desc_kernel, dim3((unsigned)ix->nlist), dim3(64), 0, sst, a,
                        reinterpret_cast<StreamDesc*>(ix->item_desc));
   }
-  if (split) {
+  if (split || group) {
     hipLaunchKernelGGL(item_desc_kernel, dim3((unsigned)ix->nlist), dim3(64), 0, sst, pair_off, ix->tile_off, item_off,
-                       mask_off, a.tseg, a.segmax, ix->item_desc);
+                       group ? nullptr : mask_off, a.order, qw, a.tseg, a.segmax, ix->item_desc);
+    a.item_desc = ix->item_desc;
+    if (group && !group_narrow(ix->W)) a.pool = group_pool(k);
+  }
+  if (split) {
     a.item_off16 = item16;
     a.mask_off = mask_off;
     a.surv_mask = ix->surv_mask;
-    a.item_desc = ix->item_desc;
     // (the refinement-only kernel lives on wavefronts in flight: smaller pools, checked every second round of 16 keys)
     a.pool = std::max(64, next_pow2_host(k + 32));
   }
@@ -470,8 +498,10 @@ int launch_scan(const rabitq_index* ix, const rabitq_query_repr& repr, const flo
     return RABITQ_EINVAL;
   }
   // (the prefetching variant's grid: the usual number of items, three for every two pairs, when the bound is larger;
-  // its workgroups go on to further items if there are more)
-  const unsigned grid = (unsigned)(a.streaming ? std::min<int64_t>(max_items, nq * nprobe + nq * nprobe / 2 + 1024) : max_items);
+  // its workgroups go on to further items if there are more.  So do the group scan's; its items are usually pairs / 16 and half
+  // a group per list, some of them more than once for their segments)
+  const int64_t usual = group ? (nq * nprobe / QM + ix->nlist) * 5 / 4 + 1024 : nq * nprobe + nq * nprobe / 2 + 1024;
+  const unsigned grid = (unsigned)(a.streaming || group ? std::min(max_items, (usual + 7) / 8 * 8) : max_items);
   const bool dbg = dbg_ip != nullptr;
   const int W = ix->W, F = field_bits(ix->total_bits);
   if (split) {
@@ -481,7 +511,9 @@ int launch_scan(const rabitq_index* ix, const rabitq_query_repr& repr, const flo
     RQ_HIP(hipGetLastError());
     if (ss.est_e) RQ_HIP(hipEventRecord(ss.est_e, st));
   }
-  if (!(scan_part0(a, W, F, impl, grid, dbg, st) || scan_part1(a, W, F, impl, grid, dbg, st) ||
+  if (group) {
+    if (!scan_group(a, W, F, grid, dbg, st)) return bad_width();
+  } else if (!(scan_part0(a, W, F, impl, grid, dbg, st) || scan_part1(a, W, F, impl, grid, dbg, st) ||
         scan_part2(a, W, F, impl, grid, dbg, st)))
     return bad_width();
   RQ_HIP(hipGetLastError());

@@ -12,21 +12,22 @@ namespace rq {
 // ---------------------------------------------------------------------------------
 template <int F>
 __global__ __launch_bounds__(256) void query_prep_kernel(const float* __restrict__ q_rot, int64_t nq, int D,
-                                                        rabitq_query_repr o) {
+                                                        rabitq_query_repr o, int form) {
   const int lane = threadIdx.x & 63;
   const int64_t q = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (q >= nq) return;
-  query_prep_row<F>(q_rot + q * D, q, D, o, lane);
+  query_prep_row<F>(q_rot + q * D, q, D, o, lane, form);
 }
 
-int launch_query_prep(const float* q_rot, int64_t nq, int D, int F, const rabitq_query_repr& out, hipStream_t st) {
+int launch_query_prep(const float* q_rot, int64_t nq, int D, int F, const rabitq_query_repr& out, int form,
+                      hipStream_t st) {
   if (nq <= 0) return RABITQ_OK;
   const unsigned grid = (unsigned)((nq + 3) / 4);
   switch (F) {
-    case 0: hipLaunchKernelGGL(query_prep_kernel<0>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out); break;
-    case 2: hipLaunchKernelGGL(query_prep_kernel<2>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out); break;
-    case 4: hipLaunchKernelGGL(query_prep_kernel<4>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out); break;
-    default: hipLaunchKernelGGL(query_prep_kernel<8>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out); break;
+    case 0: hipLaunchKernelGGL(query_prep_kernel<0>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form); break;
+    case 2: hipLaunchKernelGGL(query_prep_kernel<2>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form); break;
+    case 4: hipLaunchKernelGGL(query_prep_kernel<4>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form); break;
+    default: hipLaunchKernelGGL(query_prep_kernel<8>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form); break;
   }
   RQ_HIP(hipGetLastError());
   return RABITQ_OK;
@@ -330,31 +331,9 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__
   // of several at the last place only as many stay as there is room for, and another copy of them is no better, so
   // the limit excludes it.
   auto keep_best = [&](const uint64_t (&key)[RB]) {
-    uint32_t ord[RB], n_le;
-#pragma unroll
-    for (int r = 0; r < RB; ++r) ord[r] = (uint32_t)(key[r] >> 32);
     wave_sync();
-    const uint32_t bound = wave_kth_ord<RB>(ord, (uint32_t)k, &n_le);
-    uint64_t last = ((uint64_t)bound << 32) | 0xffffffffu;  // the k-th smallest key, or a value between it and the next
-    // (equal distances at the last place: the lower ids)
-    if (n_le != (uint32_t)k) last = wave_kth_bound<RB>(key, k);
-    int at = 0;
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      const uint64_t m = __ballot(key[r] < last);
-      if (key[r] < last) buf[at + __popcll(m & lower)] = key[r];
-      at += __popcll(m);
-    }
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      const uint64_t m = __ballot(key[r] == last);
-      const int place = at + __popcll(m & lower);
-      if (key[r] == last && place < k) buf[place] = key[r];
-      at += __popcll(m);
-    }
-    const uint64_t next = at > k ? last : last + 1ull;
+    const uint64_t next = wave_keep_best<RB>(key, k, lane, &cnt, [&](int at, uint64_t v) { buf[at] = v; }) + 1ull;
     limit = next < limit ? next : limit;
-    cnt = min(at, k);
     wave_sync();
   };
   auto cut = [&]() {
