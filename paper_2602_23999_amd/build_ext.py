@@ -13,7 +13,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "librabitq_hip.so")
 PROBE = os.path.join(HERE, "stream_probe")
 # (source, extra defines, object name)
-UNITS = [("api.hip", [], "api.o"), ("gemm.hip", [], "gemm.o"), ("coarse.hip", [], "coarse.o"), ("stages.hip", [], "stages.o"),
+UNITS = [("api.hip", [], "api.o"), ("gemm.hip", [], "gemm.o"), ("stages.hip", [], "stages.o"),
          ("scan_dispatch.hip", [], "scan_dispatch.o"), ("build.hip", [], "build.o"),
          ("scan.hip", ["-DRQ_PART=0"], "scan0.o"), ("scan.hip", ["-DRQ_PART=1"], "scan1.o"),
          ("scan.hip", ["-DRQ_PART=2"], "scan2.o"),

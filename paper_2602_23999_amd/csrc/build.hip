@@ -447,7 +447,7 @@ static int assign_rows(const float* x, int64_t rows, int D, int nlist, const flo
                        int64_t chunk, int32_t* out, hipStream_t st) {
   for (int64_t s = 0; s < rows; s += chunk) {
     const int64_t m = std::min(chunk, rows - s);
-    int rc = launch_gemm(x + s * D, ct, scores, m, nlist, D, 3, csq, st);
+    int rc = launch_gemm(x + s * D, ct, scores, m, nlist, D, 3, nullptr, csq, st);
     if (rc) return rc;
     hipLaunchKernelGGL(argmin_rows_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, scores, m, nlist, out + s);
   }
@@ -488,8 +488,7 @@ int build_index_device(rabitq_index* ix, const float* data, const float* rotatio
   hipLaunchKernelGGL(gather_rows_kernel, dim3(grid_for(nt * D)), dim3(256), 0, st, xr.p, N, nt, D, tr.p);
   hipLaunchKernelGGL(gather_rows_kernel, dim3(grid_for((int64_t)nlist * D)), dim3(256), 0, st, tr.p, nt, (int64_t)nlist,
                      D, c_rows.p);
-  RQ_HIP(hipMalloc(reinterpret_cast<void**>(&ix->centroids_t), (size_t)(centroid_bytes(nlist, D) + 16 * centroid_pieces_words(nlist, D))));
-  ix->centroid_pieces = reinterpret_cast<uint4*>(reinterpret_cast<char*>(ix->centroids_t) + centroid_bytes(nlist, D));
+  RQ_HIP(hipMalloc(reinterpret_cast<void**>(&ix->centroids_t), (size_t)D * nlist * sizeof(float)));
   RQ_HIP(hipMalloc(reinterpret_cast<void**>(&ix->centroid_sq), (size_t)nlist * sizeof(float)));
   const int64_t chunk = std::max<int64_t>(1024, (int64_t)(64 << 20) / nlist);
   RQ_TRY(scores.alloc(std::min<int64_t>(chunk, std::max(N, nt)) * nlist));
@@ -507,7 +506,6 @@ int build_index_device(rabitq_index* ix, const float* data, const float* rotatio
   }
   hipLaunchKernelGGL(transpose_centroids_kernel, dim3((nlist + 255) / 256), dim3(256), 0, st, c_rows.p, nlist, D,
                      ix->centroids_t, ix->centroid_sq);
-  RQ_TRY(launch_centroid_pieces(ix->centroids_t, ix->centroid_sq, nlist, D, ix->centroid_pieces, st));
   RQ_TRY(assign_rows(xr.p, N, D, nlist, ix->centroids_t, ix->centroid_sq, scores.p, chunk, asg.p, st));
   RQ_TRY(launch_group_rows(asg.p, N, nlist, off.p, members.p, hist.p, total.p, st));
   // layout: cluster sizes, tile offsets (the total is needed on the host to size the arrays)

@@ -1,11 +1,13 @@
-// fp32 MFMA GEMM for the query rotation Q' = Q P (Section 3.3.1) and the assignment scores of the index build, and the
-// first kernel of a small batch, which also computes the coarse scores.
+// fp32 MFMA GEMM for the two dense contractions of the search path:
+//   query rotation  Q' = Q P            (Section 3.3.1)
+//   coarse scores   s_q 1^T + 1 s_c^T - 2 Q' C^T   (Section 3.3.2)
 // fp32 inputs are kept (v_mfma_f32_32x32x2_f32): the rotated query feeds an integer
 // quantisation and the estimator, so reduced-precision inputs are not an option.
 #include "rq_device.h"
-#include "rq_split.h"
 
 namespace rq {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 16;
 
@@ -18,7 +20,7 @@ constexpr int BK = 16;
 template <int MODE, int TM, int TN>
 __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                    float* __restrict__ C, int64_t M, int N, int K,
-                                                   const float* __restrict__ colv) {
+                                                   const float* __restrict__ rowv, const float* __restrict__ colv) {
   constexpr int BM = 64 * TM, BN = 64 * TN;
   constexpr int AF = 4 * TM, BF = 4 * TN;  // floats of the A / B tile each thread moves per k-step
   __shared__ float As[2][BK][BM];  // k-major so that the 32 lanes of an MFMA operand read consecutive words
@@ -98,14 +100,19 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, 
     for (int r = 0; r < 16; ++r) {
       const int64_t m = m0 + wm * 32 * TM + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
       if (m >= M) continue;
+      float rv = 0.f;
+      if (MODE == 1) rv = rowv[m];
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int n = n0 + wn * 32 * TN + 32 * j + (lane & 31);
         if (n >= N) continue;
         float v = acc[i][j][r];
+        if (MODE == 1) v = rv + colv[n] - 2.0f * v;
+        if (MODE == 2) v = -v;
         if (MODE == 3) v = colv[n] - 2.0f * v;
         if (MODE == 4) v = v - colv[n];
-        C[m * (int64_t)N + n] = v;
+        if (MODE == 1 || MODE == 2) __builtin_nontemporal_store(v, &C[m * (int64_t)N + n]);  // coarse scores: read once, by the selection
+        else C[m * (int64_t)N + n] = v;
       }
     }
   }
@@ -116,13 +123,14 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, 
 // in ONE launch.  A workgroup takes 32 queries and 128 lists.  Every workgroup first rotates its 32 queries itself
 // (each wavefront a 32 x 32 block of Q' at a time, operands straight from memory) and keeps Q' in LDS; the
 // workgroups of the first list group also store Q', and the list groups share the queries' representation.  Then each wavefront
-// contracts Q' with 32 centroids.  Both contractions issue the matrix instructions of gemm_kernel and coarse_kernel in their
-// order and finish with the same expressions, so every number is the one the three separate kernels produce, bit for bit.
+// contracts Q' with 32 centroids.  Both contractions issue v_mfma_f32_32x32x2_f32 over k = 0, 2, 4, ... exactly as
+// gemm_kernel does and finish with the same expressions, so every number is the one the three separate kernels
+// produce, bit for bit.
 // ---------------------------------------------------------------------------------
 template <int F>
 __global__ __launch_bounds__(256) void small_front_kernel(const float* __restrict__ queries, int nq, int D, int nlist,
                                                           const float* __restrict__ P, const float* __restrict__ mean_rot,
-                                                          const uint4* __restrict__ pieces, const float* __restrict__ csq,
+                                                          const float* __restrict__ ct, const float* __restrict__ csq,
                                                           int metric, float* __restrict__ q_rot, rabitq_query_repr o,
                                                           int form, float* __restrict__ scores) {
   extern __shared__ float qs[];  // [32][D + 1] rotated queries, then [32] squared norms
@@ -193,51 +201,48 @@ __global__ __launch_bounds__(256) void small_front_kernel(const float* __restric
   {
     const int c0 = 128 * blockIdx.x + 32 * wave;
     if (c0 >= nlist) return;
-    // (the lane's register r holds list 8 (r / 4) + 4 half + r % 4 of the tile against query l32; four steps of 16 dimensions in
-    // flight, D / 16 is even)
-    SplitSum acc;
-    acc.lo = acc.hi = floatx16{0};
-    const int steps = D / 16;
-    const uint4* from = pieces + (int64_t)(c0 / 32) * steps * 3 * 64 + lane;
-    const float* q_ptr = qs + l32 * ld + 8 * half;
-    constexpr int SU = 2;
-    auto load = [&](uint4 (&c)[SU][3], int s0) {
+    floatx16 acc = {0};
+    const int col = c0 + l32;
+    const bool col_ok = col < nlist;
+    const float* b_ptr = ct + (int64_t)half * nlist + min(col, nlist - 1);
+    const float* a_ptr = qs + l32 * ld + half;
+    constexpr int KU = 16;
+    auto load = [&](float (&b_)[KU], int k0) {
 #pragma unroll
-      for (int u = 0; u < SU; ++u)
-#pragma unroll
-        for (int p = 0; p < 3; ++p) c[u][p] = from[((s0 + u) * 3 + p) * 64];
+      for (int u = 0; u < KU; ++u) b_[u] = b_ptr[(int64_t)(k0 + 2 * u) * nlist];
     };
-    auto mma = [&](const uint4 (&c)[SU][3], int s0) {
+    auto mma = [&](float (&b_)[KU], int k0) {
 #pragma unroll
-      for (int u = 0; u < SU; ++u) {
-        float x[8];
+      for (int u = 0; u < KU; ++u) b_[u] = pinned(b_[u]);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = q_ptr[(s0 + u) * 16 + i];
-        bf16x8 cp[3];
-#pragma unroll
-        for (int p = 0; p < 3; ++p) cp[p] = __builtin_bit_cast(bf16x8, c[u][p]);
-        split_mma(cp, split8(x), acc);
-      }
+      for (int u = 0; u < KU; ++u)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a_ptr[k0 + 2 * u], col_ok ? b_[u] : 0.f, acc, 0, 0, 0);
     };
-    uint4 ca[SU][3], cb[SU][3];
-    load(ca, 0);
-    for (int s0 = 0; s0 < steps; s0 += 2 * SU) {
-      if (s0 + SU < steps) load(cb, s0 + SU);
-      mma(ca, s0);
-      if (s0 + SU >= steps) break;
-      if (s0 + 2 * SU < steps) load(ca, s0 + 2 * SU);
-      mma(cb, s0 + SU);
+    float b0[KU], b1[KU];
+    load(b0, 0);
+    for (int k0 = 0;;) {
+      if (k0 + 32 < D) load(b1, k0 + 32);
+      mma(b0, k0);
+      k0 += 32;
+      if (k0 >= D) break;
+      if (k0 + 32 < D) load(b0, k0 + 32);
+      mma(b1, k0);
+      k0 += 32;
+      if (k0 >= D) break;
     }
-    if (m0 + l32 >= nq) return;
-    const float rv = s_sq[l32];
+    const float cv = col_ok ? csq[col] : 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int col = c0 + 8 * (r >> 2) + 4 * half + (r & 3);
-      if (col >= nlist) continue;
-      float v = acc.hi[r] + acc.lo[r];
-      if (metric == RABITQ_L2) v = rv + csq[col] - 2.0f * v;
-      else v = -v;
-      scores[(int64_t)(m0 + l32) * nlist + col] = v;
+      const int row = 8 * (r >> 2) + 4 * half + (r & 3);
+      if (m0 + row >= nq || !col_ok) continue;
+      float v = acc[r];
+      if (metric == RABITQ_L2) {
+        const float rv = s_sq[row];
+        v = rv + cv - 2.0f * v;
+      } else {
+        v = -v;
+      }
+      scores[(int64_t)(m0 + row) * nlist + col] = v;
     }
   }
 }
@@ -253,7 +258,7 @@ int launch_small_front(const rabitq_index* ix, const float* queries, int64_t nq,
     if (smem > 64 * 1024) RQ_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(small_front_kernel<F_>),             \
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));            \
     hipLaunchKernelGGL(small_front_kernel<F_>, grid, dim3(256), smem, st, queries, (int)nq, D, ix->nlist, ix->rotation,  \
-                       ix->mean_rot, ix->centroid_pieces, ix->centroid_sq, ix->metric, q_rot, o, form, scores);                    \
+                       ix->mean_rot, ix->centroids_t, ix->centroid_sq, ix->metric, q_rot, o, form, scores);                    \
   }
   switch (ix->F) {
     case 0: RQ_SF(0) break;
@@ -267,8 +272,8 @@ int launch_small_front(const rabitq_index* ix, const float* queries, int64_t nq,
 }
 
 template <int TM, int TN>
-static int launch_gemm_tile(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* colv,
-                            hipStream_t st) {
+static int launch_gemm_tile(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* rowv,
+                            const float* colv, hipStream_t st) {
   constexpr int BM = 64 * TM, BN = 64 * TN;
   if ((M + BM - 1) / BM > 0x7fffffff || (N + BN - 1) / BN > 65535) {
     set_error("gemm: matrix too large");
@@ -276,16 +281,19 @@ static int launch_gemm_tile(const float* A, const float* B, float* C, int64_t M,
   }
   dim3 grid((unsigned)((M + BM - 1) / BM), (unsigned)((N + BN - 1) / BN));
   switch (mode) {
-    case 0: hipLaunchKernelGGL((gemm_kernel<0, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, colv); break;
-    case 3: hipLaunchKernelGGL((gemm_kernel<3, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, colv); break;
-    case 4: hipLaunchKernelGGL((gemm_kernel<4, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, colv); break;
+    case 0: hipLaunchKernelGGL((gemm_kernel<0, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv); break;
+    case 1: hipLaunchKernelGGL((gemm_kernel<1, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv); break;
+    case 2: hipLaunchKernelGGL((gemm_kernel<2, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv); break;
+    case 3: hipLaunchKernelGGL((gemm_kernel<3, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv); break;
+    case 4: hipLaunchKernelGGL((gemm_kernel<4, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv); break;
     default: set_error("gemm: bad mode"); return RABITQ_EINVAL;
   }
   RQ_HIP(hipGetLastError());
   return RABITQ_OK;
 }
 
-int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* colv, hipStream_t st) {
+int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* rowv,
+                const float* colv, hipStream_t st) {
   if (M <= 0) return RABITQ_OK;
   if (K % BK != 0 || N <= 0) {
     set_error("gemm: K must be a multiple of 16 and N positive");
@@ -296,10 +304,10 @@ int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int 
   // its prologue, epilogue and the write of C, where more and smaller workgroups do better; and a small problem
   // needs small tiles to give every compute unit a workgroup at all.
   auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * (int64_t)((N + bn - 1) / bn); };
-  if (K >= 256 && tiles(128, 128) >= 384) return launch_gemm_tile<2, 2>(A, B, C, M, N, K, mode, colv, st);
+  if (K >= 256 && tiles(128, 128) >= 384) return launch_gemm_tile<2, 2>(A, B, C, M, N, K, mode, rowv, colv, st);
   // (64 x 128 rather than 128 x 64: a wavefront then stores 256 contiguous bytes of a row of C)
-  if (tiles(64, 128) >= 512) return launch_gemm_tile<1, 2>(A, B, C, M, N, K, mode, colv, st);
-  return launch_gemm_tile<1, 1>(A, B, C, M, N, K, mode, colv, st);
+  if (tiles(64, 128) >= 512) return launch_gemm_tile<1, 2>(A, B, C, M, N, K, mode, rowv, colv, st);
+  return launch_gemm_tile<1, 1>(A, B, C, M, N, K, mode, rowv, colv, st);
 }
 
 }  // namespace rq

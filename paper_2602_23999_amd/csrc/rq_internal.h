@@ -51,8 +51,7 @@ struct rabitq_index {
   float* rotation = nullptr;        // [D][D]
   float* mean_rot = nullptr;        // [D] mean * P of a centred index (nullptr: not centred)
   std::vector<float> host_mean;     // [D] the mean itself (empty: not centred)
-  float* centroids_t = nullptr;     // [D][nlist]  (transposed c'), and behind it, in the same allocation:
-  uint4* centroid_pieces = nullptr; // the centroids in three bf16 pieces (coarse.hip)
+  float* centroids_t = nullptr;     // [D][nlist]  (transposed c')
   float* centroid_sq = nullptr;     // [nlist]
   int32_t* tile_off = nullptr;      // [nlist+1] tile offsets | [nlist+1] scan work-item offsets | [TICKET_WORDS] zeroed ticket
                                     // | [nlist+1] work items of 16 pairs | [nlist+1] first survivor block (split search)
@@ -133,29 +132,22 @@ __host__ __device__ inline float ord2f(uint32_t o) {
 }
 
 // ---- launchers (each returns a rabitq_status) ----
-// C[M,N] = A[M,K] * B[K,N], row-major fp32.  mode 0: plain.  mode 3 (assignment): C = colv[n] - 2*acc.
+// C[M,N] = A[M,K] * B[K,N], row-major fp32.  mode 0: plain.  mode 1 (L2 coarse):
+// C = rowv[m] + colv[n] - 2*acc.  mode 2 (IP coarse): C = -acc.  mode 3 (assignment): C = colv[n] - 2*acc.
 // mode 4 (rotation of a centred index): C = acc - colv[n].
-int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* colv, hipStream_t st);
+int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* rowv,
+                const float* colv, hipStream_t st);
 // small batches: Q' = (Q - mean) P, the queries' representation and the coarse scores [nq][nlist] from one launch,
-// bit-identical to launch_rotate + launch_query_prep + launch_coarse
+// bit-identical to launch_rotate + launch_query_prep + launch_gemm (mode 1 / 2)
 int launch_small_front(const rabitq_index* ix, const float* queries, int64_t nq, float* q_rot, const rabitq_query_repr& o,
                        int form, float* scores, hipStream_t st);
 // form: what the members hold (query_form).  The stage entry points hand out and take what the header says (0); a search hands
 // its scans what they would otherwise make of it themselves, in the same space: the refinement's digits of q' in
 // q_stage, the group scan's operand in qhat8 (rq_device.h).  Same numbers either way.
 enum QueryForm { QUERY_DIGITS = 1, QUERY_FP8 = 2 };
-// coarse scores [nq][nlist] and, unless tmin is null, the smallest of every 32 lists, tmin [nq][ceil(nlist / 32)]
-int launch_coarse(const rabitq_index* ix, const float* q_rot, const float* sq_norm, int64_t nq, float* scores, float* tmin,
-                  hipStream_t st);
-int64_t centroid_pieces_words(int nlist, int D);
-int launch_centroid_pieces(const float* ct, const float* csq, int nlist, int D, uint4* pieces, hipStream_t st);
-// bytes of the allocation of centroids_t, and where in it the pieces are
-inline int64_t centroid_bytes(int nlist, int D) { return ((int64_t)D * nlist * 4 + 255) / 256 * 256; }
 int launch_query_prep(const float* q_rot, int64_t nq, int D, int F, const rabitq_query_repr& out, int form, hipStream_t st);
-// tmin: the smallest score of every 32 lists (launch_coarse), or null
-int launch_select_probes(const float* scores, const float* tmin, const float* sq_norm, const float* centroid_sq, int64_t nq, int nlist,
+int launch_select_probes(const float* scores, const float* sq_norm, const float* centroid_sq, int64_t nq, int nlist,
                          int nprobe, int metric, int32_t* probe_ids, float* probe_G, float* probe_E, hipStream_t st);
-bool select_by_minima(int nlist, int nprobe);    // is tmin worth having
 int probe_select_variant(int nlist, int nprobe);  // which selection kernel launch_select_probes takes (see stages.hip)
 int64_t probe_list_scratch_words(int32_t nlist, int64_t nq);
 int launch_clear_list_bitmap(int64_t nq, int nlist, uint32_t* scratch, hipStream_t st);
