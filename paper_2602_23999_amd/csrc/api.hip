@@ -239,7 +239,7 @@ int set_index_mean(rabitq_index* ix, const float* mean, const float* rotation_ho
 }
 
 int launch_rotate(const rabitq_index* ix, const float* q, float* q_rot, int64_t nq, hipStream_t st) {
-  return launch_gemm(q, ix->rotation, q_rot, nq, ix->dim, ix->dim, ix->mean_rot ? 4 : 0, nullptr, ix->mean_rot, st);
+  return launch_gemm(q, ix->rotation, q_rot, nq, ix->dim, ix->dim, ix->mean_rot ? 4 : 0, nullptr, ix->mean_rot, nullptr, st);
 }
 
 }  // namespace rq
@@ -535,9 +535,9 @@ int rabitq_coarse_probe(rabitq_index_t ix, const float* q_rot, const float* sq_n
   if (!q_rot || !sq_norm || !scores || !probe_ids || !probe_G || !probe_E) { set_error("coarse_probe: null pointer"); return RABITQ_EINVAL; }
   hipStream_t st = (hipStream_t)stream;
   rc = launch_gemm(q_rot, ix->centroids_t, scores, nq, ix->nlist, ix->dim, ix->metric == RABITQ_L2 ? 1 : 2, sq_norm,
-                   ix->centroid_sq, st);
+                   ix->centroid_sq, nullptr, st);
   if (rc) return rc;
-  return launch_select_probes(scores, sq_norm, ix->centroid_sq, nq, ix->nlist, nprobe, ix->metric, probe_ids, probe_G,
+  return launch_select_probes(scores, nullptr, sq_norm, ix->centroid_sq, nq, ix->nlist, nprobe, ix->metric, probe_ids, probe_G,
                               probe_E, st);
 }
 
@@ -653,13 +653,20 @@ static int search_batch_body(rabitq_index* ix, Workspace& w, const float* querie
   if (ix->scan_impl != 2) repr.lut = nullptr;  // tables are only built for the scan that reads them
   // a small batch is bound by the number of dependent launches (Section 4.2.2): it takes fused kernels
   const bool small = ix->small_batch && nq <= SMALL_BATCH_MAX;
+  // the smallest score of every 32 lists, where the probe selection gains by it, in the memory of the candidate keys, which the
+  // scan is the first to write (nprobe regions of at least 128 keys per query)
+  int cap = 1;
+  while (cap < k + TILE) cap <<= 1;
+  const int n_t = (ix->nlist + 31) / 32;
+  const bool by_minima = !small && select_by_minima(ix->nlist, nprobe) && n_t <= 2 * (int64_t)nprobe * cap;
+  float* tmin = by_minima ? reinterpret_cast<float*>(w.cand_keys) : nullptr;
   if (small) {
     RQ_STAGE(0, st, launch_small_front(ix, queries, nq, w.q_rot, repr, form, w.scores, st));
   } else {
     RQ_STAGE(0, st, launch_rotate(ix, queries, w.q_rot, nq, st));
     RQ_STAGE(1, st, launch_query_prep(w.q_rot, nq, ix->dim, ix->F, repr, form, st));
     RQ_STAGE(2, st, launch_gemm(w.q_rot, ix->centroids_t, w.scores, nq, ix->nlist, ix->dim,
-                                ix->metric == RABITQ_L2 ? 1 : 2, w.repr.sq_norm, ix->centroid_sq, st));
+                                ix->metric == RABITQ_L2 ? 1 : 2, w.repr.sq_norm, ix->centroid_sq, tmin, st));
   }
   // ... and, when the per-query selections fit one wavefront, everything up to the scan from a second one
   const bool small_fused = small && nprobe <= 64 && k <= 64 && effective_impl(ix) != 2;
@@ -667,7 +674,7 @@ static int search_batch_body(rabitq_index* ix, Workspace& w, const float* querie
     RQ_STAGE(3, st, launch_small_select_seed(ix, w.repr, w.scores, nq, k, nprobe, w.probe_ids, w.probe_G, w.probe_E, w.tau,
                                              w.pair_off, w.pair_ids, w.list_scratch, w.cand_cnt, st));
   } else {
-    RQ_STAGE(3, st, launch_select_probes(w.scores, w.repr.sq_norm, ix->centroid_sq, nq, ix->nlist, nprobe, ix->metric,
+    RQ_STAGE(3, st, launch_select_probes(w.scores, tmin, w.repr.sq_norm, ix->centroid_sq, nq, ix->nlist, nprobe, ix->metric,
                                          w.probe_ids, w.probe_G, w.probe_E, st));
   }
   // The pair lists and the scan's work-item table depend on the probes only, and so does the threshold seeding:

@@ -447,7 +447,7 @@ static int assign_rows(const float* x, int64_t rows, int D, int nlist, const flo
                        int64_t chunk, int32_t* out, hipStream_t st) {
   for (int64_t s = 0; s < rows; s += chunk) {
     const int64_t m = std::min(chunk, rows - s);
-    int rc = launch_gemm(x + s * D, ct, scores, m, nlist, D, 3, nullptr, csq, st);
+    int rc = launch_gemm(x + s * D, ct, scores, m, nlist, D, 3, nullptr, csq, nullptr, st);
     if (rc) return rc;
     hipLaunchKernelGGL(argmin_rows_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, scores, m, nlist, out + s);
   }

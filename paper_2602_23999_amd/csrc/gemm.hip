@@ -11,6 +11,38 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 16;
 
+template <int CTRL>
+__device__ inline float dpp_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
+// The smallest value of each accumulator row: 16 registers over the 32 lanes of a half wavefront.  Every step but the last halves the
+// registers: of two rows a lane keeps the one that its bit of the lane number names, so 16 + 8 + 4 + 2 + 1 steps stand for 5 x 16.
+// The lanes of a half with bit 2 clear hold the sixteen rows, each its own *row.  (Lanes in a row of 16 without a source get 0, but
+// those are lanes with bit 2 set.)
+__device__ __forceinline__ float least_of_rows(floatx16 v, int lane, int* row) {
+  float a[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {  // bit 4
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[r]), __float_as_uint(v[r + 8]), false, false);
+    a[r] = fminf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {  // bit 0: quad_perm [1,0,3,2]
+    const float keep = (lane & 1) ? a[r + 4] : a[r], give = (lane & 1) ? a[r] : a[r + 4];
+    a[r] = fminf(keep, dpp_move<0xB1>(give));
+  }
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {  // bit 1: quad_perm [2,3,0,1]
+    const float keep = (lane & 2) ? a[r + 2] : a[r], give = (lane & 2) ? a[r] : a[r + 2];
+    a[r] = fminf(keep, dpp_move<0x4E>(give));
+  }
+  const float keep = (lane & 8) ? a[1] : a[0], give = (lane & 8) ? a[0] : a[1];  // bit 3: row_ror:8
+  const float t = fminf(keep, dpp_move<0x128>(give));
+  *row = ((lane >> 4) & 1) * 8 + (lane & 1) * 4 + ((lane >> 1) & 1) * 2 + ((lane >> 3) & 1);
+  return fminf(t, dpp_move<0x104>(t));  // bit 2: row_shl:4
+}
+
 // Block: 256 threads = 4 wavefronts in a 2 x 2 arrangement; a wavefront owns 32 TM rows x 32 TN columns of the block
 // tile (64 TM x 64 TN) as TM x TN 32x32 MFMA accumulators, so with TM = TN = 2 every operand word read from LDS feeds
 // two matrix instructions.  The LDS tiles are double buffered: the next k-step's operands travel from memory to
@@ -20,7 +52,8 @@ constexpr int BK = 16;
 template <int MODE, int TM, int TN>
 __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                    float* __restrict__ C, int64_t M, int N, int K,
-                                                   const float* __restrict__ rowv, const float* __restrict__ colv) {
+                                                   const float* __restrict__ rowv, const float* __restrict__ colv,
+                                                   float* __restrict__ tmin) {
   constexpr int BM = 64 * TM, BN = 64 * TN;
   constexpr int AF = 4 * TM, BF = 4 * TN;  // floats of the A / B tile each thread moves per k-step
   __shared__ float As[2][BK][BM];  // k-major so that the 32 lanes of an MFMA operand read consecutive words
@@ -99,20 +132,32 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, 
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int64_t m = m0 + wm * 32 * TM + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      if (m >= M) continue;
+      const bool m_ok = m < M;
       float rv = 0.f;
-      if (MODE == 1) rv = rowv[m];
+      if (MODE == 1) rv = rowv[m_ok ? m : M - 1];
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int n = n0 + wn * 32 * TN + 32 * j + (lane & 31);
-        if (n >= N) continue;
         float v = acc[i][j][r];
-        if (MODE == 1) v = rv + colv[n] - 2.0f * v;
+        if (MODE == 1) v = rv + colv[min(n, N - 1)] - 2.0f * v;
         if (MODE == 2) v = -v;
-        if (MODE == 3) v = colv[n] - 2.0f * v;
-        if (MODE == 4) v = v - colv[n];
-        if (MODE == 1 || MODE == 2) __builtin_nontemporal_store(v, &C[m * (int64_t)N + n]);  // coarse scores: read once, by the selection
-        else C[m * (int64_t)N + n] = v;
+        if (MODE == 3) v = colv[min(n, N - 1)] - 2.0f * v;
+        if (MODE == 4) v = v - colv[min(n, N - 1)];
+        if (m_ok && n < N) {
+          if (MODE == 1 || MODE == 2) __builtin_nontemporal_store(v, &C[m * (int64_t)N + n]);  // coarse scores: read once, by the selection
+          else C[m * (int64_t)N + n] = v;
+        }
+        if (MODE == 1 || MODE == 2) acc[i][j][r] = n < N ? v : INFINITY;
+      }
+    }
+    if ((MODE == 1 || MODE == 2) && tmin != nullptr) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        int r;
+        const float least = least_of_rows(acc[i][j], lane, &r);
+        const int64_t m = m0 + wm * 32 * TM + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const int t = (n0 + wn * 32 * TN + 32 * j) / 32;
+        if ((lane & 4) == 0 && m < M && 32 * t < N) tmin[m * ((N + 31) / 32) + t] = least;
       }
     }
   }
@@ -273,7 +318,7 @@ int launch_small_front(const rabitq_index* ix, const float* queries, int64_t nq,
 
 template <int TM, int TN>
 static int launch_gemm_tile(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* rowv,
-                            const float* colv, hipStream_t st) {
+                            const float* colv, float* tmin, hipStream_t st) {
   constexpr int BM = 64 * TM, BN = 64 * TN;
   if ((M + BM - 1) / BM > 0x7fffffff || (N + BN - 1) / BN > 65535) {
     set_error("gemm: matrix too large");
@@ -281,11 +326,11 @@ static int launch_gemm_tile(const float* A, const float* B, float* C, int64_t M,
   }
   dim3 grid((unsigned)((M + BM - 1) / BM), (unsigned)((N + BN - 1) / BN));
   switch (mode) {
-    case 0: hipLaunchKernelGGL((gemm_kernel<0, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv); break;
-    case 1: hipLaunchKernelGGL((gemm_kernel<1, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv); break;
-    case 2: hipLaunchKernelGGL((gemm_kernel<2, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv); break;
-    case 3: hipLaunchKernelGGL((gemm_kernel<3, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv); break;
-    case 4: hipLaunchKernelGGL((gemm_kernel<4, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv); break;
+    case 0: hipLaunchKernelGGL((gemm_kernel<0, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv, tmin); break;
+    case 1: hipLaunchKernelGGL((gemm_kernel<1, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv, tmin); break;
+    case 2: hipLaunchKernelGGL((gemm_kernel<2, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv, tmin); break;
+    case 3: hipLaunchKernelGGL((gemm_kernel<3, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv, tmin); break;
+    case 4: hipLaunchKernelGGL((gemm_kernel<4, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv, tmin); break;
     default: set_error("gemm: bad mode"); return RABITQ_EINVAL;
   }
   RQ_HIP(hipGetLastError());
@@ -293,7 +338,7 @@ static int launch_gemm_tile(const float* A, const float* B, float* C, int64_t M,
 }
 
 int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* rowv,
-                const float* colv, hipStream_t st) {
+                const float* colv, float* tmin, hipStream_t st) {
   if (M <= 0) return RABITQ_OK;
   if (K % BK != 0 || N <= 0) {
     set_error("gemm: K must be a multiple of 16 and N positive");
@@ -304,10 +349,10 @@ int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int 
   // its prologue, epilogue and the write of C, where more and smaller workgroups do better; and a small problem
   // needs small tiles to give every compute unit a workgroup at all.
   auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * (int64_t)((N + bn - 1) / bn); };
-  if (K >= 256 && tiles(128, 128) >= 384) return launch_gemm_tile<2, 2>(A, B, C, M, N, K, mode, rowv, colv, st);
+  if (K >= 256 && tiles(128, 128) >= 384) return launch_gemm_tile<2, 2>(A, B, C, M, N, K, mode, rowv, colv, tmin, st);
   // (64 x 128 rather than 128 x 64: a wavefront then stores 256 contiguous bytes of a row of C)
-  if (tiles(64, 128) >= 512) return launch_gemm_tile<1, 2>(A, B, C, M, N, K, mode, rowv, colv, st);
-  return launch_gemm_tile<1, 1>(A, B, C, M, N, K, mode, rowv, colv, st);
+  if (tiles(64, 128) >= 512) return launch_gemm_tile<1, 2>(A, B, C, M, N, K, mode, rowv, colv, tmin, st);
+  return launch_gemm_tile<1, 1>(A, B, C, M, N, K, mode, rowv, colv, tmin, st);
 }
 
 }  // namespace rq

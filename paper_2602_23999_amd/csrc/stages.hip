@@ -130,6 +130,83 @@ __global__ __launch_bounds__(256) void select_probes_stream_kernel(const float* 
   }
 }
 
+// The same from the smallest score of every 32 lists: the nprobe best scores lie in the nprobe tiles of 32 with the smallest
+// minima, so only those tiles are read.  Tiles and scores are selected by bisection of values in registers (wave_kth_ord): RT words
+// per lane for the minima, RS for the scores of at most 2 RS tiles.  What bounds it is the read of the minima and of nprobe
+// scattered 128-byte tiles.  (10^4 queries, 8192 lists, 32 probes: 87 us for the whole rows, 30.5 for this, and 71 when the
+// second selection inserted one score after another into a sorted list; 6000 queries, 4096 lists, 8 probes: 42 -> 9.5.  The
+// minima cost the GEMM that writes them nothing that shows: 212 us and 169 against 212 and 175.)
+template <int RT, int RS>
+__global__ __launch_bounds__(256) void select_probes_tiles_kernel(const float* __restrict__ scores, const float* __restrict__ tmin,
+                                                                 const float* __restrict__ sq_norm,
+                                                                 const float* __restrict__ centroid_sq, int64_t nq,
+                                                                 int nlist, int nprobe, int metric,
+                                                                 int32_t* __restrict__ probe_ids,
+                                                                 float* __restrict__ probe_G,
+                                                                 float* __restrict__ probe_E) {
+  __shared__ uint64_t s_sel[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t q = (int64_t)blockIdx.x * 4 + wave;
+  if (q >= nq) return;
+  uint64_t* sel = s_sel[wave];
+  const float* row = scores + q * nlist;
+  const int n_t = (nlist + 31) / 32;  // more than nprobe
+  uint32_t n_le;
+  {
+    float v[RT];
+    uint32_t ord[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) v[r] = tmin[q * n_t + min(r * 64 + lane, n_t - 1)];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) v[r] = pinned(v[r]);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) ord[r] = r * 64 + lane < n_t ? min(f2ord(v[r]), 0xfffffffeu) : 0xffffffffu;
+    const uint32_t bound = wave_kth_ord<RT>(ord, (uint32_t)nprobe, &n_le);
+    wave_put_smallest<RT>(ord, bound, n_le, (uint32_t)nprobe, lane, [&](int at, int r) { sel[at] = (uint64_t)(r * 64 + lane); });
+  }
+  wave_sync();
+  int at[RS];
+  float sc[RS];
+  uint32_t ord[RS];
+#pragma unroll
+  for (int u = 0; u < RS; ++u) {
+    const int t = 2 * u + (lane >> 5);
+    at[u] = 32 * (int)sel[min(t, nprobe - 1)] + (lane & 31);
+    sc[u] = __builtin_nontemporal_load(row + min(at[u], nlist - 1));
+    if (t >= nprobe) at[u] = nlist;
+  }
+#pragma unroll
+  for (int u = 0; u < RS; ++u) sc[u] = pinned(sc[u]);
+#pragma unroll
+  for (int u = 0; u < RS; ++u) ord[u] = at[u] < nlist ? min(f2ord(sc[u]), 0xfffffffeu) : 0xffffffffu;
+  wave_sync();
+  // (the selected tiles are in ascending order, so equals are taken in the order of their lists)
+  const uint32_t bound = wave_kth_ord<RS>(ord, (uint32_t)nprobe, &n_le);
+  const int got = wave_put_smallest<RS>(ord, bound, n_le, (uint32_t)nprobe, lane, [&](int place, int r) {
+    sel[place] = ((uint64_t)ord[r] << 32) | (uint32_t)at[r];
+  });
+  wave_sync();
+  WaveTopK top;
+  top.init_sorted(lane < got ? sel[lane] : KEY_NONE, lane);
+  if (lane < nprobe) {
+    const uint64_t key = top.v;
+    const int c = (int)(uint32_t)key;
+    const float s = ord2f((uint32_t)(key >> 32));
+    probe_ids[q * nprobe + lane] = c;
+    probe_G[q * nprobe + lane] = s;
+    const float d2 = (metric == RABITQ_L2) ? s : (sq_norm[q] + centroid_sq[c] + 2.0f * s);
+    probe_E[q * nprobe + lane] = sqrtf(fmaxf(d2, 0.f));
+  }
+}
+
+// From how many lists the minima of 32 pay: at least four times as many tiles as are read, so that at most a quarter of the row
+// and of the minima's 1/32 are (1024 lists, 32 probes: 15.5 us for the whole rows, whose tiles would all be read); no more minima
+// than 16 words a lane hold.
+bool select_by_minima(int nlist, int nprobe) {
+  const int n_t = (nlist + 31) / 32;
+  return nprobe <= 64 && n_t >= 4 * nprobe && n_t <= 1024;
+}
+
 // Which selection kernel a given (nlist, nprobe) takes: 0 = one wavefront per query streaming the score row through
 // a register-resident sorted list (nprobe <= 64, any nlist); 1, 2, 3 = one wavefront per query with the whole row
 // in registers, 8 / 16 / 32 scores per lane (nprobe > 64, nlist <= 512 / 1024 / 2048); 4 = one workgroup per
@@ -142,13 +219,22 @@ int probe_select_variant(int nlist, int nprobe) {
   return 4;
 }
 
-int launch_select_probes(const float* scores, const float* sq_norm, const float* centroid_sq, int64_t nq, int nlist,
+int launch_select_probes(const float* scores, const float* tmin, const float* sq_norm, const float* centroid_sq, int64_t nq, int nlist,
                          int nprobe, int metric, int32_t* probe_ids, float* probe_G, float* probe_E, hipStream_t st) {
   if (nq <= 0) return RABITQ_OK;
   const int npad = next_pow2(nprobe);
   const size_t smem = npad * sizeof(uint64_t);
   switch (probe_select_variant(nlist, nprobe)) {
     case 0:
+      if (tmin != nullptr) {
+        const bool many = nlist > 32 * 256;
+        auto kernel = nprobe <= 8    ? (many ? select_probes_tiles_kernel<16, 4> : select_probes_tiles_kernel<4, 4>)
+                      : nprobe <= 32 ? (many ? select_probes_tiles_kernel<16, 16> : select_probes_tiles_kernel<4, 16>)
+                                     : (many ? select_probes_tiles_kernel<16, 32> : select_probes_tiles_kernel<4, 32>);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, scores, tmin, sq_norm, centroid_sq, nq, nlist,
+                           nprobe, metric, probe_ids, probe_G, probe_E);
+        break;
+      }
       hipLaunchKernelGGL(select_probes_stream_kernel, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, scores, sq_norm,
                          centroid_sq, nq, nlist, nprobe, metric, probe_ids, probe_G, probe_E);
       break;
