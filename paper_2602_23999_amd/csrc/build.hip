@@ -31,16 +31,27 @@ __global__ void gather_rows_kernel(const float* __restrict__ src, int64_t n_src,
   }
 }
 
-// ct[d][c] = c_rows[c][d], csq[c] = ||c||^2
-__global__ void transpose_centroids_kernel(const float* __restrict__ c_rows, int nlist, int D, float* __restrict__ ct,
-                                           float* __restrict__ csq) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+// ct[d][c] = c_rows[c][d], csq[c] = ||c||^2 (summed in the order of the dimensions).  A thread's row arrives 32 values at a time
+// (D is a multiple of 32): the chain of dependent loads was all its time.  (512 x 128: 21 us -> 4.3)
+__global__ __launch_bounds__(64) void transpose_centroids_kernel(const float* __restrict__ c_rows, int nlist, int D,
+                                                                 float* __restrict__ ct, float* __restrict__ csq) {
+  const int c = blockIdx.x * 64 + threadIdx.x;
   if (c >= nlist) return;
   float s = 0.f;
-  for (int d = 0; d < D; ++d) {
-    const float v = c_rows[(int64_t)c * D + d];
-    ct[(int64_t)d * nlist + c] = v;
-    s += v * v;
+  for (int d0 = 0; d0 < D; d0 += 32) {
+    float4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(c_rows + (int64_t)c * D + d0 + 4 * u);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        ct[(int64_t)(d0 + 4 * u + i) * nlist + c] = x[i];
+        s += x[i] * x[i];
+      }
+    }
   }
   csq[c] = s;
 }
@@ -71,20 +82,35 @@ __global__ __launch_bounds__(256) void argmin_rows_kernel(const float* __restric
   if (lane == 0) out[r] = (int32_t)(uint32_t)best;
 }
 
-// Lloyd update: one workgroup per cluster sums its members in list order (deterministic);
-// an empty cluster keeps its centroid.
-__global__ __launch_bounds__(256) void centroid_update_kernel(const float* __restrict__ x, const int32_t* __restrict__ off,
+// Lloyd update: one wavefront per cluster and 64 dimensions sums the members in list order (deterministic); an empty cluster keeps
+// its centroid.  The order makes every sum a chain, so the longest list decides: its rows are asked for 32 ahead of the additions.
+// (128-d, 512 lists: 43 us a pass over 50 000 rows with one row in flight -> 6)
+__global__ __launch_bounds__(64) void centroid_update_kernel(const float* __restrict__ x, const int32_t* __restrict__ off,
                                                              const int32_t* __restrict__ members, int D,
                                                              float* __restrict__ c_rows) {
-  const int c = blockIdx.x;
+  constexpr int AHEAD = 32;
+  const int c = blockIdx.x, lane = threadIdx.x;
   const int s = off[c], e = off[c + 1];
   if (e == s) return;
   const float inv = 1.0f / (float)(e - s);
-  for (int d = threadIdx.x; d < D; d += blockDim.x) {
-    float acc = 0.f;
-    for (int i = s; i < e; ++i) acc += x[(int64_t)members[i] * D + d];
-    c_rows[(int64_t)c * D + d] = acc * inv;
+  const int d = blockIdx.y * 64 + lane;
+  const int dl = min(d, D - 1);
+  float acc = 0.f;
+  for (int i0 = s; i0 < e; i0 += 64) {
+    const int32_t mem = members[min(i0 + lane, e - 1)];
+#pragma unroll
+    for (int h = 0; h < 64; h += AHEAD) {
+      if (i0 + h >= e) break;
+      float v[AHEAD];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) v[u] = x[(int64_t)__builtin_amdgcn_readlane(mem, h + u) * D + dl];  // (past the end: the last member)
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u)
+        if (i0 + h + u < e) acc += v[u];
+    }
   }
+  if (d < D) c_rows[(int64_t)c * D + d] = acc * inv;
 }
 
 __global__ void cluster_layout_kernel(const int32_t* __restrict__ off, int nlist, int32_t* __restrict__ csize) {
@@ -304,24 +330,42 @@ struct DevBuf {
 // Column means of a row-major [n][D] matrix in two fixed-order passes (deterministic): every
 // workgroup sums its own block of rows per column in fp64, then one workgroup adds the
 // partial sums in block order.
+// Both are chains of additions: the next 16 rows and 64 partial sums are on their way meanwhile.  (250 000 x 128: 109 + 39 us -> 34 + 14)
 constexpr int MEAN_BLOCKS = 1024;
 __global__ __launch_bounds__(256) void column_partial_kernel(const float* __restrict__ x, int64_t n, int D,
                                                             double* __restrict__ partial) {
+  constexpr int AHEAD = 16;
   const int64_t rows_per = (n + MEAN_BLOCKS - 1) / MEAN_BLOCKS;
   const int64_t r0 = (int64_t)blockIdx.x * rows_per, r1 = r0 + rows_per < n ? r0 + rows_per : n;
-  for (int d = threadIdx.x; d < D; d += 256) {
+  for (int d = threadIdx.x; d < D; d += blockDim.x) {
     double acc = 0.0;
-    for (int64_t r = r0; r < r1; ++r) acc += (double)x[r * D + d];
+    for (int64_t r = r0; r < r1; r += AHEAD) {
+      float v[AHEAD];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) v[u] = x[(r + u < r1 ? r + u : r1 - 1) * D + d];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u)
+        if (r + u < r1) acc += (double)v[u];
+    }
     partial[(int64_t)blockIdx.x * D + d] = acc;
   }
 }
-__global__ __launch_bounds__(256) void column_mean_kernel(const double* __restrict__ partial, int64_t n, int D,
+__global__ __launch_bounds__(64) void column_mean_kernel(const double* __restrict__ partial, int64_t n, int D,
                                                          float* __restrict__ mean) {
-  for (int d = threadIdx.x; d < D; d += 256) {
-    double acc = 0.0;
-    for (int b = 0; b < MEAN_BLOCKS; ++b) acc += partial[(int64_t)b * D + d];
-    mean[d] = (float)(acc / (double)n);
+  constexpr int AHEAD = 64;
+  const int d = blockIdx.x * 64 + threadIdx.x;
+  if (d >= D) return;
+  double acc = 0.0;
+  for (int b = 0; b < MEAN_BLOCKS; b += AHEAD) {
+    double v[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) v[u] = partial[(int64_t)(b + u) * D + d];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) acc += v[u];
   }
+  mean[d] = (float)(acc / (double)n);
 }
 
 static unsigned grid_for(int64_t n, int block = 256, int64_t cap = 65535) {
@@ -331,18 +375,21 @@ static unsigned grid_for(int64_t n, int block = 256, int64_t cap = 65535) {
 // ---- rows grouped by cluster -------------------------------------------------------------------
 // A stable counting sort of row ids by cluster id whose memory grows with rows + blocks * nlist (the
 // search path's builder keeps one bit per (cluster, query), which is right for 10^4 queries and far
-// too much for 10^7 vectors).  The rows are cut into `nb` contiguous blocks; a workgroup counts its
-// block per cluster, the counts are scanned block-major per cluster, and the same workgroup then places
-// its rows tile by tile in row order, so every list holds its rows in ascending order whatever the
-// scheduling.
-constexpr int GROUP_TILE = 256;
+// too much for 10^7 vectors).  The rows are cut into `nb` contiguous blocks; a wavefront counts its
+// block per cluster, the counts are scanned block-major per cluster, and the same wavefront then places
+// its rows 64 by 64 in row order, so every list holds its rows in ascending order whatever the
+// scheduling.  A block is a chain of round trips to its counters, so there are as many blocks as the
+// counters' memory allows: 16 MiB of them, or one block per 4096 rows where that is more.
+constexpr int GROUP_TILE = 64;
 struct GroupPlan {
-  int nb;       // workgroups = row blocks
+  int nb;       // wavefronts = row blocks
   int64_t ch;   // rows per block, a multiple of GROUP_TILE
 };
-static GroupPlan group_plan(int64_t rows) {
+static GroupPlan group_plan(int64_t rows, int nlist) {
   GroupPlan g;
-  const int64_t want = std::max<int64_t>(1, std::min<int64_t>((rows + 4095) / 4096, 1024));
+  const int64_t few = std::min<int64_t>((rows + 4095) / 4096, 1024);
+  const int64_t many = std::min<int64_t>({(rows + 4 * GROUP_TILE - 1) / (4 * GROUP_TILE), ((int64_t)1 << 22) / nlist, 4096});
+  const int64_t want = std::max<int64_t>({1, few, many});
   g.ch = ((rows + want - 1) / want + GROUP_TILE - 1) / GROUP_TILE * GROUP_TILE;
   if (g.ch < GROUP_TILE) g.ch = GROUP_TILE;
   g.nb = (int)std::max<int64_t>(1, (rows + g.ch - 1) / g.ch);
@@ -356,17 +403,41 @@ __global__ __launch_bounds__(GROUP_TILE) void group_count_kernel(const int32_t* 
   for (int64_t i = r0 + threadIdx.x; i < r1; i += GROUP_TILE) atomicAdd(&h[asg[i]], 1);
 }
 
-// per cluster: counts of the row blocks -> exclusive prefix over the blocks (in place) and the list length
-__global__ void group_block_prefix_kernel(int32_t* __restrict__ hist, int nb, int nlist, int32_t* __restrict__ total) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+// per cluster: counts of the row blocks -> exclusive prefix over the blocks (in place) and the list length.  32 clusters a
+// workgroup, the blocks of each in 32 segments, whose sums are exchanged through LDS.
+__global__ __launch_bounds__(1024) void group_block_prefix_kernel(int32_t* __restrict__ hist, int nb, int nlist,
+                                                                  int32_t* __restrict__ total) {
+  constexpr int AHEAD = 8;
+  __shared__ int32_t s_sum[32][32];
+  const int cl = threadIdx.x & 31, seg = threadIdx.x >> 5;
+  const int c = blockIdx.x * 32 + cl;
+  const int per = (nb + 31) / 32, b0 = min(seg * per, nb), b1 = min(b0 + per, nb);
+  int32_t* col = hist + min(c, nlist - 1);
+  int32_t sum = 0;
+  for (int b = b0; b < b1; b += AHEAD) {
+    int32_t v[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) v[u] = col[(int64_t)min(b + u, b1 - 1) * nlist];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) sum += b + u < b1 ? v[u] : 0;
+  }
+  s_sum[seg][cl] = sum;
+  __syncthreads();
   if (c >= nlist) return;
   int32_t run = 0;
-  for (int b = 0; b < nb; ++b) {
-    const int32_t v = hist[(int64_t)b * nlist + c];
-    hist[(int64_t)b * nlist + c] = run;
-    run += v;
+  for (int t = 0; t < seg; ++t) run += s_sum[t][cl];
+  if (seg == 31) total[c] = run + sum;
+  for (int b = b0; b < b1; b += AHEAD) {
+    int32_t v[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) v[u] = col[(int64_t)min(b + u, b1 - 1) * nlist];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      if (b + u < b1) col[(int64_t)(b + u) * nlist] = run;
+      run += v[u];
+    }
   }
-  total[c] = run;
 }
 
 // off[c] = sum of total[0..c), off[nlist] = rows; one workgroup walks the lists in order
@@ -395,49 +466,50 @@ __global__ __launch_bounds__(1024) void group_offsets_kernel(const int32_t* __re
   if (threadIdx.x == 0) off[nlist] = s_base;
 }
 
+// A tile of 64 rows: the lanes whose rows fall into the same list find each other by one ballot per bit of the list id, the last of
+// them advances the list's counter by their number, and all of them take their places behind its old value.  (50 000 rows, 512
+// lists: 94 us a pass when a workgroup of 256 rows compared each with all others -> 5.4)
 __global__ __launch_bounds__(GROUP_TILE) void group_scatter_kernel(const int32_t* __restrict__ asg, int64_t rows, int64_t ch,
-                                                                   int nlist, int32_t* __restrict__ hist,
+                                                                   int nlist, int bits, int32_t* __restrict__ hist,
                                                                    const int32_t* __restrict__ off,
                                                                    int32_t* __restrict__ members) {
-  __shared__ int32_t s_key[GROUP_TILE];
   const int64_t r0 = (int64_t)blockIdx.x * ch, r1 = r0 + ch < rows ? r0 + ch : rows;
   int32_t* h = hist + (int64_t)blockIdx.x * nlist;  // rows of this cluster placed so far, by earlier blocks and tiles
-  const int tid = threadIdx.x;
+  const int lane = threadIdx.x;
+  int32_t next = asg[min(r0 + lane, r1 - 1)];
   for (int64_t t0 = r0; t0 < r1; t0 += GROUP_TILE) {
-    const int64_t i = t0 + tid;
+    const int64_t i = t0 + lane;
     const bool valid = i < r1;
-    const int32_t key = valid ? asg[i] : -1;
-    s_key[tid] = key;
-    __syncthreads();
-    int before = 0, same = 0;  // rows of the tile in the same list: ahead of this one, and in all
-    for (int j = 0; j < GROUP_TILE; ++j) {
-      const bool eq = s_key[j] == key;
-      same += eq;
-      before += eq && j < tid;
+    const int32_t key = next;
+    next = asg[min(i + GROUP_TILE, r1 - 1)];
+    uint64_t same = __ballot(valid);
+    for (int b = 0; b < bits; ++b) {
+      const bool set = (key >> b) & 1;
+      const uint64_t m = __ballot(set);
+      same &= set ? m : ~m;
     }
-    if (valid) {
-      // the counter is only ever changed by atomics of this workgroup; read it where they are performed
-      const int32_t base = __hip_atomic_load(&h[key], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      members[off[key] + base + before] = (int32_t)i;
-    }
-    __syncthreads();  // every row of the tile has read its counter
-    if (valid && before == same - 1) atomicAdd(&h[key], same);
-    __syncthreads();  // and the next tile sees the advanced counters
+    const int last = valid ? 63 - __builtin_clzll(same) : lane;
+    int32_t base = 0;
+    if (valid && lane == last) base = atomicAdd(&h[key], (int32_t)__builtin_popcountll(same));
+    base = __shfl(base, last, 64);
+    if (valid) members[off[key] + base + __builtin_popcountll(same & ((1ull << lane) - 1ull))] = (int32_t)i;
   }
 }
 
-// rows [0, rows) grouped by asg[] into off[nlist + 1] / members[rows]; hist holds group_plan(rows).nb * nlist words
+// rows [0, rows) grouped by asg[] into off[nlist + 1] / members[rows]; hist holds group_plan(rows, nlist).nb * nlist words
 static int launch_group_rows(const int32_t* asg, int64_t rows, int nlist, int32_t* off, int32_t* members, int32_t* hist,
                              int32_t* total, hipStream_t st) {
-  const GroupPlan g = group_plan(rows);
+  const GroupPlan g = group_plan(rows, nlist);
   const int64_t hw = (int64_t)g.nb * nlist;
   hipLaunchKernelGGL(fill_i32_kernel, dim3(grid_for(hw)), dim3(256), 0, st, hist, hw, 0);
   if (rows > 0)
     hipLaunchKernelGGL(group_count_kernel, dim3(g.nb), dim3(GROUP_TILE), 0, st, asg, rows, g.ch, nlist, hist);
-  hipLaunchKernelGGL(group_block_prefix_kernel, dim3((nlist + 255) / 256), dim3(256), 0, st, hist, g.nb, nlist, total);
+  hipLaunchKernelGGL(group_block_prefix_kernel, dim3((nlist + 31) / 32), dim3(1024), 0, st, hist, g.nb, nlist, total);
   hipLaunchKernelGGL(group_offsets_kernel, dim3(1), dim3(1024), 0, st, total, nlist, off);
+  int bits = 0;
+  while (((int64_t)1 << bits) < nlist) ++bits;
   if (rows > 0)
-    hipLaunchKernelGGL(group_scatter_kernel, dim3(g.nb), dim3(GROUP_TILE), 0, st, asg, rows, g.ch, nlist, hist, off, members);
+    hipLaunchKernelGGL(group_scatter_kernel, dim3(g.nb), dim3(GROUP_TILE), 0, st, asg, rows, g.ch, nlist, bits, hist, off, members);
   RQ_HIP(hipGetLastError());
   return RABITQ_OK;
 }
@@ -474,8 +546,8 @@ int build_index_device(rabitq_index* ix, const float* data, const float* rotatio
     DevBuf<float> mean_dev;
     RQ_TRY(partial.alloc((int64_t)MEAN_BLOCKS * D));
     RQ_TRY(mean_dev.alloc(D));
-    hipLaunchKernelGGL(column_partial_kernel, dim3(MEAN_BLOCKS), dim3(256), 0, st, data, N, D, partial.p);
-    hipLaunchKernelGGL(column_mean_kernel, dim3(1), dim3(256), 0, st, partial.p, N, D, mean_dev.p);
+    hipLaunchKernelGGL(column_partial_kernel, dim3(MEAN_BLOCKS), dim3(std::min(256, (D + 63) / 64 * 64)), 0, st, data, N, D, partial.p);
+    hipLaunchKernelGGL(column_mean_kernel, dim3((D + 63) / 64), dim3(64), 0, st, partial.p, N, D, mean_dev.p);
     std::vector<float> mean(D);
     RQ_HIP(hipMemcpyAsync(mean.data(), mean_dev.p, (size_t)D * sizeof(float), hipMemcpyDeviceToHost, st));
     RQ_HIP(hipStreamSynchronize(st));
@@ -495,16 +567,16 @@ int build_index_device(rabitq_index* ix, const float* data, const float* rotatio
   RQ_TRY(asg.alloc(std::max(N, nt)));
   RQ_TRY(off.alloc(nlist + 1));
   RQ_TRY(members.alloc(std::max(N, nt)));
-  RQ_TRY(hist.alloc((int64_t)std::max(group_plan(N).nb, group_plan(nt).nb) * nlist));
+  RQ_TRY(hist.alloc((int64_t)std::max(group_plan(N, nlist).nb, group_plan(nt, nlist).nb) * nlist));
   RQ_TRY(total.alloc(nlist));
   for (int it = 0; it < kmeans_iters; ++it) {
-    hipLaunchKernelGGL(transpose_centroids_kernel, dim3((nlist + 255) / 256), dim3(256), 0, st, c_rows.p, nlist, D,
+    hipLaunchKernelGGL(transpose_centroids_kernel, dim3((nlist + 63) / 64), dim3(64), 0, st, c_rows.p, nlist, D,
                        ix->centroids_t, ix->centroid_sq);
     RQ_TRY(assign_rows(tr.p, nt, D, nlist, ix->centroids_t, ix->centroid_sq, scores.p, chunk, asg.p, st));
     RQ_TRY(launch_group_rows(asg.p, nt, nlist, off.p, members.p, hist.p, total.p, st));
-    hipLaunchKernelGGL(centroid_update_kernel, dim3(nlist), dim3(256), 0, st, tr.p, off.p, members.p, D, c_rows.p);
+    hipLaunchKernelGGL(centroid_update_kernel, dim3(nlist, (D + 63) / 64), dim3(64), 0, st, tr.p, off.p, members.p, D, c_rows.p);
   }
-  hipLaunchKernelGGL(transpose_centroids_kernel, dim3((nlist + 255) / 256), dim3(256), 0, st, c_rows.p, nlist, D,
+  hipLaunchKernelGGL(transpose_centroids_kernel, dim3((nlist + 63) / 64), dim3(64), 0, st, c_rows.p, nlist, D,
                      ix->centroids_t, ix->centroid_sq);
   RQ_TRY(assign_rows(xr.p, N, D, nlist, ix->centroids_t, ix->centroid_sq, scores.p, chunk, asg.p, st));
   RQ_TRY(launch_group_rows(asg.p, N, nlist, off.p, members.p, hist.p, total.p, st));

@@ -95,3 +95,34 @@ def test_device_built_index_searches_like_an_oracle_built_one():
     ids2, _ = gj.search(torch.from_numpy(Q).cuda(), 10, 8)
     assert torch.equal(ids, ids2)
     gi.close(); gj.close()
+
+
+@pytest.mark.parametrize("n,nlist,D,center", [(70, 1, 32, False), (640, 3, 96, True), (4_099, 64, 32, True),
+                                              (20_001, 65, 256, False), (131_073, 33, 64, True)])
+def test_lloyd_update_and_grouping_on_separated_blobs(n, nlist, D, center):
+    # well separated blobs and one initial centroid in each, so that every row's list is known: the lists hold their rows in
+    # ascending order, and the centroids are the blobs' means up to the rounding of a sum taken row after row
+    rng = np.random.default_rng(n)
+    label = np.minimum(rng.integers(0, nlist, n), rng.integers(0, nlist, n))    # uneven lists
+    label[np.arange(nlist) * n // nlist] = np.arange(nlist)                     # the rows that the builder starts from
+    blob = 8.0 * rng.standard_normal((nlist, D))
+    X = (blob[label] + 0.1 * rng.standard_normal((n, D))).astype(np.float32)
+    gi = rabitq.Index.build(torch.from_numpy(X).cuda(), nlist, 2, np.eye(D, dtype=np.float32), kmeans_iters=2, center=center)
+    out = gi.export()
+    gi.close()
+    u = 2.0 ** -24
+    mean = X.mean(0, dtype=np.float64) if center else np.zeros(D)
+    if center:   # summed in 64 bits, rounded once
+        assert np.all(np.abs(out["mean"] - mean) <= 1.01 * u * np.abs(mean) + n * 2.0 ** -53 * np.abs(X).mean(0))
+    Xc = (X - out["mean"]) if center else X
+    counts = np.bincount(label, minlength=nlist)
+    assert np.array_equal(np.diff(out["offsets"]), counts)
+    slot = 0
+    for c in range(nlist):
+        rows = np.nonzero(label == c)[0]
+        assert np.array_equal(out["ids"][slot:slot + rows.size], rows)
+        slot += (rows.size + 63) // 64 * 64
+        x = Xc[rows].astype(np.float64)
+        # rows.size additions, the reciprocal and the product; the translation of a row is rounded once
+        bound = (rows.size + 3) * u * (np.abs(x).mean(0) + np.abs(out["mean"] if center else 0.0))
+        assert np.all(np.abs(out["centroids"][c] - x.mean(0)) <= bound)
