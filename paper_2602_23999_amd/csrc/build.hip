@@ -56,30 +56,17 @@ __global__ __launch_bounds__(64) void transpose_centroids_kernel(const float* __
   csq[c] = s;
 }
 
-// nearest centroid of each row of a score chunk (scores = ||c||^2 - 2<x,c>), ties to the lower id
-__global__ __launch_bounds__(256) void argmin_rows_kernel(const float* __restrict__ scores, int64_t rows, int nlist,
-                                                         int32_t* __restrict__ out) {
-  const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  const float* row = scores + r * nlist;
+// nearest centroid of each row from the best of every 32 or 64 (launch_gemm_nearest), ties to the lower id; 16 lanes a row
+__global__ __launch_bounds__(256) void nearest_of_parts_kernel(const uint64_t* __restrict__ keys, int64_t rows, int parts,
+                                                              int32_t* __restrict__ out) {
+  const int l = threadIdx.x & 15;
+  const int64_t r = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+  const uint64_t* row = keys + min(r, rows - 1) * parts;
   uint64_t best = KEY_NONE;
-  // eight requests in flight (clamped indices, so that no load sits under a condition)
-  for (int c0 = lane; c0 < nlist; c0 += 8 * 64) {
-    float v[8];
+  for (int p = l; p < parts; p += 16) best = min(best, row[p]);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = row[min(c0 + u * 64, nlist - 1)];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = pinned(v[u]);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int c = c0 + u * 64;
-      const uint64_t key = c < nlist ? make_key(v[u], (uint32_t)c) : KEY_NONE;
-      best = key < best ? key : best;
-    }
-  }
-  best = wave_reduce_u64(best, [](uint64_t a, uint64_t b) { return a < b ? a : b; });
-  if (lane == 0) out[r] = (int32_t)(uint32_t)best;
+  for (int d = 1; d < 16; d <<= 1) best = min(best, (uint64_t)__shfl_xor(best, d, 16));
+  if (l == 0 && r < rows) out[r] = (int32_t)(uint32_t)best;
 }
 
 // Lloyd update: one wavefront per cluster and 64 dimensions sums the members in list order (deterministic); an empty cluster keeps
@@ -514,14 +501,15 @@ static int launch_group_rows(const int32_t* asg, int64_t rows, int nlist, int32_
   return RABITQ_OK;
 }
 
-// nearest rotated centroid of every row of `x` [rows][D]; `scores` holds chunk x nlist floats
-static int assign_rows(const float* x, int64_t rows, int D, int nlist, const float* ct, const float* csq, float* scores,
+// nearest rotated centroid of every row of `x` [rows][D]; `keys` holds chunk x ceil(nlist / 32) words
+static int assign_rows(const float* x, int64_t rows, int D, int nlist, const float* ct, const float* csq, uint64_t* keys,
                        int64_t chunk, int32_t* out, hipStream_t st) {
   for (int64_t s = 0; s < rows; s += chunk) {
     const int64_t m = std::min(chunk, rows - s);
-    int rc = launch_gemm(x + s * D, ct, scores, m, nlist, D, 3, nullptr, csq, nullptr, st);
+    int parts = 0;
+    int rc = launch_gemm_nearest(x + s * D, ct, keys, m, nlist, D, csq, &parts, st);
     if (rc) return rc;
-    hipLaunchKernelGGL(argmin_rows_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, scores, m, nlist, out + s);
+    hipLaunchKernelGGL(nearest_of_parts_kernel, dim3((unsigned)((m + 15) / 16)), dim3(256), 0, st, keys, m, parts, out + s);
   }
   RQ_HIP(hipGetLastError());
   return RABITQ_OK;
@@ -537,7 +525,8 @@ int build_index_device(rabitq_index* ix, const float* data, const float* rotatio
   // clustering and residuals are taken in the rotated space)
   RQ_HIP(hipMalloc(reinterpret_cast<void**>(&ix->rotation), (size_t)D * D * sizeof(float)));
   RQ_HIP(hipMemcpyAsync(ix->rotation, rotation_host, (size_t)D * D * sizeof(float), hipMemcpyHostToDevice, st));
-  DevBuf<float> xr, tr, c_rows, scores;
+  DevBuf<float> xr, tr, c_rows;
+  DevBuf<uint64_t> keys;
   DevBuf<int32_t> asg, off, members, hist, total;
   RQ_TRY(xr.alloc(N * D));
   if (center && N > 0) {
@@ -562,8 +551,9 @@ int build_index_device(rabitq_index* ix, const float* data, const float* rotatio
                      D, c_rows.p);
   RQ_HIP(hipMalloc(reinterpret_cast<void**>(&ix->centroids_t), (size_t)D * nlist * sizeof(float)));
   RQ_HIP(hipMalloc(reinterpret_cast<void**>(&ix->centroid_sq), (size_t)nlist * sizeof(float)));
-  const int64_t chunk = std::max<int64_t>(1024, (int64_t)(64 << 20) / nlist);
-  RQ_TRY(scores.alloc(std::min<int64_t>(chunk, std::max(N, nt)) * nlist));
+  const int nearest_words = (nlist + 31) / 32;
+  const int64_t chunk = std::max<int64_t>(1024, ((int64_t)1 << 23) / nearest_words);  // 64 MiB of keys
+  RQ_TRY(keys.alloc(std::min<int64_t>(chunk, std::max(N, nt)) * nearest_words));
   RQ_TRY(asg.alloc(std::max(N, nt)));
   RQ_TRY(off.alloc(nlist + 1));
   RQ_TRY(members.alloc(std::max(N, nt)));
@@ -572,13 +562,13 @@ int build_index_device(rabitq_index* ix, const float* data, const float* rotatio
   for (int it = 0; it < kmeans_iters; ++it) {
     hipLaunchKernelGGL(transpose_centroids_kernel, dim3((nlist + 63) / 64), dim3(64), 0, st, c_rows.p, nlist, D,
                        ix->centroids_t, ix->centroid_sq);
-    RQ_TRY(assign_rows(tr.p, nt, D, nlist, ix->centroids_t, ix->centroid_sq, scores.p, chunk, asg.p, st));
+    RQ_TRY(assign_rows(tr.p, nt, D, nlist, ix->centroids_t, ix->centroid_sq, keys.p, chunk, asg.p, st));
     RQ_TRY(launch_group_rows(asg.p, nt, nlist, off.p, members.p, hist.p, total.p, st));
     hipLaunchKernelGGL(centroid_update_kernel, dim3(nlist, (D + 63) / 64), dim3(64), 0, st, tr.p, off.p, members.p, D, c_rows.p);
   }
   hipLaunchKernelGGL(transpose_centroids_kernel, dim3((nlist + 63) / 64), dim3(64), 0, st, c_rows.p, nlist, D,
                      ix->centroids_t, ix->centroid_sq);
-  RQ_TRY(assign_rows(xr.p, N, D, nlist, ix->centroids_t, ix->centroid_sq, scores.p, chunk, asg.p, st));
+  RQ_TRY(assign_rows(xr.p, N, D, nlist, ix->centroids_t, ix->centroid_sq, keys.p, chunk, asg.p, st));
   RQ_TRY(launch_group_rows(asg.p, N, nlist, off.p, members.p, hist.p, total.p, st));
   // layout: cluster sizes, tile offsets (the total is needed on the host to size the arrays)
   RQ_HIP(hipMalloc(reinterpret_cast<void**>(&ix->cluster_size), (size_t)nlist * sizeof(int32_t)));

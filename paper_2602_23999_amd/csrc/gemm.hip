@@ -43,6 +43,40 @@ __device__ __forceinline__ float least_of_rows(floatx16 v, int lane, int* row) {
   return fminf(t, dpp_move<0x104>(t));  // bit 2: row_shl:4
 }
 
+// The same over keys of a value and its column (make_key), whose minimum is the smallest value's lowest column.
+struct RowKey {
+  uint32_t ord, col;
+};
+__device__ __forceinline__ RowKey lesser(RowKey a, RowKey b) {
+  const bool first = a.ord < b.ord || (a.ord == b.ord && a.col < b.col);
+  return RowKey{first ? a.ord : b.ord, first ? a.col : b.col};
+}
+template <int CTRL>
+__device__ __forceinline__ RowKey dpp_key(RowKey k) {
+  return RowKey{(uint32_t)__builtin_amdgcn_update_dpp(0, (int)k.ord, CTRL, 0xF, 0xF, true),
+                (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k.col, CTRL, 0xF, 0xF, true)};
+}
+__device__ __forceinline__ RowKey either(bool c, RowKey a, RowKey b) { return RowKey{c ? a.ord : b.ord, c ? a.col : b.col}; }
+
+template <int TN, class Key>
+__device__ __forceinline__ RowKey least_key_of_rows(int lane, int* row, Key&& key) {
+  RowKey a[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const RowKey x = key(r), y = key(r + 8);
+    const auto o = __builtin_amdgcn_permlane16_swap(x.ord, y.ord, false, false);
+    const auto c = __builtin_amdgcn_permlane16_swap(x.col, y.col, false, false);
+    a[r] = lesser(RowKey{o[0], c[0]}, RowKey{o[1], c[1]});
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) a[r] = lesser(either(lane & 1, a[r + 4], a[r]), dpp_key<0xB1>(either(lane & 1, a[r], a[r + 4])));
+#pragma unroll
+  for (int r = 0; r < 2; ++r) a[r] = lesser(either(lane & 2, a[r + 2], a[r]), dpp_key<0x4E>(either(lane & 2, a[r], a[r + 2])));
+  const RowKey t = lesser(either(lane & 8, a[1], a[0]), dpp_key<0x128>(either(lane & 8, a[0], a[1])));
+  *row = ((lane >> 4) & 1) * 8 + (lane & 1) * 4 + ((lane >> 1) & 1) * 2 + ((lane >> 3) & 1);
+  return lesser(t, dpp_key<0x104>(t));
+}
+
 // Block: 256 threads = 4 wavefronts in a 2 x 2 arrangement; a wavefront owns 32 TM rows x 32 TN columns of the block
 // tile (64 TM x 64 TN) as TM x TN 32x32 MFMA accumulators, so with TM = TN = 2 every operand word read from LDS feeds
 // two matrix instructions.  The LDS tiles are double buffered: the next k-step's operands travel from memory to
@@ -127,6 +161,31 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, 
     __syncthreads();
   }
   // accumulator register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32
+  if constexpr (MODE == 5) {
+    // assignment: only the best of a row's 32 TN columns leaves the wavefront
+    const int parts = (N + 32 * TN - 1) / (32 * TN), part = (n0 + wn * 32 * TN) / (32 * TN);
+    float cv[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) cv[j] = colv[min(n0 + wn * 32 * TN + 32 * j + (lane & 31), N - 1)];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      int r;
+      const RowKey best = least_key_of_rows<TN>(lane, &r, [&](int reg) {
+        RowKey k{0xffffffffu, 0xffffffffu};
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int n = n0 + wn * 32 * TN + 32 * j + (lane & 31);
+          const float v = cv[j] - 2.0f * acc[i][j][reg];
+          k = lesser(k, n < N ? RowKey{f2ord(v), (uint32_t)n} : RowKey{0xffffffffu, 0xffffffffu});
+        }
+        return k;
+      });
+      const int64_t m = m0 + wm * 32 * TM + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+      if ((lane & 4) == 0 && m < M && part < parts)
+        reinterpret_cast<uint64_t*>(C)[m * parts + part] = ((uint64_t)best.ord << 32) | best.col;
+    }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -141,7 +200,6 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, 
         float v = acc[i][j][r];
         if (MODE == 1) v = rv + colv[min(n, N - 1)] - 2.0f * v;
         if (MODE == 2) v = -v;
-        if (MODE == 3) v = colv[min(n, N - 1)] - 2.0f * v;
         if (MODE == 4) v = v - colv[min(n, N - 1)];
         if (m_ok && n < N) {
           if (MODE == 1 || MODE == 2) __builtin_nontemporal_store(v, &C[m * (int64_t)N + n]);  // coarse scores: read once, by the selection
@@ -329,7 +387,7 @@ static int launch_gemm_tile(const float* A, const float* B, float* C, int64_t M,
     case 0: hipLaunchKernelGGL((gemm_kernel<0, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv, tmin); break;
     case 1: hipLaunchKernelGGL((gemm_kernel<1, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv, tmin); break;
     case 2: hipLaunchKernelGGL((gemm_kernel<2, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv, tmin); break;
-    case 3: hipLaunchKernelGGL((gemm_kernel<3, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv, tmin); break;
+    case 5: hipLaunchKernelGGL((gemm_kernel<5, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv, tmin); break;
     case 4: hipLaunchKernelGGL((gemm_kernel<4, TM, TN>), grid, dim3(256), 0, st, A, B, C, M, N, K, rowv, colv, tmin); break;
     default: set_error("gemm: bad mode"); return RABITQ_EINVAL;
   }
@@ -353,6 +411,25 @@ int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int 
   // (64 x 128 rather than 128 x 64: a wavefront then stores 256 contiguous bytes of a row of C)
   if (tiles(64, 128) >= 512) return launch_gemm_tile<1, 2>(A, B, C, M, N, K, mode, rowv, colv, tmin, st);
   return launch_gemm_tile<1, 1>(A, B, C, M, N, K, mode, rowv, colv, tmin, st);
+}
+
+// Nearest column of every row of A (by colv[n] - 2 <row, column>, the lowest of equals), as keys over 64 columns each (32 in a small
+// problem): keys[m * *parts + t].  The scores themselves are not written: for 250 000 x 512 x 128 the product that wrote them took 418 us
+// and the search through them 82; this takes 349 and 10 (and 256 MiB less of scratch).
+// (All column tiles of a row tile on one XCD, one after another: 345, within the noise.)
+int launch_gemm_nearest(const float* A, const float* B, uint64_t* keys, int64_t M, int N, int K, const float* colv, int* parts,
+                        hipStream_t st) {
+  if (K % BK != 0 || N <= 0 || M <= 0) {
+    set_error("gemm: K must be a multiple of 16 and the matrix not empty");
+    return RABITQ_EINVAL;
+  }
+  float* C = reinterpret_cast<float*>(keys);
+  auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * (int64_t)((N + bn - 1) / bn); };
+  *parts = (N + 63) / 64;
+  if (K >= 256 && tiles(128, 128) >= 384) return launch_gemm_tile<2, 2>(A, B, C, M, N, K, 5, nullptr, colv, nullptr, st);
+  if (tiles(64, 128) >= 512) return launch_gemm_tile<1, 2>(A, B, C, M, N, K, 5, nullptr, colv, nullptr, st);
+  *parts = (N + 31) / 32;
+  return launch_gemm_tile<1, 1>(A, B, C, M, N, K, 5, nullptr, colv, nullptr, st);
 }
 
 }  // namespace rq

@@ -133,11 +133,13 @@ __host__ __device__ inline float ord2f(uint32_t o) {
 
 // ---- launchers (each returns a rabitq_status) ----
 // C[M,N] = A[M,K] * B[K,N], row-major fp32.  mode 0: plain.  mode 1 (L2 coarse):
-// C = rowv[m] + colv[n] - 2*acc.  mode 2 (IP coarse): C = -acc.  mode 3 (assignment): C = colv[n] - 2*acc.
+// C = rowv[m] + colv[n] - 2*acc.  mode 2 (IP coarse): C = -acc.  (launch_gemm_nearest, the assignment: colv[n] - 2*acc.)
 // mode 4 (rotation of a centred index): C = acc - colv[n].
 // tmin: null, or (modes 1 and 2) receives the smallest entry of every 32 columns, [M][ceil(N / 32)]
 int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* rowv,
                 const float* colv, float* tmin, hipStream_t st);
+int launch_gemm_nearest(const float* A, const float* B, uint64_t* keys, int64_t M, int N, int K, const float* colv, int* parts,
+                        hipStream_t st);
 // small batches: Q' = (Q - mean) P, the queries' representation and the coarse scores [nq][nlist] from one launch,
 // bit-identical to launch_rotate + launch_query_prep + launch_gemm (mode 1 / 2)
 int launch_small_front(const rabitq_index* ix, const float* queries, int64_t nq, float* q_rot, const rabitq_query_repr& o,
