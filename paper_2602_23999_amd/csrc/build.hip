@@ -134,164 +134,197 @@ struct EncodeArgs {
 };
 
 // ---------------------------------------------------------------------------------
-// One wavefront per stored vector (Section 3.2.2 maps a thread block to a vector; a
-// 64-wide wavefront is that block here).  Phase 1: lanes = dimensions (residual, norm,
-// |o'|).  Phase 2: lanes = sampled rescaling factors — every lane walks all dimensions for
-// its own t, so the N_coarse = 64 samples need no cross-lane reduction until the arg-max;
-// then N_fine = 32 samples around the best one (plus the coarse winner itself).  Phase 3:
-// lanes = dimensions again (codes, factor sums, packing).
+// One wavefront per two stored vectors (Section 3.2.2 maps a thread block to a vector).  Phase 1, for each: lanes =
+// dimensions (residual, norm, o').  Phase 2: lanes = sampled rescaling factors — every lane walks all dimensions for
+// its own t, so the N_coarse = 64 samples need no cross-lane reduction until the arg-max; then the N_fine = 32 samples
+// around the best one, half a wavefront for each of the two vectors, against the coarse winner itself.  Phase 3, for
+// each: lanes = dimensions again (codes, factor sums, packing).
+// Bound by the vector instructions of phase 2 (about 6.5 per dimension and sample).  (250 000 x 128: 696 us when a
+// wavefront had one vector, half of its lanes idle in the fine search -> 563)
 // ---------------------------------------------------------------------------------
 template <int DPL>  // dimensions per lane = ceil(D / 64)
 __global__ __launch_bounds__(256) void encode_kernel(EncodeArgs a) {
   extern __shared__ unsigned char smem_raw[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float* ybuf = reinterpret_cast<float*>(smem_raw) + (size_t)wave * a.D;                          // [D] |o'|
-  unsigned char* ubuf = smem_raw + 4 * (size_t)a.D * sizeof(float) + (size_t)wave * a.D;         // [D] codes
-  const int64_t p = a.p0 + (int64_t)blockIdx.x * 4 + wave;  // position in cluster order
-  if (p >= a.n) return;
-  // cluster of this position: largest c with off[c] <= p
-  int lo = 0, hi = a.nlist;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (a.off[mid] <= p) lo = mid; else hi = mid;
-  }
-  const int c = lo;
-  const int32_t vid = a.members[p];
-  const int64_t slot = (int64_t)a.tile_off[c] * TILE + (p - a.off[c]);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int D = a.D, B = a.B;
+  float* obuf = reinterpret_cast<float*>(smem_raw) + (size_t)wave * 2 * D;                        // [2][D] o'
+  unsigned char* ubuf = smem_raw + 8 * (size_t)D * sizeof(float) + (size_t)wave * D;              // [D] codes
+  const int64_t p = a.p0 + 2 * ((int64_t)blockIdx.x * 4 + wave);  // positions in cluster order: this one and the next
+  if (p >= a.n) return;
   const int half = 1 << (B - 1), L = half - 1;
+  const float Lf = (float)L;
 
-  float res[DPL], cr[DPL];
-  float r2 = 0.f, cdotres = 0.f;
-#pragma unroll
-  for (int k = 0; k < DPL; ++k) {
-    const int d = k * 64 + lane;
-    res[k] = 0.f;
-    cr[k] = 0.f;
-    if (d < D) {
-      cr[k] = a.c_rows[(int64_t)c * D + d];
-      res[k] = a.xr[(int64_t)vid * D + d] - cr[k];
-    }
-    r2 += res[k] * res[k];
-    cdotres += cr[k] * res[k];
-  }
-  r2 = wave_sum_f32(r2);
-  cdotres = wave_sum_f32(cdotres);
-  const float r = sqrtf(r2);
-  const bool ok = r > 0.f;
-  const float inv_r = ok ? 1.0f / r : 0.f;
-  float o[DPL], ymax = 0.f;
-#pragma unroll
-  for (int k = 0; k < DPL; ++k) {
-    o[k] = res[k] * inv_r;
-    const int d = k * 64 + lane;
-    if (d < D) ybuf[d] = fabsf(o[k]);
-    ymax = fmaxf(ymax, fabsf(o[k]));
-  }
-  ymax = wave_max_f32(ymax);
-  float t_best = 0.f;
-  if (L > 0 && ok) {
+  int cluster[2];
+  int32_t vid[2];
+  float r[2], r2[2], cdotres[2], t_end[2], t_c[2];
+  bool ok[2];
+  uint32_t coarse[2];  // best objective of the coarse samples, as ordered bits
+  auto wave_fence = [] {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  auto objective = [&](const float* o, float t) -> float {
+    float num = 0.f, den = 0.f;
+    for (int d = 0; d < D; d += 4) {
+      const float4 y = *reinterpret_cast<const float4*>(o + d);
+      const float y0 = fabsf(y.x), y1 = fabsf(y.y), y2 = fabsf(y.z), y3 = fabsf(y.w);
+      const float m0 = fminf(floorf(t * y0), Lf) + 0.5f, m1 = fminf(floorf(t * y1), Lf) + 0.5f;
+      const float m2 = fminf(floorf(t * y2), Lf) + 0.5f, m3 = fminf(floorf(t * y3), Lf) + 0.5f;
+      num += m0 * y0 + m1 * y1 + m2 * y2 + m3 * y3;
+      den += m0 * m0 + m1 * m1 + m2 * m2 + m3 * m3;
+    }
+    return num * rsqrtf(den);
+  };
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    const int64_t pv = p + v < a.n ? p + v : p;
+    // cluster of this position: largest c with off[c] <= p
+    int lo = 0, hi = a.nlist;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (a.off[mid] <= pv) lo = mid; else hi = mid;
+    }
+    cluster[v] = lo;
+    vid[v] = a.members[pv];
+    float res[DPL];
+    r2[v] = 0.f;
+    cdotres[v] = 0.f;
+#pragma unroll
+    for (int k = 0; k < DPL; ++k) {
+      const int d = k * 64 + lane;
+      res[k] = 0.f;
+      float cr = 0.f;
+      if (d < D) {
+        cr = a.c_rows[(int64_t)lo * D + d];
+        res[k] = a.xr[(int64_t)vid[v] * D + d] - cr;
+      }
+      r2[v] += res[k] * res[k];
+      cdotres[v] += cr * res[k];
+    }
+    r2[v] = wave_sum_f32(r2[v]);
+    cdotres[v] = wave_sum_f32(cdotres[v]);
+    r[v] = sqrtf(r2[v]);
+    ok[v] = r[v] > 0.f;
+    const float inv_r = ok[v] ? 1.0f / r[v] : 0.f;
+    float ymax = 0.f;
+#pragma unroll
+    for (int k = 0; k < DPL; ++k) {
+      const float o = res[k] * inv_r;
+      const int d = k * 64 + lane;
+      if (d < D) obuf[v * D + d] = o;
+      ymax = fmaxf(ymax, fabsf(o));
+    }
+    ymax = wave_max_f32(ymax);
     // search range: the best factor lies below range_mult * 2^(B-1) / max|o'| (the fewer
     // levels, the further the bulk of the coordinates may be pushed past the largest one)
     const float range_mult = (B >= 5) ? 1.5f : (B == 4 ? 2.5f : (B == 3 ? 4.5f : 6.0f));
-    const float t_end = range_mult * (float)half / ymax;
-    const float Lf = (float)L;
-    auto objective = [&](float t) -> float {
-      float num = 0.f, den = 0.f;
-      for (int d = 0; d < D; d += 4) {
-        const float4 y = *reinterpret_cast<const float4*>(ybuf + d);
-        const float m0 = fminf(floorf(t * y.x), Lf) + 0.5f, m1 = fminf(floorf(t * y.y), Lf) + 0.5f;
-        const float m2 = fminf(floorf(t * y.z), Lf) + 0.5f, m3 = fminf(floorf(t * y.w), Lf) + 0.5f;
-        num += m0 * y.x + m1 * y.y + m2 * y.z + m3 * y.w;
-        den += m0 * m0 + m1 * m1 + m2 * m2 + m3 * m3;
-      }
-      return num * rsqrtf(den);
-    };
+    t_end[v] = range_mult * (float)half / ymax;
+    t_c[v] = 0.f;
+    coarse[v] = 0u;
+  }
+  wave_fence();
+  float t_best[2] = {0.f, 0.f};
+  if (L > 0 && (ok[0] || ok[1])) {
     // coarse: t_k = (k+1)/64 * t_end, one sample per lane; ties go to the smaller t
-    const float tc = (float)(lane + 1) * (1.0f / 64.0f) * t_end;
-    uint64_t key = ((uint64_t)f2ord(objective(tc)) << 32) | (uint32_t)(63 - lane);
-    key = wave_reduce_u64(key, [](uint64_t x, uint64_t y) { return x > y ? x : y; });
-    const int kc = 63 - (int)(uint32_t)key;
-    const float t_c = (float)(kc + 1) * (1.0f / 64.0f) * t_end;
-    // fine: 32 samples uniform over t_c -+ t_end/64 (lanes 0..31), lane 32 re-evaluates t_c
-    const float width = t_end * (1.0f / 64.0f);
-    float tf = t_c;
-    if (lane < 32) tf = fmaxf(t_c + width * (-1.0f + 2.0f * (float)lane * (1.0f / 31.0f)), 0.f);
-    uint64_t key2 = 0ull;
-    if (lane <= 32) key2 = ((uint64_t)f2ord(objective(tf)) << 32) | (uint32_t)(63 - lane);
-    key2 = wave_reduce_u64(key2, [](uint64_t x, uint64_t y) { return x > y ? x : y; });
-    const int kf = 63 - (int)(uint32_t)key2;
-    t_best = __shfl(tf, kf, 64);
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      if (!ok[v]) continue;
+      const float tc = (float)(lane + 1) * (1.0f / 64.0f) * t_end[v];
+      uint64_t key = ((uint64_t)f2ord(objective(obuf + v * D, tc)) << 32) | (uint32_t)(63 - lane);
+      key = wave_reduce_u64(key, [](uint64_t x, uint64_t y) { return x > y ? x : y; });
+      const int kc = 63 - (int)(uint32_t)key;
+      t_c[v] = (float)(kc + 1) * (1.0f / 64.0f) * t_end[v];
+      coarse[v] = (uint32_t)(key >> 32);
+    }
+    // fine: 32 samples uniform over t_c -+ t_end/64, a half of the wavefront for each vector, and t_c itself after them
+    const int mine = lane >> 5, sample = lane & 31;
+    const float my_t_c = mine ? t_c[1] : t_c[0];
+    const float width = (mine ? t_end[1] : t_end[0]) * (1.0f / 64.0f);
+    const float tf = fmaxf(my_t_c + width * (-1.0f + 2.0f * (float)sample * (1.0f / 31.0f)), 0.f);
+    uint64_t key = ((uint64_t)f2ord(objective(obuf + mine * D, tf)) << 32) | (uint32_t)(63 - sample);
+#pragma unroll
+    for (int d = 1; d < 32; d <<= 1) {
+      const uint64_t other = (uint64_t)__shfl_xor((unsigned long long)key, d, 64);
+      key = other > key ? other : key;
+    }
+    const uint64_t at_c = ((uint64_t)(mine ? coarse[1] : coarse[0]) << 32) | 31u;
+    const float t_fine = __shfl(tf, 32 * mine + ((63 - (int)(uint32_t)key) & 31), 64);
+    const float t_mine = at_c > key ? my_t_c : t_fine;
+    t_best[0] = __shfl(t_mine, 0, 64);
+    t_best[1] = __shfl(t_mine, 32, 64);
   }
   // codes and factor sums (lanes = dimensions)
   const float cB = (float)((1 << B) - 1) * 0.5f;
-  float xo = 0.f, xc = 0.f, xx = 0.f, bo = 0.f, bc = 0.f;
-  uint32_t u[DPL];
 #pragma unroll
-  for (int k = 0; k < DPL; ++k) {
-    const int d = k * 64 + lane;
-    const float y = fabsf(o[k]);
-    const int m = (L > 0 && ok) ? (int)fminf(floorf(t_best * y), (float)L) : 0;
-    const bool pos = o[k] >= 0.f;
-    u[k] = ok ? (uint32_t)(pos ? half + m : half - 1 - m) : (uint32_t)half;
-    if (d < D) {
-      ubuf[d] = (unsigned char)u[k];
-      const float x = (float)u[k] - cB;
-      const float xb = (float)(u[k] >> (B - 1)) - 0.5f;
-      xo += x * o[k]; xc += x * cr[k]; xx += x * x;
-      bo += xb * o[k]; bc += xb * cr[k];
+  for (int v = 0; v < 2; ++v) {
+    if (p + v >= a.n) break;
+    const int64_t slot = (int64_t)a.tile_off[cluster[v]] * TILE + (p + v - a.off[cluster[v]]);
+    float xo = 0.f, xc = 0.f, xx = 0.f, bo = 0.f, bc = 0.f;
+    uint32_t u[DPL];
+#pragma unroll
+    for (int k = 0; k < DPL; ++k) {
+      const int d = k * 64 + lane;
+      const float o = d < D ? obuf[v * D + d] : 0.f, cr = d < D ? a.c_rows[(int64_t)cluster[v] * D + d] : 0.f;
+      const float y = fabsf(o);
+      const int m = (L > 0 && ok[v]) ? (int)fminf(floorf(t_best[v] * y), Lf) : 0;
+      const bool pos = o >= 0.f;
+      u[k] = ok[v] ? (uint32_t)(pos ? half + m : half - 1 - m) : (uint32_t)half;
+      if (d < D) {
+        ubuf[d] = (unsigned char)u[k];
+        const float x = (float)u[k] - cB;
+        const float xb = (float)(u[k] >> (B - 1)) - 0.5f;
+        xo += x * o; xc += x * cr; xx += x * x;
+        bo += xb * o; bc += xb * cr;
+      }
     }
-  }
-  xo = wave_sum_f32(xo); xc = wave_sum_f32(xc); xx = wave_sum_f32(xx);
-  bo = wave_sum_f32(bo); bc = wave_sum_f32(bc);
-  // short code: sign bits, 64 dimensions per ballot
-  const int W = D >> 5;
-  const int64_t tile = slot >> 6;
-  const int ln = (int)(slot & 63);
+    xo = wave_sum_f32(xo); xc = wave_sum_f32(xc); xx = wave_sum_f32(xx);
+    bo = wave_sum_f32(bo); bc = wave_sum_f32(bc);
+    // short code: sign bits, 64 dimensions per ballot
+    const int W = D >> 5;
+    const int64_t tile = slot >> 6;
+    const int ln = (int)(slot & 63);
 #pragma unroll
-  for (int k = 0; k < DPL; ++k) {
-    const int d = k * 64 + lane;
-    const uint64_t m = __ballot(d < D && ((u[k] >> (B - 1)) & 1u));
+    for (int k = 0; k < DPL; ++k) {
+      const int d = k * 64 + lane;
+      const uint64_t m = __ballot(d < D && ((u[k] >> (B - 1)) & 1u));
+      if (lane == 0) {
+        const int w = 2 * k;
+        if (w < W) a.short_codes[(tile * W + w) * TILE + ln] = (uint32_t)m;
+        if (w + 1 < W) a.short_codes[(tile * W + w + 1) * TILE + ln] = (uint32_t)(m >> 32);
+      }
+    }
     if (lane == 0) {
-      const int w = 2 * k;
-      if (w < W) a.short_codes[(tile * W + w) * TILE + ln] = (uint32_t)m;
-      if (w + 1 < W) a.short_codes[(tile * W + w + 1) * TILE + ln] = (uint32_t)(m >> 32);
+      const float Df = (float)D;
+      float f1[3] = {0.f, 0.f, 0.f}, fB[2] = {0.f, 0.f};
+      if (ok[v]) {
+        const float scale = (a.metric == RABITQ_L2) ? 2.0f : 1.0f;
+        const float lead = (a.metric == RABITQ_L2) ? r2[v] : -cdotres[v];
+        const float a1 = fminf(fmaxf(bo / (0.5f * sqrtf(Df)), 0.f), 1.f);
+        f1[0] = lead + scale * r[v] * bc / bo;
+        f1[1] = -scale * r[v] / bo;
+        f1[2] = scale * r[v] * a.eps0 * sqrtf(fmaxf(1.f - a1 * a1, 0.f)) / (a1 * sqrtf(Df - 1.f));
+        fB[0] = lead + scale * r[v] * xc / xo;
+        fB[1] = -scale * r[v] / xo;
+      }
+      a.short_factors[(tile * 3 + 0) * TILE + ln] = f1[0];
+      a.short_factors[(tile * 3 + 1) * TILE + ln] = f1[1];
+      a.short_factors[(tile * 3 + 2) * TILE + ln] = f1[2];
+      if (B > 1) {
+        a.long_factors[2 * slot] = fB[0];
+        a.long_factors[2 * slot + 1] = fB[1];
+      }
+      a.ids[slot] = vid[v];
     }
-  }
-  if (lane == 0) {
-    const float Df = (float)D;
-    float f1[3] = {0.f, 0.f, 0.f}, fB[2] = {0.f, 0.f};
-    if (ok) {
-      const float scale = (a.metric == RABITQ_L2) ? 2.0f : 1.0f;
-      const float lead = (a.metric == RABITQ_L2) ? r2 : -cdotres;
-      const float a1 = fminf(fmaxf(bo / (0.5f * sqrtf(Df)), 0.f), 1.f);
-      f1[0] = lead + scale * r * bc / bo;
-      f1[1] = -scale * r / bo;
-      f1[2] = scale * r * a.eps0 * sqrtf(fmaxf(1.f - a1 * a1, 0.f)) / (a1 * sqrtf(Df - 1.f));
-      fB[0] = lead + scale * r * xc / xo;
-      fB[1] = -scale * r / xo;
-    }
-    a.short_factors[(tile * 3 + 0) * TILE + ln] = f1[0];
-    a.short_factors[(tile * 3 + 1) * TILE + ln] = f1[1];
-    a.short_factors[(tile * 3 + 2) * TILE + ln] = f1[2];
     if (B > 1) {
-      a.long_factors[2 * slot] = fB[0];
-      a.long_factors[2 * slot + 1] = fB[1];
-    }
-    a.ids[slot] = vid;
-  }
-  if (B > 1) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int per = 32 / a.F;
-    for (int w = lane; w < a.LW; w += 64) {
-      uint32_t word = 0;
-      for (int j = 0; j < per; ++j) word |= (uint32_t)ubuf[w * per + j] << (a.F * j);
-      a.long_codes[slot * a.LW + w] = word;
+      wave_fence();
+      const int per = 32 / a.F;
+      for (int w = lane; w < a.LW; w += 64) {
+        uint32_t word = 0;
+        for (int j = 0; j < per; ++j) word |= (uint32_t)ubuf[w * per + j] << (a.F * j);
+        a.long_codes[slot * a.LW + w] = word;
+      }
+      wave_fence();  // (the next vector's codes take the same place)
     }
   }
 }
@@ -615,8 +648,8 @@ int build_index_device(rabitq_index* ix, const float* data, const float* rotatio
   constexpr int64_t SLICE = (int64_t)1 << 24;
   for (int64_t p0 = 0; p0 < N; p0 += SLICE) {
     a.p0 = p0;
-    const unsigned grid = (unsigned)((std::min(SLICE, N - p0) + 3) / 4);
-    const size_t smem = 4 * (size_t)D * (sizeof(float) + 1);
+    const unsigned grid = (unsigned)((std::min(SLICE, N - p0) + 7) / 8);
+    const size_t smem = 4 * (size_t)D * (2 * sizeof(float) + 1);
     const int dpl = (D + 63) / 64;
     if (dpl <= 2) hipLaunchKernelGGL(encode_kernel<2>, dim3(grid), dim3(256), smem, st, a);
     else if (dpl <= 4) hipLaunchKernelGGL(encode_kernel<4>, dim3(grid), dim3(256), smem, st, a);
