@@ -87,7 +87,8 @@ def scan_algorithmic_bytes(gi, Qd, nprobe, cluster_sizes, dim):
 def kernel_source_hash():
     """Identifies the scan kernel a stored counter reading belongs to."""
     h = hashlib.sha256()
-    for fn in ("scan.hip", "estimate_mfma.hip", "rq_device.h", "rq_scan_args.h", "scan_dispatch.hip"):
+    for fn in ("scan.hip", "scan_group.hip", "estimate_mfma.hip", "rq_estimate.h", "rq_device.h", "rq_scan_args.h",
+               "scan_dispatch.hip"):
         h.update(open(os.path.join(ROOT, "paper_2602_23999_amd", "csrc", fn), "rb").read())
     return h.hexdigest()[:16]
 
@@ -256,7 +257,10 @@ def scan_roofline(gi, Qd, w, pt, cluster_sizes, args):
                 "hbm_view": {"algorithmic_bytes_per_launch": alg_bytes, "achieved_gbs": achieved, "peak_gbs": HBM_PEAK_GBS,
                              "frac": achieved / HBM_PEAK_GBS,
                              "note": "above 1 when the launch is cache-served; the HBM-bound regime is roofline.stream"}}
-    if split:
+    if split and pt["scan_estimate_ms"] <= 0:
+        # Scan by groups: one kernel estimates (matrix cores) and refines for 16 pairs of a list per wavefront
+        roofline["kernel"] = "scan_group_kernel"
+    elif split:
         # Split search: the estimates run as estimate_mfma_kernel (matrix cores), the refinement as scan_kernel in its
         # refinement-only form; kernel_ms is the time of the two together (HIP events around both), and `achieved`
         # prices the stage with the same algorithmic figure as the fused kernel, 8W + 6 lane-operations per evaluation.
@@ -272,12 +276,12 @@ def scan_roofline(gi, Qd, w, pt, cluster_sizes, args):
                                           "achieved_tops": mfma_ops / (est_ms * 1e-3) / 1e12 if est_ms > 0 else None,
                                           "peak_tops": MFMA_I8_PEAK_TOPS,
                                           "frac": mfma_ops / (est_ms * 1e-3) / 1e12 / MFMA_I8_PEAK_TOPS if est_ms > 0 else None}})
-    if impl == 1:
-        # the matrix-core scan contracts sign bytes with the int8 query: 2 D integer operations per evaluation on
-        # v_mfma_i32_16x16x64_i8, priced against the dense int8 peak
+    if impl == 1 or roofline["kernel"] == "scan_group_kernel":
+        # the matrix-core scans contract sign bits with the quantised query: 2 D operations per evaluation (int8, by
+        # groups fp8 x fp4), priced against the dense 8-bit peak
         mfma_ops = qv * 2 * w.dim
         mfma_achieved = mfma_ops / (scan_ms * 1e-3) / 1e12
-        roofline.update({"bound": "mfma", "achieved": mfma_achieved, "peak": MFMA_I8_PEAK_TOPS, "unit": "TOP/s (int8)",
+        roofline.update({"bound": "mfma", "achieved": mfma_achieved, "peak": MFMA_I8_PEAK_TOPS, "unit": "TOP/s (8-bit)",
                          "frac": mfma_achieved / MFMA_I8_PEAK_TOPS, "algorithmic_ops_per_launch": mfma_ops,
                          "alu_view": {"lane_ops_per_launch": alu_ops, "achieved_tops": alu_achieved,
                                       "peak_tops": ALU_PEAK_TOPS,
