@@ -204,7 +204,8 @@ int rabitq_search_noalloc(rabitq_index_t index, const float* queries, int64_t nq
  *             qhat with v_mfma_i32_16x16x64_i8).  Results of 0 and 1 are identical; only speed differs.
  *             4: scan by groups: one wavefront per 16 pairs of a cluster estimates and filters on the matrix cores
  *             (v_mfma_scale_f32_16x16x128_f8f6f4 on the exact fp8 and fp4 forms of qhat and the sign bits) and refines
- *             the survivors.  For 256 < D < 960, and where one list is so long that its wavefront would outlast the launch, as two
+ *             the survivors.  For 256 < D < 960, and where the groups are few or one list is so long that its wavefront would outlast
+ *             the launch, as two
  *             kernels: the first leaves one bit per (pair, vector), the kernel of 0 then only refines.  Taken for B > 1 and
  *             at least "split_min_pairs" (an option; default 32; from D = 960 on at most 8) pairs per list on average,
  *             otherwise as 0.  Same results.  The survivor bits and the work-item descriptors live in buffers the handle

@@ -197,11 +197,16 @@ inline bool split_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
 // ... as one kernel, the group scan (scan_group.hip says why these widths).  For codes of up to 256 dimensions it does not cut
 // lists into segments, so the longest list must not outlast the launch: one wavefront works on it, while the chip's about
 // 3072 share the rest.  From D = 960 on it takes the place of the four-wavefront matrix-core kernel from 8 pairs per list on.
+// A wavefront has 16 pairs to itself, so a search of few pairs leaves the chip idle: with less than a wavefront for every place
+// (16 lists, 424 queries x 8: 120 us split, 244 by groups; 31 lists, 1733 x 15: 205 and 323; from 512 groups on with the shorter work
+// items of D >= 960, where 250 took 727 us against 583 and 1000 take 819 against 964) the former kernels keep it.  (split_min_pairs
+// scales both lines, 0 takes it always.)
 inline bool group_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
   if (!split_built(ix) || (ix->scan_impl != 3 && ix->scan_impl != 4)) return false;
   const int64_t pairs = nq * nprobe;
-  if (ix->W >= 30) return pairs >= (int64_t)(ix->split_min_pairs < 8 ? ix->split_min_pairs : 8) * ix->nlist;
-  if (ix->W > 8 || pairs < (int64_t)ix->split_min_pairs * ix->nlist) return false;
+  const int64_t least = ix->split_min_pairs < 32 ? ix->split_min_pairs : 32;
+  if (ix->W >= 30) return pairs >= (least < 8 ? least : 8) * ix->nlist && pairs >= QM * 16 * least;
+  if (ix->W > 8 || pairs < (int64_t)ix->split_min_pairs * ix->nlist || pairs < QM * 96 * least) return false;
   const int64_t share = (pairs / QM + ix->nlist) * (ix->n_tiles / (ix->nlist > 0 ? ix->nlist : 1) + 1) / 3072;
   return ix->max_tiles <= (share > 32 ? 2 * share : 64);
 }

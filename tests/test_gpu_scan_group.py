@@ -36,7 +36,7 @@ def test_group_scan_finds_what_the_single_kernels_find(D, bits, nlist, n, nq, np
     Q[3] *= 1e-20
     gi = rabitq.Index.build(torch.from_numpy(X).cuda(), nlist, bits, build.random_rotation(D, 7), metric=metric, kmeans_iters=2)
     q = torch.from_numpy(Q).cuda()
-    gi.set_option("split_min_pairs", 1)
+    gi.set_option("split_min_pairs", 0)   # by groups however few the pairs
     for prune in (1, 0):
         gi.set_option("prune", prune)
         gi.set_option("scan_impl", 0)
