@@ -523,7 +523,7 @@ int rabitq_query_prep(rabitq_index_t ix, const float* q_rot, int64_t nq, const r
   if (rc) return rc;
   if (nq == 0) return RABITQ_OK;
   if (!q_rot || !repr_ok(out)) { set_error("query_prep: null pointer"); return RABITQ_EINVAL; }
-  return launch_query_prep(q_rot, nq, ix->dim, ix->F, *out, 0, (hipStream_t)stream);
+  return launch_query_prep(q_rot, nq, ix->dim, ix->F, *out, 0, PrepClear{}, (hipStream_t)stream);
 }
 
 int rabitq_coarse_probe(rabitq_index_t ix, const float* q_rot, const float* sq_norm, int64_t nq, int32_t nprobe,
@@ -660,11 +660,13 @@ static int search_batch_body(rabitq_index* ix, Workspace& w, const float* querie
   const int n_t = (ix->nlist + 31) / 32;
   const bool by_minima = !small && select_by_minima(ix->nlist, nprobe) && n_t <= 2 * (int64_t)nprobe * cap;
   float* tmin = by_minima ? reinterpret_cast<float*>(w.cand_keys) : nullptr;
+  const PrepClear clear = small || early_clear ? PrepClear{} : prep_clear(nq, ix->nlist, nprobe, w.list_scratch, w.cand_cnt);
+  const bool cleared = early_clear || clear.n_bitmap > 0;
   if (small) {
     RQ_STAGE(0, st, launch_small_front(ix, queries, nq, w.q_rot, repr, form, w.scores, st));
   } else {
     RQ_STAGE(0, st, launch_rotate(ix, queries, w.q_rot, nq, st));
-    RQ_STAGE(1, st, launch_query_prep(w.q_rot, nq, ix->dim, ix->F, repr, form, st));
+    RQ_STAGE(1, st, launch_query_prep(w.q_rot, nq, ix->dim, ix->F, repr, form, clear, st));
     RQ_STAGE(2, st, launch_gemm(w.q_rot, ix->centroids_t, w.scores, nq, ix->nlist, ix->dim,
                                 ix->metric == RABITQ_L2 ? 1 : 2, w.repr.sq_norm, ix->centroid_sq, tmin, st));
   }
@@ -694,7 +696,7 @@ static int search_batch_body(rabitq_index* ix, Workspace& w, const float* querie
                                               w.cand_cnt, lst));
   } else {
     RQ_STAGE(4, lst, launch_build_lists(w.probe_ids, nq, nprobe, ix->nlist, w.pair_off, w.pair_ids, w.list_scratch, lst,
-                                        early_clear));
+                                        cleared));
   }
   // With one probed list and 1-bit codes the threshold would be the k-th smallest estimate of that very list: the
   // scan's own top-k selects the same vectors, so the seeding pass (a second read of the list) is left out.
@@ -707,7 +709,7 @@ static int search_batch_body(rabitq_index* ix, Workspace& w, const float* querie
   }
   ScanStreams ss;
   ss.main = st; ss.setup = lst; ss.join = ix->ev_join;
-  ss.counters_clear = early_clear;
+  ss.counters_clear = cleared;
   ss.setup_done = small;
   ss.desc_done = small_fused;
   if (ev && ((ix->prof_mask >> 6) & 1u)) { ss.setup_b = ev->b[6]; ss.setup_e = ev->e[6]; ev->rec |= 1u << 6; }

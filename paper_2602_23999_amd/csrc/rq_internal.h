@@ -148,7 +148,15 @@ int launch_small_front(const rabitq_index* ix, const float* queries, int64_t nq,
 // its scans what they would otherwise make of it themselves, in the same space: the refinement's digits of q' in
 // q_stage, the group scan's operand in qhat8 (rq_device.h).  Same numbers either way.
 enum QueryForm { QUERY_DIGITS = 1, QUERY_FP8 = 2 };
-int launch_query_prep(const float* q_rot, int64_t nq, int D, int F, const rabitq_query_repr& out, int form, hipStream_t st);
+struct PrepClear {  // memory that the preparation of a batch sets to zero on the way (none: all zero)
+  uint32_t* bitmap = nullptr;
+  int64_t n_bitmap = 0;
+  int32_t* counters = nullptr;
+  int64_t n_counters = 0;
+};
+PrepClear prep_clear(int64_t nq, int nlist, int nprobe, uint32_t* bitmap, int32_t* counters);
+int launch_query_prep(const float* q_rot, int64_t nq, int D, int F, const rabitq_query_repr& out, int form, const PrepClear& clear,
+                      hipStream_t st);
 // tmin: the smallest score of every 32 lists (launch_gemm), or null
 bool select_by_minima(int nlist, int nprobe);  // is it worth having
 int launch_select_probes(const float* scores, const float* tmin, const float* sq_norm, const float* centroid_sq, int64_t nq, int nlist,

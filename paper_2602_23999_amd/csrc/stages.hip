@@ -12,22 +12,33 @@ namespace rq {
 // ---------------------------------------------------------------------------------
 template <int F>
 __global__ __launch_bounds__(256) void query_prep_kernel(const float* __restrict__ q_rot, int64_t nq, int D,
-                                                        rabitq_query_repr o, int form) {
+                                                        rabitq_query_repr o, int form, PrepClear clear) {
   const int lane = threadIdx.x & 63;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < clear.n_bitmap; i += (int64_t)gridDim.x * 256) clear.bitmap[i] = 0u;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < clear.n_counters; i += (int64_t)gridDim.x * 256) clear.counters[i] = 0;
   const int64_t q = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (q >= nq) return;
   query_prep_row<F>(q_rot + q * D, q, D, o, lane, form);
 }
 
+// A batch that is too small for a stream of its own to clear the list builder's bitmap and the candidate counters lets its query
+// preparation do it: two launches of 3-5 us fewer in a chain of fourteen.  Up to 8 words per thread of that kernel (a few us; beyond
+// it the launches of their own have more workgroups to do it with).
+PrepClear prep_clear(int64_t nq, int nlist, int nprobe, uint32_t* bitmap, int32_t* counters) {
+  const int64_t n_bitmap = (int64_t)nlist * ((nq + 31) / 32), n_counters = nq * nprobe;
+  if (n_bitmap + n_counters > 8 * 64 * nq) return PrepClear{};
+  return PrepClear{bitmap, n_bitmap, counters, n_counters};
+}
+
 int launch_query_prep(const float* q_rot, int64_t nq, int D, int F, const rabitq_query_repr& out, int form,
-                      hipStream_t st) {
+                      const PrepClear& clear, hipStream_t st) {
   if (nq <= 0) return RABITQ_OK;
   const unsigned grid = (unsigned)((nq + 3) / 4);
   switch (F) {
-    case 0: hipLaunchKernelGGL(query_prep_kernel<0>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form); break;
-    case 2: hipLaunchKernelGGL(query_prep_kernel<2>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form); break;
-    case 4: hipLaunchKernelGGL(query_prep_kernel<4>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form); break;
-    default: hipLaunchKernelGGL(query_prep_kernel<8>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form); break;
+    case 0: hipLaunchKernelGGL(query_prep_kernel<0>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form, clear); break;
+    case 2: hipLaunchKernelGGL(query_prep_kernel<2>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form, clear); break;
+    case 4: hipLaunchKernelGGL(query_prep_kernel<4>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form, clear); break;
+    default: hipLaunchKernelGGL(query_prep_kernel<8>, dim3(grid), dim3(256), 0, st, q_rot, nq, D, out, form, clear); break;
   }
   RQ_HIP(hipGetLastError());
   return RABITQ_OK;
