@@ -459,6 +459,7 @@ int64_t rabitq_index_info(rabitq_index_t ix, const char* name) {
   if (!std::strcmp(name, "long_field_bits")) return ix->F;
   if (!std::strcmp(name, "metric")) return ix->metric;
   if (!std::strcmp(name, "last_scan_split")) return ix->last_scan_split;
+  if (!std::strcmp(name, "last_scan_group")) return ix->last_scan_group;
   if (!std::strcmp(name, "last_scan_stream")) return ix->last_scan_stream;
   set_error("index_info: unknown name");
   return RABITQ_EINVAL;
@@ -600,6 +601,7 @@ int rabitq_scan(rabitq_index_t ix, const rabitq_query_repr* repr, const float* p
   rc = launch_scan(ix, *repr, 0, probe_G, probe_E, pair_off, pair_ids, tau, nq, k, nprobe, cand_keys, cand_cnt, dbg_ip,
                    dbg_off, ss);
   ix->last_scan_split = ss.split ? 1 : 0;
+  ix->last_scan_group = ss.grouped ? 1 : 0;
   ix->last_scan_stream = ss.streamed ? 1 : 0;
   return rc;
 }
@@ -720,6 +722,7 @@ static int search_batch_body(rabitq_index* ix, Workspace& w, const float* querie
     return rc;
   if (ss.est_b && ss.estimated) ev->rec |= 1u << 9;
   ix->last_scan_split = ss.split ? 1 : 0;
+  ix->last_scan_group = ss.grouped ? 1 : 0;
   ix->last_scan_stream = ss.streamed ? 1 : 0;
   RQ_STAGE(8, st, launch_merge(w.cand_keys, w.cand_cnt, nq, k, nprobe, ix->metric, out_ids, out_dists, st));
 #undef RQ_STAGE

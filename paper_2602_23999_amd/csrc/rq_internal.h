@@ -75,6 +75,7 @@ struct rabitq_index {
                       // 4 estimates on the matrix cores + refinement by the popcount kernel (split search)
   // survivor bits of the split search: blocks of 16 words; grown on demand by ensure_split_buffers, kept by the handle
   int last_scan_split = 0;   // the scan of the latest rabitq_search / rabitq_scan was split (rabitq_index_info)
+  int last_scan_group = 0;   // ... by the group scan, as one kernel
   int last_scan_stream = 0;  // ... was the prefetching variant of the popcount kernel (one pair per work item)
   int split_min_pairs = 32;  // pairs per list, on average, from which scan_impl 3 / 4 split the search
   uint64_t* surv_mask = nullptr;
@@ -178,6 +179,7 @@ struct ScanStreams {
   hipEvent_t est_b = nullptr, est_e = nullptr;  // around the estimate kernel of a split search
   mutable bool split = false;                  // out: the estimates ran on the matrix cores (group scan or split search)
   mutable bool estimated = false;              // out: ... as a kernel of their own, between est_b and est_e
+  mutable bool grouped = false;                // out: ... in the group scan
   mutable bool streamed = false;               // out: the prefetching variant of the popcount kernel ran
   bool counters_clear = false;  // cand_cnt was already zeroed by launch_clear_counters
   bool desc_done = false;       // ... and so were the descriptors of the prefetching scan's work items (launch_small_select_seed)
@@ -213,7 +215,8 @@ inline bool group_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
   if (!split_built(ix) || (ix->scan_impl != 3 && ix->scan_impl != 4)) return false;
   const int64_t pairs = nq * nprobe;
   const int64_t least = ix->split_min_pairs < 32 ? ix->split_min_pairs : 32;
-  if (ix->W >= 30) return pairs >= (least < 8 ? least : 8) * ix->nlist && pairs >= QM * 16 * least;
+  // (scan_impl 4 takes it at any number of groups: there is no split search of that width)
+  if (ix->W >= 30) return pairs >= (least < 8 ? least : 8) * ix->nlist && (ix->scan_impl == 4 || pairs >= QM * 16 * least);
   if (ix->W > 8 || pairs < (int64_t)ix->split_min_pairs * ix->nlist || pairs < QM * 96 * least) return false;
   const int64_t share = (pairs / QM + ix->nlist) * (ix->n_tiles / (ix->nlist > 0 ? ix->nlist : 1) + 1) / 3072;
   return ix->max_tiles <= (share > 32 ? 2 * share : 64);

@@ -175,9 +175,10 @@ int64_t split_mask_blocks(rabitq_index* ix, int64_t nq, int nprobe) {
   return (nq * ix->tiles_prefix[top] + QM - 1) / QM + ix->n_tiles;
 }
 
-// few pairs per list, popcount kernel, not split: the shape the prefetching variant is for
+// few pairs per list, popcount kernel, neither split nor by groups: the shape the prefetching variant is for
 static bool stream_shape(const rabitq_index* ix, int64_t nq, int nprobe) {
-  return effective_impl(ix) == 0 && nq * nprobe <= 4 * (int64_t)ix->nlist && !split_wanted(ix, nq, nprobe);
+  return effective_impl(ix) == 0 && nq * nprobe <= 4 * (int64_t)ix->nlist && !split_wanted(ix, nq, nprobe) &&
+         !group_wanted(ix, nq, nprobe);
 }
 static ScanPlan plan_for(const rabitq_index* ix, int64_t nq, int nprobe, int k, bool streaming, bool group = false);
 static ScanPlan group_plan(const rabitq_index* ix, int64_t nq, int nprobe, int k) { return plan_for(ix, nq, nprobe, k, false, true); }
@@ -450,6 +451,7 @@ int launch_scan(rabitq_index* ix, const rabitq_query_repr& repr, int form, const
   const int64_t max_items = a.streaming ? stream_item_bound(ix, nq, nprobe, plan) : item_bound(ix, nq, nprobe, qw);
   ss.split = split || group;
   ss.estimated = split;
+  ss.grouped = group;
   ss.streamed = a.streaming != 0;
   int32_t* item16 = ix->tile_off + 2 * (ix->nlist + 1) + TICKET_WORDS;
   uint32_t* mask_off = reinterpret_cast<uint32_t*>(item16 + (ix->nlist + 1));
