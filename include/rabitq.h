@@ -204,19 +204,21 @@ int rabitq_search_noalloc(rabitq_index_t index, const float* queries, int64_t nq
  *             qhat with v_mfma_i32_16x16x64_i8).  Results of 0 and 1 are identical; only speed differs.
  *             4: scan by groups: one wavefront per 16 pairs of a cluster estimates and filters on the matrix cores
  *             (v_mfma_scale_f32_16x16x128_f8f6f4 on the exact fp8 and fp4 forms of qhat and the sign bits) and refines
- *             the survivors.  For 256 < D < 960, and up to 256 dimensions where the groups are few or one list is so long that
- *             its wavefront would outlast the launch, as two kernels: the first leaves one bit per (pair, vector), the kernel of 0 then only refines.  Taken for B > 1 and
+ *             the survivors.  For 256 < D < 960, and up to 256 dimensions where there are less than "group_min" groups or one
+ *             list is so long that its wavefront would outlast the launch, as two kernels: the first leaves one bit per (pair, vector), the kernel of 0 then only refines.  Taken for B > 1 and
  *             at least "split_min_pairs" (an option; default 32; from D = 960 on at most 8) pairs per list on average,
  *             otherwise as 0.  Same results.  The survivor bits and the work-item descriptors live in buffers the handle
  *             grows on demand (rabitq_search and rabitq_scan may allocate when a larger batch arrives;
  *             rabitq_search_noalloc never does and takes this form only if the buffers are already large enough).
  *             3 (default): the faster in measurements: 4 where it is taken (see above; from D = 960 on only where there are at least
- *             512 groups of 16 pairs), else 1 for D >= 960 and 0 below.
+ *             "group_min" groups), else 1 for D >= 960 and 0 below.
  *             2: the lookup-table scheme of Section 3.4.1(1) instead of the quantised query:
  *             <x_b, q'> is the fp32 sum, in ascending block order, of one binary16 table entry per
  *             4 dimensions (tables in LDS, 4 queries per wavefront).  Used by the threshold
  *             seeding and the scan; its estimates differ from those of 0/1 by the query
  *             quantisation error.
+ *   "group_min" n: groups of 16 pairs from which scan_impl 3 and 4 scan by groups in one kernel; -1 (default): 3072 up to 256
+ *             dimensions; from 960 on 512 for scan_impl 3 and 0 for 4.
  * Errors: RABITQ_EINVAL for an unknown name or value. */
 int rabitq_set_option(rabitq_index_t index, const char* name, int64_t value);
 

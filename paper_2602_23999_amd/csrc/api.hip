@@ -417,6 +417,7 @@ int rabitq_set_option(rabitq_index_t ix, const char* name, int64_t value) {
   if (!std::strcmp(name, "prune") && (value == 0 || value == 1)) { ix->prune = (int)value; return RABITQ_OK; }
   if (!std::strcmp(name, "scan_impl") && value >= 0 && value <= 4) { ix->scan_impl = (int)value; return RABITQ_OK; }
   if (!std::strcmp(name, "split_min_pairs") && value >= 0 && value <= 0x7fffffff) { ix->split_min_pairs = (int)value; return RABITQ_OK; }
+  if (!std::strcmp(name, "group_min") && value >= -1 && value <= 0x7fffffff) { ix->group_min = (int)value; return RABITQ_OK; }
   if (!std::strcmp(name, "overlap") && (value == 0 || value == 1)) { ix->overlap = (int)value; return RABITQ_OK; }
   if (!std::strcmp(name, "max_batch") && value >= 0 && value <= 0x7fffffff) { ix->max_batch = value; return RABITQ_OK; }
   if (!std::strcmp(name, "small_batch") && (value == 0 || value == 1)) { ix->small_batch = (int)value; return RABITQ_OK; }

@@ -78,6 +78,7 @@ struct rabitq_index {
   int last_scan_group = 0;   // ... by the group scan, as one kernel
   int last_scan_stream = 0;  // ... was the prefetching variant of the popcount kernel (one pair per work item)
   int split_min_pairs = 32;  // pairs per list, on average, from which scan_impl 3 / 4 split the search
+  int group_min = -1;        // groups of 16 pairs from which they do it as one kernel; -1: chosen by code width (group_min_of)
   uint64_t* surv_mask = nullptr;
   int64_t surv_mask_blocks = 0;
   rq::ItemDesc* item_desc = nullptr;  // descriptors of work items (split search, group scan, streaming scan), grown on demand
@@ -209,15 +210,18 @@ inline bool split_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
 // 3072 share the rest.  From D = 960 on it takes the place of the four-wavefront matrix-core kernel from 8 pairs per list on.
 // A wavefront has 16 pairs to itself, so a search of few pairs leaves the chip idle: with less than a wavefront for every place
 // (16 lists, 424 queries x 8: 120 us split, 244 by groups; 31 lists, 1733 x 15: 205 and 323; from 512 groups on with the shorter work
-// items of D >= 960, where 250 took 727 us against 583 and 1000 take 819 against 964) the former kernels keep it.  (split_min_pairs
-// scales both lines, 0 takes it always.)
+// items of D >= 960, where 250 took 727 us against 583 and 1000 take 819 against 964) the former kernels keep it.  (scan_impl 4
+// from D = 960 on takes it at any number of groups: there is no split search of that width.)
+inline int64_t group_min_of(const rabitq_index* ix) {
+  if (ix->group_min >= 0) return ix->group_min;
+  return ix->W < 30 ? 3072 : (ix->scan_impl == 4 ? 0 : 512);
+}
 inline bool group_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
   if (!split_built(ix) || (ix->scan_impl != 3 && ix->scan_impl != 4)) return false;
   const int64_t pairs = nq * nprobe;
-  const int64_t least = ix->split_min_pairs < 32 ? ix->split_min_pairs : 32;
-  // (scan_impl 4 takes it at any number of groups: there is no split search of that width)
-  if (ix->W >= 30) return pairs >= (least < 8 ? least : 8) * ix->nlist && (ix->scan_impl == 4 || pairs >= QM * 16 * least);
-  if (ix->W > 8 || pairs < (int64_t)ix->split_min_pairs * ix->nlist || pairs < QM * 96 * least) return false;
+  if (pairs < QM * group_min_of(ix)) return false;
+  if (ix->W >= 30) return pairs >= (int64_t)(ix->split_min_pairs < 8 ? ix->split_min_pairs : 8) * ix->nlist;
+  if (ix->W > 8 || pairs < (int64_t)ix->split_min_pairs * ix->nlist) return false;
   const int64_t share = (pairs / QM + ix->nlist) * (ix->n_tiles / (ix->nlist > 0 ? ix->nlist : 1) + 1) / 3072;
   return ix->max_tiles <= (share > 32 ? 2 * share : 64);
 }

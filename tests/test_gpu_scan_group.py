@@ -16,7 +16,8 @@ CASES = [
     (64, 3, 7, 3_000, 90, 7, 1, "l2"),         # every list probed: 90 pairs a list, the last group of 10
     (96, 4, 3, 200, 100, 1, 100, "l2"),        # lists below k, some of less than a tile; 4-bit fields
     (96, 8, 16, 9_000, 257, 4, 128, "ip"),     # flipped bytes; regions cut at k = 128
-    (128, 4, 9, 20_000, 64, 5, 64, "l2"),      # lists of 30 tiles and more
+    (128, 4, 1, 4_096, 64, 1, 64, "l2"),       # a list of 64 tiles, the longest that a few groups take
+    (128, 4, 4, 7_000, 64, 4, 64, "l2"),       # lists of 27 tiles and more
     (128, 5, 1, 1_000, 17, 1, 10, "l2"),       # one list, a group of one pair beside a full one
     (256, 7, 6, 2_500, 130, 2, 33, "l2"),      # the widest of the narrow form
     (960, 5, 4, 1_500, 40, 3, 10, "l2"),       # the wide form, lists in segments
@@ -37,6 +38,7 @@ def test_group_scan_finds_what_the_single_kernels_find(D, bits, nlist, n, nq, np
     gi = rabitq.Index.build(torch.from_numpy(X).cuda(), nlist, bits, build.random_rotation(D, 7), metric=metric, kmeans_iters=2)
     q = torch.from_numpy(Q).cuda()
     gi.set_option("split_min_pairs", 0)   # by groups however few the pairs
+    gi.set_option("group_min", 0)
     for prune in (1, 0):
         gi.set_option("prune", prune)
         gi.set_option("scan_impl", 0)
@@ -44,6 +46,6 @@ def test_group_scan_finds_what_the_single_kernels_find(D, bits, nlist, n, nq, np
         assert gi.index_info("last_scan_split") == 0
         gi.set_option("scan_impl", 4)
         got_i, got_d = gi.search(q, k, nprobe)
-        assert gi.index_info("last_scan_split") == 1
+        assert gi.index_info("last_scan_split") == 1 and gi.index_info("last_scan_group") == 1
         assert torch.equal(got_d, want_d) and torch.equal(got_i, want_i)
     gi.close()

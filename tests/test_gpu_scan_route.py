@@ -29,7 +29,7 @@ def check(D, bits, nlist, nq, nprobe, options, want, k=5):
     try:
         gi.set_option("scan_impl", 0)
         ref_i, ref_d = gi.search(q, k, nprobe)
-        for name, value in options:
+        for name, value in [("scan_impl", 3), *options]:
             gi.set_option(name, value)
         ids, d = gi.search(q, k, nprobe)
         assert (gi.index_info("last_scan_split"), gi.index_info("last_scan_group")) == want
@@ -37,6 +37,7 @@ def check(D, bits, nlist, nq, nprobe, options, want, k=5):
     finally:
         gi.set_option("scan_impl", 3)
         gi.set_option("split_min_pairs", 32)
+        gi.set_option("group_min", -1)
 
 
 @pytest.mark.parametrize("D,nq,nprobe,options,want", [
@@ -44,8 +45,39 @@ def check(D, bits, nlist, nq, nprobe, options, want, k=5):
     (960, 1, 8, [("scan_impl", 4), ("split_min_pairs", 1)], GROUP),     # one pair a list
     (960, 24, 4, [("scan_impl", 4)], GROUP),                            # 12 pairs a list, at least 8 asked for
     (960, 15, 4, [("scan_impl", 4)], SINGLE),                           # 7.5
-    (1024, 1023, 8, [("scan_impl", 3)], SINGLE),                        # chosen by itself from 512 groups of 16 pairs on
-    (1024, 1024, 8, [("scan_impl", 3)], GROUP),
+    (1024, 1023, 8, [], SINGLE),                                        # chosen by itself from 512 groups of 16 pairs on
+    (1024, 1024, 8, [], GROUP),
 ])
 def test_wide_codes_go_by_groups(D, nq, nprobe, options, want):
     check(D, 4, 8, nq, nprobe, options, want)
+
+
+@pytest.mark.parametrize("D,nq,nprobe,options,want", [
+    (64, 8191, 6, [], SPLIT),                                           # 49 146 pairs: 3071.6 groups
+    (64, 8192, 6, [], GROUP),
+    (256, 8192, 6, [("scan_impl", 4)], GROUP),
+    (64, 8192, 6, [("split_min_pairs", 6145)], SINGLE),                 # 6144 pairs a list
+    (64, 100, 3, [("scan_impl", 4), ("split_min_pairs", 0)], SPLIT),    # few pairs a list ask for no fewer groups
+    (64, 100, 3, [("scan_impl", 4), ("group_min", 0)], GROUP),          # 37 pairs a list
+    (64, 100, 3, [("scan_impl", 4), ("group_min", 19)], SPLIT),
+    (512, 100, 3, [("scan_impl", 4), ("group_min", 0)], SPLIT),         # not built for that width
+    (960, 100, 3, [("group_min", 0)], GROUP),
+    (960, 100, 3, [("scan_impl", 4), ("group_min", 19)], SINGLE),
+])
+def test_groups_from_group_min_on(D, nq, nprobe, options, want):
+    check(D, 4, 8, nq, nprobe, options, want)
+
+
+@pytest.mark.parametrize("n,want", [(64 * 64, GROUP), (64 * 64 + 1, SPLIT)])
+def test_a_list_too_long_for_one_wavefront_is_split(n, want):
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, 64)).astype(np.float32)
+    gi = rabitq.Index.build(torch.from_numpy(X).cuda(), 1, 4, build.random_rotation(64, 7), kmeans_iters=1)
+    q = torch.from_numpy(X[:50] + 0.1).cuda()
+    gi.set_option("group_min", 0)
+    ids, d = gi.search(q, 9, 1)
+    assert (gi.index_info("last_scan_split"), gi.index_info("last_scan_group")) == want
+    gi.set_option("scan_impl", 0)
+    ref_i, ref_d = gi.search(q, 9, 1)
+    assert torch.equal(ids, ref_i) and torch.equal(d, ref_d)
+    gi.close()
