@@ -35,11 +35,13 @@ __device__ __forceinline__ void estimate_body(const ScanArgs& a) {
   uint16_t* blocks = reinterpret_cast<uint16_t*>(a.surv_mask + ((int64_t)a.mask_off[c] + (int64_t)grp * (tc1 - t0)) * 16);
 
   __shared__ __align__(16) int8_t scratch[ESTIMATE_SCRATCH];
+  __shared__ float4 table[QM];
   TileEstimator<W, DBG> est;
   if (ts < te) est.fetch(a, ts, lj, g);  // (before the pairs, so that the two waits overlap)
   const int pp = a.pair_ids[pbeg + min(lj, np - 1)];
   float G, dl;
-  est.pairs(a, pp, pair_query(a, pp), np, scratch, lane, G, dl);
+  est.pairs(a, pp, pair_query(a, pp), np, scratch, table, lane, G, dl);
+  wave_sync();
   for (int tile = ts; tile < te; ++tile) {
     const uint32_t alive = est.scan(a, min(tile + 1, te - 1), lj, g, [&](int pair, int v, int I) {  // (past the end: a harmless re-read)
       if (pair < np) a.dbg_ip[a.dbg_off[pbeg + pair] + (int64_t)(tile - t0) * TILE + v] = I;

@@ -34,7 +34,8 @@ __device__ __forceinline__ void scan_group_item(const ScanArgs& a, const int ite
   extern __shared__ __align__(16) unsigned char smem_raw[];
   constexpr int NQ = D / 4;                                                       // dwords of a digit row
   float4* scal = reinterpret_cast<float4*>(smem_raw);                             // [QM] G, cB * sum(q'), unit of the digits, pair
-  uint64_t* s_kth = reinterpret_cast<uint64_t*>(scal + QM);                       // [QM] only keys up to this one count
+  float4* est_pair = scal + QM;                                                   // [QM] TileEstimator's
+  uint64_t* s_kth = reinterpret_cast<uint64_t*>(est_pair + QM);                     // [QM] only keys up to this one count
   uint32_t* lists = reinterpret_cast<uint32_t*>(s_kth + QM);                      // [GLISTS][GLIST_CAP]
   uint32_t* qdig = lists + GLISTS * GLIST_CAP;                                    // [QM * 4][NQ] (NARROW)
   uint64_t* pools = reinterpret_cast<uint64_t*>(qdig);                            // [QM][pool] (wide codes)
@@ -53,7 +54,7 @@ __device__ __forceinline__ void scan_group_item(const ScanArgs& a, const int ite
   const int pp = a.pair_ids[pbeg + min(lj, np - 1)];
   const int q = pair_query(a, pp);
   float G, dl;
-  est.pairs(a, pp, q, np, reinterpret_cast<int8_t*>(lists), lane, G, dl);
+  est.pairs(a, pp, q, np, reinterpret_cast<int8_t*>(lists), est_pair, lane, G, dl);
   if (lane < QM) scal[lane] = make_float4(G, a.cB * a.sum_q[q], digit_unit(dl), __int_as_float(pp));
 
   // The digits: row 4 j + d is digit d of query j, and piece c (four dwords) of row x is kept at place c ^ (x % 8) % pieces.
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(W <= 4 ? 4 :
 }
 
 static size_t group_smem(int W, int pool) {
-  return QM * (sizeof(float4) + sizeof(uint64_t)) + GLISTS * GLIST_CAP * sizeof(uint32_t) +
+  return QM * (2 * sizeof(float4) + sizeof(uint64_t)) + GLISTS * GLIST_CAP * sizeof(uint32_t) +
          (group_narrow(W) ? (size_t)QM * 4 * 8 * W * sizeof(uint32_t) : (size_t)QM * pool * sizeof(uint64_t));
 }
 
