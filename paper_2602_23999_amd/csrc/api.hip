@@ -662,7 +662,7 @@ static int search_batch_body(rabitq_index* ix, Workspace& w, const float* querie
   while (cap < k + TILE) cap <<= 1;
   const int n_t = (ix->nlist + 31) / 32;
   const bool by_minima = !small && select_by_minima(ix->nlist, nprobe) && n_t <= 2 * (int64_t)nprobe * cap;
-  float* tmin = by_minima ? reinterpret_cast<float*>(w.cand_keys) : nullptr;
+  uint32_t* tmin = by_minima ? reinterpret_cast<uint32_t*>(w.cand_keys) : nullptr;
   const PrepClear clear = small || early_clear ? PrepClear{} : prep_clear(nq, ix->nlist, nprobe, w.list_scratch, w.cand_cnt);
   const bool cleared = early_clear || clear.n_bitmap > 0;
   if (small) {

@@ -12,35 +12,42 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int BK = 16;
 
 template <int CTRL>
-__device__ inline float dpp_move(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+__device__ inline uint32_t dpp_move(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
 
-// The smallest value of each accumulator row: 16 registers over the 32 lanes of a half wavefront.  Every step but the last halves the
-// registers: of two rows a lane keeps the one that its bit of the lane number names, so 16 + 8 + 4 + 2 + 1 steps stand for 5 x 16.
-// The lanes of a half with bit 2 clear hold the sixteen rows, each its own *row.  (Lanes in a row of 16 without a source get 0, but
-// those are lanes with bit 2 set.)
-__device__ __forceinline__ float least_of_rows(floatx16 v, int lane, int* row) {
-  float a[8];
+// Order-preserving bits (f2ord) in two instructions.
+__device__ __forceinline__ uint32_t ordered(float v) {
+  const uint32_t u = __float_as_uint(v);
+  return u ^ ((uint32_t)((int)u >> 31) | 0x80000000u);
+}
+
+// The smallest of the words of each accumulator row: 16 registers over the 32 lanes of a half wavefront.  Every step but the last
+// halves the registers: of two rows a lane keeps the one that its bit of the lane number names, so 16 + 8 + 4 + 2 + 1 steps
+// stand for 5 x 16.  The lanes of a half with bit 2 clear hold the sixteen rows, each its own *row.  (Lanes in a row of 16 without a
+// source get 0, but those are lanes with bit 2 set.)
+template <class Word>
+__device__ __forceinline__ uint32_t least_of_rows(int lane, int* row, Word&& word) {
+  uint32_t a[8];
 #pragma unroll
   for (int r = 0; r < 8; ++r) {  // bit 4
-    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[r]), __float_as_uint(v[r + 8]), false, false);
-    a[r] = fminf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    const auto p = __builtin_amdgcn_permlane16_swap(word(r), word(r + 8), false, false);
+    a[r] = min(p[0], p[1]);
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {  // bit 0: quad_perm [1,0,3,2]
-    const float keep = (lane & 1) ? a[r + 4] : a[r], give = (lane & 1) ? a[r] : a[r + 4];
-    a[r] = fminf(keep, dpp_move<0xB1>(give));
+    const uint32_t keep = (lane & 1) ? a[r + 4] : a[r], give = (lane & 1) ? a[r] : a[r + 4];
+    a[r] = min(keep, dpp_move<0xB1>(give));
   }
 #pragma unroll
   for (int r = 0; r < 2; ++r) {  // bit 1: quad_perm [2,3,0,1]
-    const float keep = (lane & 2) ? a[r + 2] : a[r], give = (lane & 2) ? a[r] : a[r + 2];
-    a[r] = fminf(keep, dpp_move<0x4E>(give));
+    const uint32_t keep = (lane & 2) ? a[r + 2] : a[r], give = (lane & 2) ? a[r] : a[r + 2];
+    a[r] = min(keep, dpp_move<0x4E>(give));
   }
-  const float keep = (lane & 8) ? a[1] : a[0], give = (lane & 8) ? a[0] : a[1];  // bit 3: row_ror:8
-  const float t = fminf(keep, dpp_move<0x128>(give));
+  const uint32_t keep = (lane & 8) ? a[1] : a[0], give = (lane & 8) ? a[0] : a[1];  // bit 3: row_ror:8
+  const uint32_t t = min(keep, dpp_move<0x128>(give));
   *row = ((lane >> 4) & 1) * 8 + (lane & 1) * 4 + ((lane >> 1) & 1) * 2 + ((lane >> 3) & 1);
-  return fminf(t, dpp_move<0x104>(t));  // bit 2: row_shl:4
+  return min(t, dpp_move<0x104>(t));  // bit 2: row_shl:4
 }
 
 // The same over keys of a value and its column (make_key), whose minimum is the smallest value's lowest column.
@@ -58,7 +65,7 @@ __device__ __forceinline__ RowKey dpp_key(RowKey k) {
 }
 __device__ __forceinline__ RowKey either(bool c, RowKey a, RowKey b) { return RowKey{c ? a.ord : b.ord, c ? a.col : b.col}; }
 
-template <int TN, class Key>
+template <class Key>
 __device__ __forceinline__ RowKey least_key_of_rows(int lane, int* row, Key&& key) {
   RowKey a[8];
 #pragma unroll
@@ -87,7 +94,7 @@ template <int MODE, int TM, int TN>
 __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                    float* __restrict__ C, int64_t M, int N, int K,
                                                    const float* __restrict__ rowv, const float* __restrict__ colv,
-                                                   float* __restrict__ tmin) {
+                                                   uint32_t* __restrict__ tmin) {
   constexpr int BM = 64 * TM, BN = 64 * TN;
   constexpr int AF = 4 * TM, BF = 4 * TN;  // floats of the A / B tile each thread moves per k-step
   __shared__ float As[2][BK][BM];  // k-major so that the 32 lanes of an MFMA operand read consecutive words
@@ -170,7 +177,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, 
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       int r;
-      const RowKey best = least_key_of_rows<TN>(lane, &r, [&](int reg) {
+      const RowKey best = least_key_of_rows(lane, &r, [&](int reg) {
         RowKey k{0xffffffffu, 0xffffffffu};
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
@@ -205,14 +212,17 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, 
           if (MODE == 1 || MODE == 2) __builtin_nontemporal_store(v, &C[m * (int64_t)N + n]);  // coarse scores: read once, by the selection
           else C[m * (int64_t)N + n] = v;
         }
-        if (MODE == 1 || MODE == 2) acc[i][j][r] = n < N ? v : INFINITY;
+        if (MODE == 1 || MODE == 2) acc[i][j][r] = v;
       }
     }
     if ((MODE == 1 || MODE == 2) && tmin != nullptr) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
+        // (as ordered bits, absent columns as the largest: the order that the selection takes the scores in, whatever a score
+        // that is not a number looks like)
+        const bool there = n0 + wn * 32 * TN + 32 * j + (lane & 31) < N;
         int r;
-        const float least = least_of_rows(acc[i][j], lane, &r);
+        const uint32_t least = least_of_rows(lane, &r, [&](int reg) { return there ? ordered(acc[i][j][reg]) : 0xffffffffu; });
         const int64_t m = m0 + wm * 32 * TM + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
         const int t = (n0 + wn * 32 * TN + 32 * j) / 32;
         if ((lane & 4) == 0 && m < M && 32 * t < N) tmin[m * ((N + 31) / 32) + t] = least;
@@ -376,7 +386,7 @@ int launch_small_front(const rabitq_index* ix, const float* queries, int64_t nq,
 
 template <int TM, int TN>
 static int launch_gemm_tile(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* rowv,
-                            const float* colv, float* tmin, hipStream_t st) {
+                            const float* colv, uint32_t* tmin, hipStream_t st) {
   constexpr int BM = 64 * TM, BN = 64 * TN;
   if ((M + BM - 1) / BM > 0x7fffffff || (N + BN - 1) / BN > 65535) {
     set_error("gemm: matrix too large");
@@ -396,7 +406,7 @@ static int launch_gemm_tile(const float* A, const float* B, float* C, int64_t M,
 }
 
 int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* rowv,
-                const float* colv, float* tmin, hipStream_t st) {
+                const float* colv, uint32_t* tmin, hipStream_t st) {
   if (M <= 0) return RABITQ_OK;
   if (K % BK != 0 || N <= 0) {
     set_error("gemm: K must be a multiple of 16 and N positive");

@@ -137,9 +137,9 @@ __host__ __device__ inline float ord2f(uint32_t o) {
 // C[M,N] = A[M,K] * B[K,N], row-major fp32.  mode 0: plain.  mode 1 (L2 coarse):
 // C = rowv[m] + colv[n] - 2*acc.  mode 2 (IP coarse): C = -acc.  (launch_gemm_nearest, the assignment: colv[n] - 2*acc.)
 // mode 4 (rotation of a centred index): C = acc - colv[n].
-// tmin: null, or (modes 1 and 2) receives the smallest entry of every 32 columns, [M][ceil(N / 32)]
+// tmin: null, or (modes 1 and 2) receives the smallest entry of every 32 columns as f2ord, [M][ceil(N / 32)]
 int launch_gemm(const float* A, const float* B, float* C, int64_t M, int N, int K, int mode, const float* rowv,
-                const float* colv, float* tmin, hipStream_t st);
+                const float* colv, uint32_t* tmin, hipStream_t st);
 int launch_gemm_nearest(const float* A, const float* B, uint64_t* keys, int64_t M, int N, int K, const float* colv, int* parts,
                         hipStream_t st);
 // small batches: Q' = (Q - mean) P, the queries' representation and the coarse scores [nq][nlist] from one launch,
@@ -159,9 +159,9 @@ struct PrepClear {  // memory that the preparation of a batch sets to zero on th
 PrepClear prep_clear(int64_t nq, int nlist, int nprobe, uint32_t* bitmap, int32_t* counters);
 int launch_query_prep(const float* q_rot, int64_t nq, int D, int F, const rabitq_query_repr& out, int form, const PrepClear& clear,
                       hipStream_t st);
-// tmin: the smallest score of every 32 lists (launch_gemm), or null
+// tmin: the smallest score of every 32 lists as f2ord (launch_gemm), or null
 bool select_by_minima(int nlist, int nprobe);  // is it worth having
-int launch_select_probes(const float* scores, const float* tmin, const float* sq_norm, const float* centroid_sq, int64_t nq, int nlist,
+int launch_select_probes(const float* scores, const uint32_t* tmin, const float* sq_norm, const float* centroid_sq, int64_t nq, int nlist,
                          int nprobe, int metric, int32_t* probe_ids, float* probe_G, float* probe_E, hipStream_t st);
 int probe_select_variant(int nlist, int nprobe);  // which selection kernel launch_select_probes takes (see stages.hip)
 int64_t probe_list_scratch_words(int32_t nlist, int64_t nq);

@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256) void select_probes_stream_kernel(const float* 
 // second selection inserted one score after another into a sorted list; 6000 queries, 4096 lists, 8 probes: 42 -> 9.5.  The
 // minima cost the GEMM that writes them nothing that shows: 212 us and 169 against 212 and 175.)
 template <int RT, int RS>
-__global__ __launch_bounds__(256) void select_probes_tiles_kernel(const float* __restrict__ scores, const float* __restrict__ tmin,
+__global__ __launch_bounds__(256) void select_probes_tiles_kernel(const float* __restrict__ scores, const uint32_t* __restrict__ tmin,
                                                                  const float* __restrict__ sq_norm,
                                                                  const float* __restrict__ centroid_sq, int64_t nq,
                                                                  int nlist, int nprobe, int metric,
@@ -167,11 +167,11 @@ __global__ __launch_bounds__(256) void select_probes_tiles_kernel(const float* _
     float v[RT];
     uint32_t ord[RT];
 #pragma unroll
-    for (int r = 0; r < RT; ++r) v[r] = tmin[q * n_t + min(r * 64 + lane, n_t - 1)];
+    for (int r = 0; r < RT; ++r) v[r] = __uint_as_float(tmin[q * n_t + min(r * 64 + lane, n_t - 1)]);
 #pragma unroll
     for (int r = 0; r < RT; ++r) v[r] = pinned(v[r]);
 #pragma unroll
-    for (int r = 0; r < RT; ++r) ord[r] = r * 64 + lane < n_t ? min(f2ord(v[r]), 0xfffffffeu) : 0xffffffffu;
+    for (int r = 0; r < RT; ++r) ord[r] = r * 64 + lane < n_t ? min(__float_as_uint(v[r]), 0xfffffffeu) : 0xffffffffu;
     const uint32_t bound = wave_kth_ord<RT>(ord, (uint32_t)nprobe, &n_le);
     wave_put_smallest<RT>(ord, bound, n_le, (uint32_t)nprobe, lane, [&](int at, int r) { sel[at] = (uint64_t)(r * 64 + lane); });
   }
@@ -230,7 +230,7 @@ int probe_select_variant(int nlist, int nprobe) {
   return 4;
 }
 
-int launch_select_probes(const float* scores, const float* tmin, const float* sq_norm, const float* centroid_sq, int64_t nq, int nlist,
+int launch_select_probes(const float* scores, const uint32_t* tmin, const float* sq_norm, const float* centroid_sq, int64_t nq, int nlist,
                          int nprobe, int metric, int32_t* probe_ids, float* probe_G, float* probe_E, hipStream_t st) {
   if (nq <= 0) return RABITQ_OK;
   const int npad = next_pow2(nprobe);

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from oracle import build
+from paper_2602_23999_amd import rabitq
 
 from gpu_helpers import upload
 
@@ -48,9 +49,35 @@ def test_minima_select_what_whole_rows_select(nlist, nprobe, nq, metric):
     ids = ids.cpu().numpy()
     off = ix["offsets"]
     for i in range(nq):
-        if i in (1, 2):
+        if i in (1, 2):             # no estimate, no neighbour: see the next test
             continue
         want = {int(v) for c in lists[i] for v in ix["ids"][off[c]:off[c + 1]]}
         got = {int(v) for v in ids[i] if v >= 0}
         assert got <= want and len(got) == min(nprobe, len(want)), (i, sorted(got ^ want))
+    gi.close()
+
+
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("nlist,nprobe", [(1000, 7), (1056, 1), (4100, 32)])
+def test_scores_that_are_no_numbers_rank_as_in_whole_rows(nlist, nprobe, metric):
+    # lists whose centroid is not a number, infinite or out of range, queries likewise; batches of 50 select from whole rows
+    D, n = 64, 3 * nlist
+    rng = np.random.default_rng(nlist)
+    X = rng.standard_normal((n, D)).astype(np.float32)
+    first = np.arange(nlist) * n // nlist          # (without a training pass these rows are the centroids)
+    X[first[5::9], 3] = np.nan
+    X[first[7::40]] = 1e30
+    X[first[-2:]] = np.inf
+    gi = rabitq.Index.build(torch.from_numpy(X).cuda(), nlist, 1, build.random_rotation(D, 7), metric=metric, kmeans_iters=0, center=False)
+    Q = (X[rng.integers(0, n, 200)] + 0.1 * rng.standard_normal((200, D))).astype(np.float32)
+    Q[:8] = 0.0
+    Q[0, :2] = 3e38
+    Q[1] = np.nan
+    Q[2] = 1e37 * rng.standard_normal(D)
+    Q[3, 4] = -np.inf
+    q = torch.from_numpy(Q).cuda()
+    got = gi.search(q, 20, nprobe)
+    want = [torch.cat(t) for t in zip(*[gi.search(q[i:i + 50].contiguous(), 20, nprobe) for i in range(0, 200, 50)])]
+    assert torch.equal(got[0], want[0])
+    assert bool(((got[1] == want[1]) | (got[1].isnan() & want[1].isnan())).all())
     gi.close()
