@@ -81,3 +81,35 @@ def test_a_list_too_long_for_one_wavefront_is_split(n, want):
     ref_i, ref_d = gi.search(q, 9, 1)
     assert torch.equal(ids, ref_i) and torch.equal(d, ref_d)
     gi.close()
+
+
+@pytest.mark.parametrize("k", [5, 100])
+def test_a_search_by_groups_makes_room_for_smaller_ones_that_are_split(k):
+    D, nlist = 64, 8
+    rng = np.random.default_rng(3)
+    X = rng.standard_normal((40 * nlist, D)).astype(np.float32)
+    q = torch.from_numpy(rng.standard_normal((12_288, D)).astype(np.float32)).cuda()
+    route = lambda gi: (gi.index_info("last_scan_split"), gi.index_info("last_scan_group"))  # noqa: E731
+    make = lambda: rabitq.Index.build(torch.from_numpy(X).cuda(), nlist, 4, build.random_rotation(D, 7), kmeans_iters=1)  # noqa: E731
+    with_split = make()
+    want_i, want_d = with_split.search(q[:8191], k, 6)
+    assert route(with_split) == SPLIT
+    gi = make()
+    gi.search(q[:8192], k, 6)
+    assert route(gi) == GROUP
+    for nq, nprobe in ((4096, 6), (8191, 6), (6000, 8), (8192, 5)):   # (nothing is allocated there)
+        ids = torch.empty((nq, k), dtype=torch.int64, device="cuda")
+        d = torch.empty((nq, k), dtype=torch.float32, device="cuda")
+        if nq * nprobe * (256 if k > 64 else 128) * 8 > 60 << 20:     # (more than the scratch of that entry point)
+            continue
+        gi.search_noalloc(q[:nq], k, nprobe, ids, d)
+        assert route(gi) == SPLIT, (nq, nprobe)
+        if nprobe == 6:
+            assert torch.equal(ids, want_i[:nq]) and torch.equal(d, want_d[:nq])
+    last = make()
+    last.set_option("max_batch", 8192)
+    ids, d = last.search(q, k, 6)         # 8192 queries by groups, then 4096
+    assert route(last) == SPLIT
+    assert torch.equal(ids[:8191], want_i) and torch.equal(d[:8191], want_d)
+    for ix in (with_split, gi, last):
+        ix.close()
