@@ -460,7 +460,7 @@ __host__ __device__ inline int qhat_mfma_pos(int d) {
 }
 
 // The same digit in the group scan's operand, an 8-bit float (e4m3) of qhat times the 2, 1, 0.5 or 2 that undoes the 0.5, 1,
-// 2 or 0.5 a sign bit in place s of a nibble stands for, and its byte (codes of up to 128 dimensions).
+// 2 or 0.5 a sign bit in place s of a nibble stands for, and its byte.
 __device__ inline uint32_t qhat_fp8(int qh, int s) {
   const uint32_t m = (uint32_t)abs(qh);
   const uint32_t lo = s == 1 ? 0x44403800u : (s == 2 ? 0x3c383000u : 0x4c484000u);  // for |qhat| = 0..3

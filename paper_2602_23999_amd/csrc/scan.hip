@@ -443,7 +443,7 @@ __global__ __launch_bounds__(256) void small_select_seed_kernel(ScanArgs a, Smal
 // QW pairs of the same cluster.  Lane l owns vector l of the current 64-vector tile; its
 // code words stay in registers while the plane words of the QW queries come through the
 // scalar cache.  Survivors of the filter are appended to a list in LDS; a full list (and
-// the list left at the end) is refined NS candidates per round, G lanes per candidate, and
+// the list left at the end) is refined NS = 16 candidates per round on the matrix cores, and
 // the refined keys go to a per-query pool in LDS.  A pool that fills up is cut back to its
 // k best (exact: it only compares final keys) and its k-th key then rejects later keys.
 // Output: the surviving keys of each pair, unsorted, at most `pool` = next_pow2(k + 64) of them.
@@ -1301,7 +1301,8 @@ static void launch_scan_mfma_wf(const ScanArgs& a, unsigned grid, bool dbg, hipS
 
 template <int W, int F, int M>
 static void launch_scan_wf(const ScanArgs& a, unsigned grid, bool dbg, hipStream_t st) {
-  const bool masked = M == 0 && F > 0 && a.surv_mask != nullptr;  // second half of the split search
+  constexpr bool SPLIT = M == 0 && F > 0 && W < 30;  // (from 960 dimensions on no search is split)
+  const bool masked = SPLIT && a.surv_mask != nullptr;  // second half of the split search
   const bool stream = M == 0 && a.streaming && !masked;
   const int qn = stream ? 1 : QW;  // pairs per work item
   constexpr int FF = F > 0 ? F : 8;
@@ -1309,9 +1310,9 @@ static void launch_scan_wf(const ScanArgs& a, unsigned grid, bool dbg, hipStream
                       (F > 0 ? ((masked ? LIST_CAP_MASKED : LIST_CAP) + (size_t)qn * RefineShape<FF, W * FF>::LDS_WORDS) * sizeof(uint32_t)
                              : 0) +
                       (M == 1 ? (size_t)qn * W * 256 : 0);
-  if (masked)  // (estimate_mfma_kernel ran)
-    hipLaunchKernelGGL((scan_kernel<W, F, false, M, 0, (M == 0 && F > 0)>), dim3(grid), dim3(64), smem, st, a);
-  else if (stream && F == 0 && dbg)
+  if (masked) {  // (estimate_mfma_kernel ran)
+    if constexpr (SPLIT) hipLaunchKernelGGL((scan_kernel<W, F, false, M, 0, true>), dim3(grid), dim3(64), smem, st, a);
+  } else if (stream && F == 0 && dbg)
     hipLaunchKernelGGL((scan_stream_kernel<W, true>), dim3(grid), dim3(64), smem, st, a);
   else if (stream && F == 0)
     hipLaunchKernelGGL((scan_stream_kernel<W, false>), dim3(grid), dim3(64), smem, st, a);
