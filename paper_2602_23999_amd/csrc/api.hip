@@ -64,7 +64,7 @@ static void free_workspace(Workspace& w) {
 
 static void free_index(rabitq_index* ix) {
   if (!ix) return;
-  dev_free(ix->rotation); dev_free(ix->mean_rot); dev_free(ix->centroids_t); dev_free(ix->centroid_sq); dev_free(ix->tile_off); dev_free(ix->surv_mask); dev_free(ix->item_desc);
+  dev_free(ix->rotation); dev_free(ix->mean_rot); dev_free(ix->centroids_t); dev_free(ix->centroid_sq); dev_free(ix->tile_off); dev_free(ix->surv_mask); dev_free(ix->item_desc); dev_free(ix->stage_queries);
   dev_free(ix->cluster_size); dev_free(ix->cluster_order); dev_free(ix->short_codes); dev_free(ix->short_factors); dev_free(ix->long_codes);
   dev_free(ix->long_factors); dev_free(ix->ids);
   free_workspace(ix->ws);

@@ -873,14 +873,37 @@ __device__ __forceinline__ v4i refine_mfma(const uint32_t (&w)[RefineShape<F, LW
   return acc;
 }
 
+// One of a query's four digit rows.
+struct DigitRow {
+  const uint32_t* row;
+  __device__ __forceinline__ v4i four(int at) const { return *reinterpret_cast<const v4i*>(row + at); }
+  __device__ __forceinline__ uint32_t one(int at) const { return row[at]; }
+};
+// The same, or made from q' where there are no digits: again for every candidate, which a stage entry point only does where it
+// may not allocate the memory for them (launch_scan).
+struct DigitRowOrQuery {
+  const uint32_t* row;  // nullptr: none
+  const float* q_stage;
+  float factor;
+  int digit;
+  __device__ __forceinline__ DigitRowOrQuery(const uint32_t* digits, const float* q, float f, int64_t index, int d, int D)
+      : row(digits != nullptr ? digits + index * D + d * (D / 4) : nullptr), q_stage(q + index * D), factor(f), digit(d) {}
+  __device__ __forceinline__ v4i four(int at) const {
+    if (row != nullptr) return *reinterpret_cast<const v4i*>(row + at);
+    v4i v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = (int)digit_of_quad(q_stage + 4 * (at + i), factor, digit);
+    return v;
+  }
+  __device__ __forceinline__ uint32_t one(int at) const { return row != nullptr ? row[at] : digit_of_quad(q_stage + 4 * at, factor, digit); }
+};
+
 // The same sums with both operands read where they are needed: for kernels that refine little and have better uses for their
-// registers meanwhile (seeding, the matrix-core scans' lists of wide codes), U units of both in flight.  `row`: this lane's candidate; its left row is
-// (q, digit).
-template <int F, int LW, int U = 16>
-__device__ __forceinline__ v4i refine_mfma_from_memory(const uint32_t* __restrict__ row, const uint32_t* digits, const float* q_stage,
-                                              float factor, int64_t q, int digit, int g, uint32_t flip) {
+// registers meanwhile (seeding, the matrix-core scans' lists of wide codes), U units of both in flight.  `row`: this lane's candidate;
+// `query`: its left row (DigitRow, or what else gives four dwords and one).
+template <int F, int LW, int U = 16, typename Query>
+__device__ __forceinline__ v4i refine_mfma_from_memory(const uint32_t* __restrict__ row, const Query query, int g, uint32_t flip) {
   using S = RefineShape<F, LW>;
-  constexpr int NQ = LW * S::QPW;
   v4i acc = v4i{0, 0, 0, 0};
   auto unit = [&](int u) __attribute__((always_inline)) {
     uint32_t w[4];
@@ -894,15 +917,8 @@ __device__ __forceinline__ v4i refine_mfma_from_memory(const uint32_t* __restric
 #pragma unroll
     for (int h = 0; h < S::QPW; ++h) {  // 4 / QPW words per instruction
       const int at = (16 * u + 4 * g) * S::QPW + 4 * h;
-      v4i qa, x;
-      if (digits != nullptr) {
-        qa = *reinterpret_cast<const v4i*>(digits + (q * 4 + digit) * NQ + at);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          qa[i] = (int)digit_of_quad(q_stage + (q * NQ + at + i) * 4, factor, digit);
-        }
-      }
+      const v4i qa = query.four(at);
+      v4i x;
 #pragma unroll
       for (int i = 0; i < 4; ++i) x[i] = (int)refine_field<F>(w[(4 * h + i) / S::QPW], (4 * h + i) % S::QPW, flip);
       acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(qa, x, acc, 0, 0, 0);
@@ -932,7 +948,7 @@ __device__ __forceinline__ v4i refine_mfma_from_memory(const uint32_t* __restric
         const int c = 4 * kc + i;
         const int at = min(16 * S::UNITS + S::RW * g + (c < RD ? c / S::QPW : 0), LW - 1) * S::QPW + c % S::QPW;
         uint32_t v = 0u;
-        if (c < RD) v = digits != nullptr ? digits[(q * 4 + digit) * NQ + at] : digit_of_quad(q_stage + (q * NQ + at) * 4, factor, digit);
+        if (c < RD) v = query.one(at);
         qa[i] = 16 * S::UNITS + S::RW * g + (c < RD ? c / S::QPW : 0) < LW ? (int)v : 0;
         x[i] = c < RD ? (int)refine_field<F>(w[c < RD ? c / S::QPW : 0], c % S::QPW, flip) : 0;
       }

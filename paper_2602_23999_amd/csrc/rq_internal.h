@@ -83,6 +83,8 @@ struct rabitq_index {
   int64_t surv_mask_blocks = 0;
   rq::ItemDesc* item_desc = nullptr;  // descriptors of work items (split search, group scan, streaming scan), grown on demand
   int64_t item_desc_cap = 0;
+  uint32_t* stage_queries = nullptr;  // the queries handed to rabitq_scan in the scans' form, grown on demand (launch_scan)
+  int64_t stage_queries_cap = 0;      // words
   std::vector<int64_t> tiles_prefix;  // [i] = tiles of the i largest lists (host; filled on first use)
   int overlap = 1;  // list building and scan set-up run beside the seeding on `side`
   int64_t max_batch = 0;  // queries per pass of rabitq_search; 0 = from the workspace budget

@@ -49,15 +49,15 @@ __device__ inline void stage_lut(_Float16* dst, const uint16_t* __restrict__ src
 constexpr int SEED_CHUNK_TILES = 32;  // 2048 keys per selection round
 
 // Refined estimate of the vector at `slot` for query q, 16 of them per wavefront: lane (lj, g) names the slot of
-// candidate lj (the same in its four lanes) and gets its estimate.
+// candidate lj (the same in its four lanes) and gets its estimate.  `digits`: the query's.
 template <int W, int F>
-__device__ __forceinline__ float seed_estimate(const ScanArgs& a, int64_t q, int64_t slot, float G, int lj, int g) {
+__device__ __forceinline__ float seed_estimate(const ScanArgs& a, int64_t q, const uint32_t* digits, int64_t slot, float G, int lj, int g) {
   constexpr int FF = (F > 0 ? F : 8), LW = W * FF;
   const float2 lf = *reinterpret_cast<const float2*>(a.long_factors + 2 * slot);
   const float dl = a.delta[q];
   // (one query: its four digits repeat in the 16 rows, so that all four lanes of a candidate get the same sums)
-  const float ip = digit_sum(refine_mfma_from_memory<FF, LW>(a.long_codes + slot * LW, a.q_digits, a.q_stage, digit_factor(dl),
-                                                             q, lj & 3, g, a.flip), digit_unit(dl));
+  const DigitRow query{digits + (lj & 3) * (8 * W)};
+  const float ip = digit_sum(refine_mfma_from_memory<FF, LW>(a.long_codes + slot * LW, query, g, a.flip), digit_unit(dl));
   return G + lf.x + lf.y * (ip - a.cB * a.sum_q[q]);
 }
 
@@ -65,12 +65,14 @@ template <int W, int F>
 __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
   extern __shared__ unsigned char smem_raw[];
   // layout: chunk keys [2048] u64 | best [kpad] u64 | out [kpad] u64 | tables [8W][16] f16
+  // | the query's digits [4][8W] u32, where it comes without
   const int m = max(a.k, SEED_M);
   const int kpad = next_pow2(m);
   uint64_t* chunk = reinterpret_cast<uint64_t*>(smem_raw);
   uint64_t* best = chunk + SEED_CHUNK_TILES * TILE;
   uint64_t* out = best + kpad;
   _Float16* lut_s = reinterpret_cast<_Float16*>(out + kpad);
+  uint32_t* own = reinterpret_cast<uint32_t*>(lut_s + W * 128);
   __shared__ SelectScratch sh;
   __shared__ int s_rank, s_t0, s_t1;
   __shared__ float s_G;
@@ -109,6 +111,7 @@ __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
   }
   for (int i = tid; i < kpad; i += 256) best[i] = KEY_NONE;
   stage_lut(lut_s, a.lut + q * (int64_t)W * 128, W, tid, 256);
+  if (F > 0 && a.q_digits == nullptr && wave == 0) stage_digits<32 * W>(own, 8 * W, nullptr, a.q_stage, digit_factor(a.delta[q]), q, lane);
   __syncthreads();
   const int rank = s_rank;
   if (rank < 0) {
@@ -151,7 +154,8 @@ __global__ __launch_bounds__(256) void seed_kernel(ScanArgs a) {
     const int sidx = base + lj;
     const bool valid = sidx < m && best[min(sidx, kpad - 1)] != KEY_NONE;
     const int64_t slot = (int64_t)t0 * TILE + (valid ? (uint32_t)best[min(sidx, kpad - 1)] : 0u);
-    const float eB = seed_estimate<W, F>(a, q, slot, G, lj, g);
+    const float eB = a.q_digits != nullptr ? seed_estimate<W, F>(a, q, a.q_digits + q * (32 * W), slot, G, lj, g)
+                                           : seed_estimate<W, F>(a, q, own, slot, G, lj, g);
     if (valid && g == 0) out[sidx] = make_key(eB, (uint32_t)sidx);
   }
   __syncthreads();
@@ -181,10 +185,10 @@ struct SeedScratch {
   int cnt[4];
 };
 
-// The work of one query (SPLIT: of the four wavefronts that share it; every one of them must call, and they meet
+// The work of one query with its digits (SPLIT: of the four wavefronts that share it; every one of them must call, and they meet
 // at barriers unless no probed cluster has k vectors, which all four find alike).
 template <int W, int F, bool SPLIT>
-__device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, int wave, SeedScratch& sh) {
+__device__ __forceinline__ void seed_wave_body(const ScanArgs& a, int64_t q, const uint32_t* digits, int lane, int wave, SeedScratch& sh) {
   // Lane j looks at probe j: everything the chosen probe contributes (cluster, coarse term, tile range) is fetched
   // for all probes at once and read from the chosen lane, so the walk to the first tile is two dependent loads deep.
   int rank = -1, t0 = 0, t1 = 0, n_c = 0;
@@ -363,7 +367,7 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
     const int lj = lane & 15, g = lane >> 4, step = SPLIT ? 64 : 16;
     for (int base = SPLIT ? wave * 16 : 0; base < cnt; base += step) {
       const int64_t slot = (int64_t)t0 * TILE + lp[min(base + lj, cnt - 1)];
-      const float eB = seed_estimate<W, F>(a, q, slot, G, lj, g);
+      const float eB = seed_estimate<W, F>(a, q, digits, slot, G, lj, g);
       if (g == 0 && base + lj < cnt) lo[base + lj] = f2ord(eB);
     }
     if (SPLIT) __syncthreads();
@@ -378,9 +382,11 @@ __device__ inline void seed_wave_body(const ScanArgs& a, int64_t q, int lane, in
   if (lane == 0) a.tau_out[q] = F == 0 ? kth : fminf(kth, 3.402823466e+38f);
 }
 
-template <int W, int F, bool SPLIT>
+// STAGED: the queries come without digits (the stage entry point's callers hand in q'), which are made once per query.
+template <int W, int F, bool SPLIT, bool STAGED>
 __global__ __launch_bounds__(256) void seed_wave_kernel(ScanArgs a, int64_t nq) {
   __shared__ SeedScratch s_seed;
+  __shared__ __align__(16) uint32_t s_digits[STAGED ? (SPLIT ? 1 : 4) : 1][STAGED ? 32 * W : 4];
   // (the wavefront index is the same in all lanes: saying so lets everything indexed by the query be fetched
   // through the scalar cache)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -391,7 +397,13 @@ __global__ __launch_bounds__(256) void seed_wave_kernel(ScanArgs a, int64_t nq) 
   const int blk = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
   const int64_t q = SPLIT ? (int64_t)blk : (int64_t)blk * 4 + wave;
   if (q >= nq) return;
-  seed_wave_body<W, F, SPLIT>(a, q, lane, wave, s_seed);
+  if constexpr (STAGED) {  // (the body has a barrier, or a wave_sync, before it reads them)
+    if (!SPLIT || wave == 0)
+      stage_digits<32 * W>(s_digits[SPLIT ? 0 : wave], 8 * W, nullptr, a.q_stage, digit_factor(a.delta[q]), q, lane);
+    seed_wave_body<W, F, SPLIT>(a, q, s_digits[SPLIT ? 0 : wave], lane, wave, s_seed);
+  } else {
+    seed_wave_body<W, F, SPLIT>(a, q, a.q_digits + q * (32 * W), lane, wave, s_seed);
+  }
 }
 
 // ---------------------------------------------------------------------------------
@@ -422,7 +434,7 @@ __global__ __launch_bounds__(256) void small_select_seed_kernel(ScanArgs a, Smal
   }
   __syncthreads();  // the probes are in memory for the other wavefronts of the workgroup
   if (b.do_seed) {
-    seed_wave_body<W, F, true>(a, q, lane, wave, s_seed);
+    seed_wave_body<W, F, true>(a, q, a.q_digits + q * (32 * W), lane, wave, s_seed);
   } else if (tid == 0) {
     a.tau_out[q] = 3.402823466e+38f;
   }
@@ -1116,8 +1128,8 @@ __global__ __launch_bounds__(64 * mfma_waves(W)) void scan_mfma_kernel(ScanArgs 
         const int64_t slot = (int64_t)t0 * TILE + (e & 0x0fffffffu);
         const float2 lf = *reinterpret_cast<const float2*>(a.long_factors + 2 * slot);
         const int id = a.ids[slot];
-        const float ip = digit_sum(refine_mfma_from_memory<FF, LW>(a.long_codes + slot * LW, a.q_digits, a.q_stage, factor_r, qr,
-                                                                   lj & 3, g, a.flip), unit_q);
+        const DigitRowOrQuery query(a.q_digits, a.q_stage, factor_r, qr, lj & 3, 32 * W);
+        const float ip = digit_sum(refine_mfma_from_memory<FF, LW>(a.long_codes + slot * LW, query, g, a.flip), unit_q);
         const float eB = G_q + lf.x + lf.y * (ip - csq_q);
         const uint64_t key = make_key(eB, (uint32_t)id);
         const bool take = idx < list_cnt && (int)(e >> 28) == g && key <= kth;
@@ -1278,13 +1290,15 @@ template <int W, int F>
 static void launch_seed_wf(const ScanArgs& a, int impl, int64_t nq, hipStream_t st) {
   const int kpad = next_pow2(std::max(a.k, SEED_M));
   const size_t smem = (size_t)(SEED_CHUNK_TILES * TILE + 2 * kpad) * sizeof(uint64_t);
+  const bool staged = F > 0 && a.q_digits == nullptr;
   if (impl == 2)
-    hipLaunchKernelGGL((seed_kernel<W, F>), dim3((unsigned)nq), dim3(256), smem + (size_t)W * 256, st, a);
+    hipLaunchKernelGGL((seed_kernel<W, F>), dim3((unsigned)nq), dim3(256), smem + (size_t)W * 256 + (staged ? W * 128 : 0), st, a);
   else if (nq <= 2048)  // few queries: four wavefronts per query
-    hipLaunchKernelGGL((seed_wave_kernel<W, F, true>), dim3((unsigned)((nq + 7) / 8 * 8)), dim3(256), 0, st, a, nq);
+    hipLaunchKernelGGL((staged ? seed_wave_kernel<W, F, true, F != 0> : seed_wave_kernel<W, F, true, false>),
+                       dim3((unsigned)((nq + 7) / 8 * 8)), dim3(256), 0, st, a, nq);
   else
-    hipLaunchKernelGGL((seed_wave_kernel<W, F, false>), dim3((unsigned)(((nq + 3) / 4 + 7) / 8 * 8)), dim3(256), 0, st, a,
-                       nq);
+    hipLaunchKernelGGL((staged ? seed_wave_kernel<W, F, false, F != 0> : seed_wave_kernel<W, F, false, false>),
+                       dim3((unsigned)(((nq + 3) / 4 + 7) / 8 * 8)), dim3(256), 0, st, a, nq);
 }
 
 template <int W, int F>

@@ -331,6 +331,59 @@ static void set_repr(ScanArgs& a, const rabitq_index* ix, const rabitq_query_rep
   a.planes = r.planes; a.delta = r.delta; a.sum_qhat = r.sum_qhat; a.sum_q = r.sum_q; a.lut = r.lut;
 }
 
+// Queries as a stage entry point hands them in -> as the scans read them (QueryForm): digits, four positions of the refinement order
+// per thread, and the group scan's operand.
+__global__ __launch_bounds__(256) void digits_kernel(const float* __restrict__ q_stage, const float* __restrict__ delta, int64_t n, int NQ,
+                                                    uint32_t* __restrict__ digits) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int64_t q = i / NQ;
+  const uint4 d = digit_quad(four_floats(q_stage + 4 * i), digit_factor(delta[q]));
+  uint32_t* out = digits + 4 * NQ * q + (i - q * NQ);
+  out[0] = d.x; out[NQ] = d.y; out[2 * NQ] = d.z; out[3 * NQ] = d.w;
+}
+__global__ __launch_bounds__(256) void fp8_operand_kernel(const int8_t* __restrict__ qhat8, int64_t n, int Dp, int8_t* __restrict__ fp8) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int64_t row = i / Dp * Dp;
+  const int d = (int)(i - row);
+  fp8[row + qhat_fp8_pos(d)] = (int8_t)qhat_fp8(qhat8[row + qhat_mfma_pos(d)], d & 3);
+}
+
+// Scans that read the digits with every candidate (the matrix-core kernel, the group scan of wide codes) would make them from q' again
+// each time, and the group scan the 16 operands of an item, which is long for wide codes: a stage entry point makes them first,
+// in memory that the handle keeps.  (960-d, 5 bits, 1000 queries x 16 lists: 1250 us by groups, 911 with the digits ready and
+// 412 with both; the matrix-core kernel 737 and 468.)  Where the memory cannot be had, as while the stream is captured, the scans take
+// what was handed in.
+static void convert_stage_queries(rabitq_index* ix, const rabitq_query_repr& r, int64_t nq, bool operand, ScanArgs& a, hipStream_t st) {
+  const int64_t digits = nq * ix->dim, bytes = operand ? nq * a.Dp : 0, words = digits + bytes / 4;
+  if (words > ix->stage_queries_cap) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone || hipDeviceSynchronize() != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    if (ix->stage_queries) (void)hipFree(ix->stage_queries);
+    ix->stage_queries = nullptr;
+    ix->stage_queries_cap = 0;
+    if (hipMalloc(reinterpret_cast<void**>(&ix->stage_queries), (size_t)words * sizeof(uint32_t)) != hipSuccess) {
+      (void)hipGetLastError();
+      ix->stage_queries = nullptr;
+      return;
+    }
+    ix->stage_queries_cap = words;
+  }
+  hipLaunchKernelGGL(digits_kernel, dim3((unsigned)((digits / 4 + 255) / 256)), dim3(256), 0, st, r.q_stage, r.delta, digits / 4,
+                     ix->dim / 4, ix->stage_queries);
+  a.q_digits = ix->stage_queries;
+  if (operand) {
+    int8_t* fp8 = reinterpret_cast<int8_t*>(ix->stage_queries + digits);
+    hipLaunchKernelGGL(fp8_operand_kernel, dim3((unsigned)((bytes + 255) / 256)), dim3(256), 0, st, r.qhat8, bytes, a.Dp, fp8);
+    a.qhat8 = fp8;
+    a.qhat_fp8 = true;
+  }
+}
+
 static int need_lut(const rabitq_index* ix, const rabitq_query_repr& r) {
   if (ix->scan_impl == 2 && r.lut == nullptr) {
     set_error("scan_impl 2 needs the lookup tables (rabitq_query_repr.lut)");
@@ -455,6 +508,8 @@ int launch_scan(rabitq_index* ix, const rabitq_query_repr& repr, int form, const
   // buffers are large enough (ensure_split_buffers, called by the entry points that may allocate).
   const ScanRoute route = scan_route(ix, nq, nprobe, k);
   const bool group = route == ROUTE_GROUP, split = route == ROUTE_SPLIT;
+  if (form == 0 && ix->total_bits > 1 && (group ? !group_narrow(ix->W) : !split && impl == 1))
+    convert_stage_queries(ix, repr, nq, group, a, st);
   const ScanPlan plan = route == ROUTE_SINGLE ? scan_plan(ix, nq, nprobe, k) : plan_for(ix, nq, nprobe, k, false, group);
   const int qw = plan.qw;
   a.probe_G = probe_G; a.probe_E = probe_E; a.pair_off = pair_off; a.pair_ids = pair_ids; a.tau = tau;

@@ -179,8 +179,8 @@ __device__ __forceinline__ void scan_group_item(const ScanArgs& a, const int ite
           });
         } else {
           const int j = 4 * list[d] + (lj >> 2);  // the query this lane's left row is of
-          sums = refine_mfma_from_memory<F, LW, 7>(a.long_codes + slot[d] * LW, a.q_digits, a.q_stage, digit_factor(__shfl(dl, j, 64)),
-                                                   __shfl(q, j, 64), lj & 3, g, a.flip);
+          const DigitRowOrQuery query(a.q_digits, a.q_stage, digit_factor(__shfl(dl, j, 64)), __shfl(q, j, 64), lj & 3, D);
+          sums = refine_mfma_from_memory<F, LW, 7>(a.long_codes + slot[d] * LW, query, g, a.flip);
         }
         const float ip = digit_sum(sums, sc.z);
         const float eB = sc.x + lf[d].x + lf[d].y * (ip - sc.y);
