@@ -64,3 +64,28 @@ def test_lists_of_several_segments_on_both_sides_of_a_chunk(nlist):
             assert (gi.index_info("last_scan_split"), gi.index_info("last_scan_stream")) == (split, stream)
             assert torch.equal(ids, want_i[:n]) and torch.equal(d, want_d[:n]), (impl, n, longest)
     gi.close()
+
+
+@pytest.mark.parametrize("D,nlist", [(64, 1), (64, 7), (64, 9), (64, 2047), (64, 2049), (64, 8191), (64, 8193), (64, 16390), (960, 9), (960, 2049)])
+def test_tables_of_the_group_scan_at_the_edges_of_a_chunk(D, nlist):
+    # the item table in the order in which the lists are dealt to the XCDs, and descriptors of 16 pairs: some lists of several tiles, which
+    # the wide form scans in segments of two
+    nprobe, k = min(5, nlist), 3
+    rng = np.random.default_rng(nlist + D)
+    C = rng.standard_normal((nlist, D))
+    long = np.unique([c for c in (0, 6, 7, 8, nlist // 2, 2046, 2047, 2048, 8191, 8192, nlist - 1) if c < nlist])
+    which = np.concatenate([np.repeat(long, rng.integers(150, 400, len(long))), rng.integers(0, nlist, 1000)])
+    X = (C[which] + 0.1 * rng.standard_normal((len(which), D))).astype(np.float32)
+    nq = 333
+    Q = torch.from_numpy((C[rng.choice(long, nq)] + 0.3 * rng.standard_normal((nq, D))).astype(np.float32)).cuda()
+    gi = upload(build.build_index(X, nlist, 4, centroids=C))
+    gi.set_option("scan_segment_tiles", 2)
+    gi.set_option("scan_impl", 0)
+    want_i, want_d = gi.search(Q, k, nprobe)
+    gi.set_option("scan_impl", 4)
+    gi.set_option("split_min_pairs", 0)
+    gi.set_option("group_min", 0)
+    ids, d = gi.search(Q, k, nprobe)
+    assert gi.index_info("last_scan_group") == 1
+    assert torch.equal(ids, want_i) and torch.equal(d, want_d)
+    gi.close()
