@@ -217,8 +217,8 @@ int rabitq_search_noalloc(rabitq_index_t index, const float* queries, int64_t nq
  *             4 dimensions (tables in LDS, 4 queries per wavefront).  Used by the threshold
  *             seeding and the scan; its estimates differ from those of 0/1 by the query
  *             quantisation error.
- *   "group_min" n: groups of 16 pairs from which scan_impl 3 and 4 scan by groups in one kernel; -1 (default): 3072 up to 256
- *             dimensions; from 960 on 512 for scan_impl 3 and 0 for 4.
+ *   "group_min" n: groups of 16 pairs from which scan_impl 3 and 4 scan by groups in one kernel; -1 (default): 4096 up to 256
+ *             dimensions, where a search of 33 to 64 neighbours does not; from 960 on 512 for scan_impl 3 and 0 for 4.
  * Errors: RABITQ_EINVAL for an unknown name or value. */
 int rabitq_set_option(rabitq_index_t index, const char* name, int64_t value);
 

@@ -210,18 +210,24 @@ inline bool split_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
 // ... as one kernel, the group scan (scan_group.hip says why these widths).  For codes of up to 256 dimensions it does not cut
 // lists into segments, so the longest list must not outlast the launch: one wavefront works on it, while the chip's about
 // 3072 share the rest.  From D = 960 on it takes the place of the four-wavefront matrix-core kernel from 8 pairs per list on.
-// A wavefront has 16 pairs to itself, so a search of few pairs leaves the chip idle: with less than a wavefront for every place
-// (16 lists, 424 queries x 8: 120 us split, 244 by groups; 31 lists, 1733 x 15: 205 and 323; from 512 groups on with the shorter work
-// items of D >= 960, where 250 took 727 us against 583 and 1000 take 819 against 964) the former kernels keep it.  (scan_impl 4
-// from D = 960 on takes it at any number of groups: there is no split search of that width.)
-inline int64_t group_min_of(const rabitq_index* ix) {
+// A wavefront has 16 pairs to itself, so a search of few pairs leaves the chip idle: with less than a wavefront for each of its
+// 4096 places (16 lists, 424 queries x 8: 120 us split, 244 by groups; 274 lists, 3438 groups: 282 and 342; 1683 lists, 3873
+// groups: 320 and 374; 639 lists, 4265 groups: 194 and 152; 227 lists, 11836 groups: 209 and 173; from 512 groups on with the
+// shorter work items of D >= 960, where 385 take 1244 us against 1124, 628 take 323 against 356 and 1000 take 837 against 1095)
+// the former kernels keep it.  (scan_impl 4 from D = 960 on takes it at any number of groups: there is no split search of that width.)
+// Up to 256 dimensions a pair's region holds the smallest power of two from k + 64 on and is cut to k when the 64 keys that a
+// round may add do not fit: for k from 33 to 64 after less than 32 new keys, and at 64 after every one, so that the cuts
+// outweigh the rest (11407 groups, k = 53: 580 us split, 1040 by groups; 3083, k = 55: 263 and 397; 24008, k = 50: 564 and 576).
+// The choice by these two lines is the default; a group_min that is set takes its place.
+inline int64_t group_min_of(const rabitq_index* ix, int k) {
   if (ix->group_min >= 0) return ix->group_min;
-  return ix->W < 30 ? 3072 : (ix->scan_impl == 4 ? 0 : 512);
+  if (ix->W < 30) return k > 32 && k <= 64 ? INT64_MAX / QM : 4096;
+  return ix->scan_impl == 4 ? 0 : 512;
 }
-inline bool group_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
+inline bool group_wanted(const rabitq_index* ix, int64_t nq, int nprobe, int k) {
   if (!split_built(ix) || (ix->scan_impl != 3 && ix->scan_impl != 4)) return false;
   const int64_t pairs = nq * nprobe;
-  if (pairs < QM * group_min_of(ix)) return false;
+  if (pairs < QM * group_min_of(ix, k)) return false;
   if (ix->W >= 30) return pairs >= (int64_t)(ix->split_min_pairs < 8 ? ix->split_min_pairs : 8) * ix->nlist;
   if (ix->W > 8 || pairs < (int64_t)ix->split_min_pairs * ix->nlist) return false;
   const int64_t share = (pairs / QM + ix->nlist) * (ix->n_tiles / (ix->nlist > 0 ? ix->nlist : 1) + 1) / 3072;

@@ -164,25 +164,21 @@ static int64_t item_bound(const rabitq_index* ix, int64_t nq, int nprobe, int pe
   return ((m + 7) / 8) * 8;
 }
 
-// tiles of the `count` largest lists
-static int64_t largest_tiles(rabitq_index* ix, int64_t count) {
+int64_t split_mask_blocks(rabitq_index* ix, int64_t nq, int nprobe) {
   if (ix->tiles_prefix.empty()) {
     std::vector<int> t(ix->host_tiles.begin(), ix->host_tiles.end());
     std::sort(t.begin(), t.end(), std::greater<int>());
     ix->tiles_prefix.assign(t.size() + 1, 0);
     for (size_t i = 0; i < t.size(); ++i) ix->tiles_prefix[i + 1] = ix->tiles_prefix[i] + t[i];
   }
-  return ix->tiles_prefix[std::min<size_t>((size_t)count, ix->tiles_prefix.size() - 1)];
-}
-
-int64_t split_mask_blocks(rabitq_index* ix, int64_t nq, int nprobe) {
-  return (nq * largest_tiles(ix, nprobe) + QM - 1) / QM + ix->n_tiles;
+  const size_t top = std::min<size_t>((size_t)nprobe, ix->tiles_prefix.size() - 1);
+  return (nq * ix->tiles_prefix[top] + QM - 1) / QM + ix->n_tiles;
 }
 
 // few pairs per list, popcount kernel, neither split nor by groups: the shape the prefetching variant is for
-static bool stream_shape(const rabitq_index* ix, int64_t nq, int nprobe) {
+static bool stream_shape(const rabitq_index* ix, int64_t nq, int nprobe, int k) {
   return effective_impl(ix) == 0 && nq * nprobe <= 4 * (int64_t)ix->nlist && !split_wanted(ix, nq, nprobe) &&
-         !group_wanted(ix, nq, nprobe);
+         !group_wanted(ix, nq, nprobe, k);
 }
 static ScanPlan plan_for(const rabitq_index* ix, int64_t nq, int nprobe, int k, bool streaming, bool group = false);
 static ScanPlan group_plan(const rabitq_index* ix, int64_t nq, int nprobe, int k) { return plan_for(ix, nq, nprobe, k, false, true); }
@@ -198,7 +194,7 @@ static int64_t stream_desc_slots(const rabitq_index* ix, int64_t nq, int nprobe,
 }
 
 int ensure_stream_buffers(rabitq_index* ix, int64_t nq, int nprobe, int k) {
-  if (!stream_shape(ix, nq, nprobe)) return RABITQ_OK;
+  if (!stream_shape(ix, nq, nprobe, k)) return RABITQ_OK;
   const int64_t slots = stream_desc_slots(ix, nq, nprobe, k);
   if (slots <= ix->item_desc_cap || slots > 0x7fffffff) return RABITQ_OK;
   RQ_HIP(hipDeviceSynchronize());
@@ -212,7 +208,7 @@ int ensure_stream_buffers(rabitq_index* ix, int64_t nq, int nprobe, int k) {
 
 ScanRoute scan_route(rabitq_index* ix, int64_t nq, int nprobe, int k) {
   if (ix->item_desc == nullptr) return ROUTE_SINGLE;
-  if (group_wanted(ix, nq, nprobe)) {
+  if (group_wanted(ix, nq, nprobe, k)) {
     const ScanPlan plan = group_plan(ix, nq, nprobe, k);
     update_seg_cache(ix, plan.tseg, plan.segmax);
     if (item_bound(ix, nq, nprobe, plan.qw) <= ix->item_desc_cap) return ROUTE_GROUP;
@@ -225,39 +221,23 @@ ScanRoute scan_route(rabitq_index* ix, int64_t nq, int nprobe, int k) {
   return ROUTE_SINGLE;
 }
 
-// The most pairs, up to `pairs`, that do not go by groups although `pairs` do (group_wanted is monotone in them).
-static int64_t pairs_below_groups(const rabitq_index* ix, int64_t pairs) {
-  int64_t below = -1, from = pairs;
-  while (from - below > 1) {
-    const int64_t mid = below + (from - below) / 2;
-    (group_wanted(ix, mid, 1) ? from : below) = mid;
-  }
-  return below;
-}
-
 int ensure_split_buffers(rabitq_index* ix, int64_t nq, int nprobe, int k) {
-  const bool group = group_wanted(ix, nq, nprobe);  // (keeps its survivors to itself)
+  const bool group = group_wanted(ix, nq, nprobe, k);  // (keeps its survivors to itself)
   if (!group && !split_wanted(ix, nq, nprobe)) return RABITQ_OK;
   int64_t need = group ? 0 : split_mask_blocks(ix, nq, nprobe);
   const ScanPlan plan = plan_for(ix, nq, nprobe, k, false, group);
   update_seg_cache(ix, plan.tseg, plan.segmax);
   int64_t items = item_bound(ix, nq, nprobe, plan.qw);
-  if (group && items <= 0x7fffffff) {
-    // A smaller batch may be split instead, and the last part of this one or a later rabitq_search_noalloc is such a batch: room for
-    // it as well.  At most `below` pairs of at most nq queries have most tiles where there are nq queries and their below / nq
-    // lists (some one more) are the largest, which does not grow as nq shrinks: a smaller search that goes by groups needs no
-    // more room than this one.  The items are bounded by segments of the least length.
-    const int64_t below = pairs_below_groups(ix, nq * nprobe);
-    if (below > 0 && split_wanted(ix, below, 1)) {
-      const ScanPlan finest = plan_for(ix, 1, 1, k, false);
-      const int64_t lists = below / nq, more = below % nq;
-      const int64_t split_blocks = ((nq - more) * largest_tiles(ix, lists) + more * largest_tiles(ix, lists + 1) + QM - 1) / QM + ix->n_tiles;
-      const int64_t segs = seg_count(ix->max_tiles, finest.tseg, finest.segmax);
-      const int64_t split_items = ix->n_tiles / finest.tseg + ix->nlist + (below * segs + QW - 1) / QW + 8;
-      if (split_blocks < ((int64_t)1 << 32) && split_items <= 0x7fffffff) {
-        need = split_blocks;
-        items = std::max(items, split_items);
-      }
+  if (group && split_wanted(ix, nq, nprobe)) {
+    // A smaller batch, or one with another k, may be split instead, and the last part of this one or a later
+    // rabitq_search_noalloc is such a batch: room for it as well.  Its items are bounded by segments of the least length, so that
+    // a smaller search by groups never needs more than this one.
+    const ScanPlan finest = plan_for(ix, 1, 1, k, false);
+    const int64_t blocks = split_mask_blocks(ix, nq, nprobe), segs = seg_count(ix->max_tiles, finest.tseg, finest.segmax);
+    const int64_t split_items = ix->n_tiles / finest.tseg + ix->nlist + (nq * nprobe * segs + QW - 1) / QW + 8;
+    if (blocks < ((int64_t)1 << 32) && split_items <= 0x7fffffff) {
+      need = blocks;
+      items = std::max(items, split_items);
     }
   }
   if (need <= ix->surv_mask_blocks && items <= ix->item_desc_cap) return RABITQ_OK;
@@ -438,7 +418,7 @@ static ScanPlan plan_for(const rabitq_index* ix, int64_t nq, int nprobe, int k, 
 // groups of pairs).  Taken when the handle's descriptor memory is large enough (ensure_stream_buffers, called by the
 // entry points that may allocate); otherwise the general kernel does the same work.
 ScanPlan scan_plan(const rabitq_index* ix, int64_t nq, int nprobe, int k) {
-  const bool streaming = stream_shape(ix, nq, nprobe) && ix->item_desc != nullptr &&
+  const bool streaming = stream_shape(ix, nq, nprobe, k) && ix->item_desc != nullptr &&
                          stream_desc_slots(ix, nq, nprobe, k) <= ix->item_desc_cap;
   return plan_for(ix, nq, nprobe, k, streaming);
 }

@@ -53,10 +53,10 @@ def test_wide_codes_go_by_groups(D, nq, nprobe, options, want):
 
 
 @pytest.mark.parametrize("D,nq,nprobe,options,want", [
-    (64, 8191, 6, [], SPLIT),                                           # 49 146 pairs: 3071.6 groups
-    (64, 8192, 6, [], GROUP),
-    (256, 8192, 6, [("scan_impl", 4)], GROUP),
-    (64, 8192, 6, [("split_min_pairs", 6145)], SINGLE),                 # 6144 pairs a list
+    (64, 8191, 8, [], SPLIT),                                           # 65 528 pairs: 4095.5 groups
+    (64, 8192, 8, [], GROUP),
+    (256, 8192, 8, [("scan_impl", 4)], GROUP),
+    (64, 8192, 8, [("split_min_pairs", 8193)], SINGLE),                 # 8192 pairs a list
     (64, 100, 3, [("scan_impl", 4), ("split_min_pairs", 0)], SPLIT),    # few pairs a list ask for no fewer groups
     (64, 100, 3, [("scan_impl", 4), ("group_min", 0)], GROUP),          # 37 pairs a list
     (64, 100, 3, [("scan_impl", 4), ("group_min", 19)], SPLIT),
@@ -66,6 +66,15 @@ def test_wide_codes_go_by_groups(D, nq, nprobe, options, want):
 ])
 def test_groups_from_group_min_on(D, nq, nprobe, options, want):
     check(D, 4, 8, nq, nprobe, options, want)
+
+
+@pytest.mark.parametrize("D,k,options,want", [
+    (64, 32, [], GROUP), (64, 33, [], SPLIT), (256, 64, [("scan_impl", 4)], SPLIT), (64, 65, [], GROUP), (64, 128, [], GROUP),
+    (64, 50, [("group_min", 4096)], GROUP),                             # asked for
+    (960, 50, [], GROUP),
+])
+def test_up_to_256_dimensions_some_k_are_split(D, k, options, want):
+    check(D, 4, 8, 8192, 8, options, want, k)
 
 
 @pytest.mark.parametrize("n,want", [(64 * 64, GROUP), (64 * 64 + 1, SPLIT)])
@@ -92,23 +101,21 @@ def test_a_search_by_groups_makes_room_for_smaller_ones_that_are_split(k):
     route = lambda gi: (gi.index_info("last_scan_split"), gi.index_info("last_scan_group"))  # noqa: E731
     make = lambda: rabitq.Index.build(torch.from_numpy(X).cuda(), nlist, 4, build.random_rotation(D, 7), kmeans_iters=1)  # noqa: E731
     with_split = make()
-    want_i, want_d = with_split.search(q[:8191], k, 6)
+    want_i, want_d = with_split.search(q[:8191], k, 8)
     assert route(with_split) == SPLIT
     gi = make()
-    gi.search(q[:8192], k, 6)
+    gi.search(q[:8192], k, 8)
     assert route(gi) == GROUP
-    for nq, nprobe in ((4096, 6), (8191, 6), (6000, 8), (8192, 5)):   # (nothing is allocated there)
-        ids = torch.empty((nq, k), dtype=torch.int64, device="cuda")
-        d = torch.empty((nq, k), dtype=torch.float32, device="cuda")
-        if nq * nprobe * (256 if k > 64 else 128) * 8 > 60 << 20:     # (more than the scratch of that entry point)
-            continue
-        gi.search_noalloc(q[:nq], k, nprobe, ids, d)
-        assert route(gi) == SPLIT, (nq, nprobe)
-        if nprobe == 6:
+    for nq, nprobe, other_k in ((2048, 8, k), (3500, 8, k), (6000, 4, k), (7000, 8, 40)):   # (nothing is allocated there)
+        ids = torch.empty((nq, other_k), dtype=torch.int64, device="cuda")
+        d = torch.empty((nq, other_k), dtype=torch.float32, device="cuda")
+        gi.search_noalloc(q[:nq], other_k, nprobe, ids, d)
+        assert route(gi) == SPLIT, (nq, nprobe, other_k)
+        if nprobe == 8 and other_k == k:
             assert torch.equal(ids, want_i[:nq]) and torch.equal(d, want_d[:nq])
     last = make()
     last.set_option("max_batch", 8192)
-    ids, d = last.search(q, k, 6)         # 8192 queries by groups, then 4096
+    ids, d = last.search(q, k, 8)         # 8192 queries by groups, then 4096
     assert route(last) == SPLIT
     assert torch.equal(ids[:8191], want_i) and torch.equal(d[:8191], want_d)
     for ix in (with_split, gi, last):
