@@ -218,7 +218,8 @@ int rabitq_search_noalloc(rabitq_index_t index, const float* queries, int64_t nq
  *             seeding and the scan; its estimates differ from those of 0/1 by the query
  *             quantisation error.
  *   "group_min" n: groups of 16 pairs from which scan_impl 3 and 4 scan by groups in one kernel; -1 (default): 4096 up to 256
- *             dimensions, where a search of 33 to 64 neighbours does not; from 960 on 512 for scan_impl 3 and 0 for 4.
+ *             dimensions, where a search of 33 to 64 neighbours does not; from 960 on, for scan_impl 3, 512 for codes of up to 4 bits and 768 for
+ *             longer ones, which do not for more than 16 neighbours, and 0 for 4.
  * Errors: RABITQ_EINVAL for an unknown name or value. */
 int rabitq_set_option(rabitq_index_t index, const char* name, int64_t value);
 

@@ -213,8 +213,11 @@ inline bool split_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
 // A wavefront has 16 pairs to itself, so a search of few pairs leaves the chip idle: with less than a wavefront for each of its
 // 4096 places (16 lists, 424 queries x 8: 120 us split, 244 by groups; 274 lists, 3438 groups: 282 and 342; 1683 lists, 3873
 // groups: 320 and 374; 639 lists, 4265 groups: 194 and 152; 227 lists, 11836 groups: 209 and 173; from 512 groups on with the
-// shorter work items of D >= 960, where 385 take 1244 us against 1124, 628 take 323 against 356 and 1000 take 837 against 1095)
-// the former kernels keep it.  (scan_impl 4 from D = 960 on takes it at any number of groups: there is no split search of that width.)
+// shorter work items of D >= 960 and codes of up to 4 bits: 330 us against 401 there) the former kernels keep it.  Longer codes
+// of that width have twice the bytes to refine with, which the four-wavefront kernel's fuller rounds of candidates are better at:
+// they go by groups from 768 on and for few neighbours (960-d, 5 bits, k = 10: 512 groups 324 us and 404 by groups, 768 groups
+// 463 and 467, 1024 groups 652 and 604, the 1000 of hub lists 1095 and 837; k = 32: 1103 and 1190, 3215 and 5433).
+// (scan_impl 4 from D = 960 on takes it at any number of groups: there is no split search of that width.)
 // Up to 256 dimensions a pair's region holds the smallest power of two from k + 64 on and is cut to k when the 64 keys that a
 // round may add do not fit: for k from 33 to 64 after less than 32 new keys, and at 64 after every one, so that the cuts
 // outweigh the rest (11407 groups, k = 53: 580 us split, 1040 by groups; 3083, k = 55: 263 and 397; 24008, k = 50: 564 and 576).
@@ -222,7 +225,8 @@ inline bool split_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
 inline int64_t group_min_of(const rabitq_index* ix, int k) {
   if (ix->group_min >= 0) return ix->group_min;
   if (ix->W < 30) return k > 32 && k <= 64 ? INT64_MAX / QM : 4096;
-  return ix->scan_impl == 4 ? 0 : 512;
+  if (ix->scan_impl == 4) return 0;
+  return ix->total_bits <= 4 ? 512 : (k <= 16 ? 768 : INT64_MAX / QM);
 }
 inline bool group_wanted(const rabitq_index* ix, int64_t nq, int nprobe, int k) {
   if (!split_built(ix) || (ix->scan_impl != 3 && ix->scan_impl != 4)) return false;

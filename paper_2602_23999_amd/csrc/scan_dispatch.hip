@@ -407,6 +407,9 @@ static ScanPlan plan_for(const rabitq_index* ix, int64_t nq, int nprobe, int k, 
   const int64_t est_items = std::min<int64_t>(np_all, (np_all + p.qw - 1) / p.qw + ix->nlist);
   const int64_t avg_tiles = std::max<int64_t>(1, ix->n_tiles / std::max(1, ix->nlist));
   p.tseg = (int)std::min<int64_t>(32, std::max<int64_t>(2, est_items * avg_tiles / 4096));
+  // (a wavefront of the group scan of wide codes takes so long for its 16 pairs that nothing is gained by longer segments: 960-d, 5 bits,
+  // 512 lists, 768 groups: 635 us in segments of 6 tiles, 467 in those of 2; 2048 groups: 1450 and 917)
+  if (group && !group_narrow(ix->W)) p.tseg = 2;
   if (ix->seg_tiles > 0) p.tseg = ix->seg_tiles;
   p.segmax = std::max(1, next_pow2_host(k + TILE) / k);
   if (group && group_narrow(ix->W)) p.segmax = 1;  // (a wavefront owns its pairs' candidate regions)

@@ -52,6 +52,15 @@ def test_wide_codes_go_by_groups(D, nq, nprobe, options, want):
     check(D, 4, 8, nq, nprobe, options, want)
 
 
+@pytest.mark.parametrize("bits,nq,k,options,want", [
+    (5, 1535, 16, [], SINGLE), (5, 1536, 16, [], GROUP), (5, 1536, 17, [], SINGLE), (8, 4096, 17, [], SINGLE),
+    (5, 1536, 17, [("scan_impl", 4)], GROUP), (5, 1536, 17, [("group_min", 768)], GROUP),
+    (4, 1024, 128, [], GROUP), (2, 1023, 5, [], SINGLE),
+])
+def test_long_wide_codes_go_by_groups_for_few_neighbours(bits, nq, k, options, want):
+    check(960, bits, 8, nq, 8, options, want, k)
+
+
 @pytest.mark.parametrize("D,nq,nprobe,options,want", [
     (64, 8191, 8, [], SPLIT),                                           # 65 528 pairs: 4095.5 groups
     (64, 8192, 8, [], GROUP),
