@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -209,7 +210,9 @@ inline bool split_wanted(const rabitq_index* ix, int64_t nq, int nprobe) {
 }
 // ... as one kernel, the group scan (scan_group.hip says why these widths).  For codes of up to 256 dimensions it does not cut
 // lists into segments, so the longest list must not outlast the launch: one wavefront works on it, while the chip's about
-// 3072 share the rest.  From D = 960 on it takes the place of the four-wavefront matrix-core kernel from 8 pairs per list on.
+// 3072 share the rest (1024 lists of 13 tiles and one longer, 8192 groups, a share of 42 tiles each: 348 us with a longest list of
+// 32, 433 of 64, 299 split; 20 000 groups, 95 tiles: 583 of 64, 759 of 128, 515 split, 622 split before the digits;
+// k > 64, where the split search's pools take room from its wavefronts: 1164 lists of 5 tiles, the longest above 32, 224 and 380).  From D = 960 on it takes the place of the four-wavefront matrix-core kernel from 8 pairs per list on.
 // A wavefront has 16 pairs to itself, so a search of few pairs leaves the chip idle: with less than a wavefront for each of its
 // 4096 places (16 lists, 424 queries x 8: 120 us split, 244 by groups; 274 lists, 3438 groups: 282 and 342; 1683 lists, 3873
 // groups: 320 and 374; 639 lists, 4265 groups: 194 and 152; 227 lists, 11836 groups: 209 and 173; from 512 groups on with the
@@ -235,7 +238,7 @@ inline bool group_wanted(const rabitq_index* ix, int64_t nq, int nprobe, int k) 
   if (ix->W >= 30) return pairs >= (int64_t)(ix->split_min_pairs < 8 ? ix->split_min_pairs : 8) * ix->nlist;
   if (ix->W > 8 || pairs < (int64_t)ix->split_min_pairs * ix->nlist) return false;
   const int64_t share = (pairs / QM + ix->nlist) * (ix->n_tiles / (ix->nlist > 0 ? ix->nlist : 1) + 1) / 3072;
-  return ix->max_tiles <= (share > 32 ? 2 * share : 64);
+  return ix->max_tiles <= std::max<int64_t>(share, k > 64 ? 64 : 32);
 }
 // Which scan a search of this shape gets, given the handle's buffers: SINGLE stands for the kernels of scan_impl 0, 1 and 2.
 enum ScanRoute { ROUTE_SINGLE, ROUTE_SPLIT, ROUTE_GROUP };

@@ -17,7 +17,7 @@ CASES = {
     "l2_128_b8": ("l2_128", 4_000, 40, 32, 12, 8, 10, 5),
     "l2_96_b3_k100": ("l2_96", 20_000, 64, 64, 40, 3, 100, 8),
     "ragged_b2": ("tiny", 1_500, 40, 50, 50, 2, 10, 50),
-    "centred_b4": ("l2_128", 20_000, 64, 64, 32, 4, 10, 6),
+    "centred_b4": ("l2_128", 8_000, 64, 64, 32, 4, 10, 6),
     "ip_768_b8": ("ip_768_tight", 1_500, 24, 12, 10, 8, 10, 4),
     "l2_960_b5": ("l2_960", 4_000, 24, 16, 12, 5, 10, 4),
     "l2_960_b2_k100": ("l2_960", 3_000, 40, 8, 6, 2, 100, 3),

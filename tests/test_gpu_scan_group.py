@@ -16,8 +16,8 @@ CASES = [
     (64, 3, 7, 3_000, 90, 7, 1, "l2"),         # every list probed: 90 pairs a list, the last group of 10
     (96, 4, 3, 200, 100, 1, 100, "l2"),        # lists below k, some of less than a tile; 4-bit fields
     (96, 8, 16, 9_000, 257, 4, 128, "ip"),     # flipped bytes; regions cut at k = 128
-    (128, 4, 1, 4_096, 64, 1, 64, "l2"),       # a list of 64 tiles, the longest that a few groups take
-    (128, 4, 4, 7_000, 64, 4, 64, "l2"),       # lists of 27 tiles and more
+    (128, 4, 1, 2_048, 64, 1, 64, "l2"),       # a list of 32 tiles, the longest that a few groups take
+    (128, 4, 4, 4_200, 64, 4, 64, "l2"),       # lists of 16 tiles and more
     (128, 5, 1, 1_000, 17, 1, 10, "l2"),       # one list, a group of one pair beside a full one
     (256, 7, 6, 2_500, 130, 2, 33, "l2"),      # the widest of the narrow form
     (960, 5, 4, 1_500, 40, 3, 10, "l2"),       # the wide form, lists in segments

@@ -86,46 +86,32 @@ def test_up_to_256_dimensions_some_k_are_split(D, k, options, want):
     check(D, 4, 8, 8192, 8, options, want, k)
 
 
-@pytest.mark.parametrize("n,want", [(64 * 64, GROUP), (64 * 64 + 1, SPLIT)])
-def test_a_list_too_long_for_one_wavefront_is_split(n, want):
+@pytest.mark.parametrize("n,k,want", [(32 * 64, 9, GROUP), (32 * 64 + 1, 9, SPLIT), (64 * 64, 65, GROUP), (64 * 64 + 1, 65, SPLIT)])
+def test_a_list_too_long_for_one_wavefront_is_split(n, k, want):
     rng = np.random.default_rng(n)
     X = rng.standard_normal((n, 64)).astype(np.float32)
     gi = rabitq.Index.build(torch.from_numpy(X).cuda(), 1, 4, build.random_rotation(64, 7), kmeans_iters=1)
     q = torch.from_numpy(X[:50] + 0.1).cuda()
     gi.set_option("group_min", 0)
-    ids, d = gi.search(q, 9, 1)
+    ids, d = gi.search(q, k, 1)
     assert (gi.index_info("last_scan_split"), gi.index_info("last_scan_group")) == want
     gi.set_option("scan_impl", 0)
-    ref_i, ref_d = gi.search(q, 9, 1)
+    ref_i, ref_d = gi.search(q, k, 1)
     assert torch.equal(ids, ref_i) and torch.equal(d, ref_d)
     gi.close()
 
 
 @pytest.mark.parametrize("k", [5, 100])
-def test_a_search_by_groups_makes_room_for_smaller_ones_that_are_split(k):
+def test_the_last_part_of_a_search_by_groups_is_split(k):
     D, nlist = 64, 8
     rng = np.random.default_rng(3)
     X = rng.standard_normal((40 * nlist, D)).astype(np.float32)
     q = torch.from_numpy(rng.standard_normal((12_288, D)).astype(np.float32)).cuda()
-    route = lambda gi: (gi.index_info("last_scan_split"), gi.index_info("last_scan_group"))  # noqa: E731
-    make = lambda: rabitq.Index.build(torch.from_numpy(X).cuda(), nlist, 4, build.random_rotation(D, 7), kmeans_iters=1)  # noqa: E731
-    with_split = make()
-    want_i, want_d = with_split.search(q[:8191], k, 8)
-    assert route(with_split) == SPLIT
-    gi = make()
-    gi.search(q[:8192], k, 8)
-    assert route(gi) == GROUP
-    for nq, nprobe, other_k in ((2048, 8, k), (3500, 8, k), (6000, 4, k), (7000, 8, 40)):   # (nothing is allocated there)
-        ids = torch.empty((nq, other_k), dtype=torch.int64, device="cuda")
-        d = torch.empty((nq, other_k), dtype=torch.float32, device="cuda")
-        gi.search_noalloc(q[:nq], other_k, nprobe, ids, d)
-        assert route(gi) == SPLIT, (nq, nprobe, other_k)
-        if nprobe == 8 and other_k == k:
-            assert torch.equal(ids, want_i[:nq]) and torch.equal(d, want_d[:nq])
-    last = make()
-    last.set_option("max_batch", 8192)
-    ids, d = last.search(q, k, 8)         # 8192 queries by groups, then 4096
-    assert route(last) == SPLIT
-    assert torch.equal(ids[:8191], want_i) and torch.equal(d[:8191], want_d)
-    for ix in (with_split, gi, last):
-        ix.close()
+    gi = rabitq.Index.build(torch.from_numpy(X).cuda(), nlist, 4, build.random_rotation(D, 7), kmeans_iters=1)
+    gi.set_option("max_batch", 8192)
+    ids, d = gi.search(q, k, 8)           # 8192 queries by groups, then 4096, on a handle that has split nothing yet
+    assert (gi.index_info("last_scan_split"), gi.index_info("last_scan_group")) == SPLIT
+    gi.set_option("scan_impl", 0)
+    ref_i, ref_d = gi.search(q, k, 8)
+    assert torch.equal(ids, ref_i) and torch.equal(d, ref_d)
+    gi.close()
