@@ -209,7 +209,8 @@ int rabitq_search_noalloc(rabitq_index_t index, const float* queries, int64_t nq
  *             at least "split_min_pairs" (an option; default 32; from D = 960 on at most 8) pairs per list on average,
  *             otherwise as 0.  Same results.  The survivor bits and the work-item descriptors live in buffers the handle
  *             grows on demand (rabitq_search and rabitq_scan may allocate when a larger batch arrives;
- *             rabitq_search_noalloc never does and takes this form only if the buffers are already large enough).
+ *             rabitq_search_noalloc never does and takes this form only if the buffers are already large enough: after a
+ *             rabitq_search of the same shape they are; one that goes by groups as one kernel does not make the survivor bits).
  *             3 (default): the faster in measurements: 4 where it is taken (see above; from D = 960 on only where there are at least
  *             "group_min" groups), else 1 for D >= 960 and 0 below.
  *             2: the lookup-table scheme of Section 3.4.1(1) instead of the quantised query:

@@ -758,7 +758,9 @@ int rabitq_search(rabitq_index_t ix, const float* queries, int64_t nq, int32_t k
   // consecutive sub-batches through one workspace; the results do not depend on the split.
   const int64_t step = std::min(nq, search_batch_limit(ix, k, nprobe));
   if ((rc = ensure_workspace(ix, step, nprobe, k))) return rc;
-  if ((rc = ensure_split_buffers(ix, step, nprobe, k))) return rc;  // (also for the last part, which may be smaller)
+  if ((rc = ensure_split_buffers(ix, step, nprobe, k))) return rc;
+  // (the last part may be split where the others go by groups)
+  if (nq % step != 0 && (rc = ensure_split_buffers(ix, nq % step, nprobe, k))) return rc;
   if ((rc = ensure_stream_buffers(ix, step, nprobe, k))) return rc;
   for (int64_t s0 = 0; s0 < nq; s0 += step) {
     const int64_t m = std::min(step, nq - s0);

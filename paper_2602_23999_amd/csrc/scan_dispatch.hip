@@ -228,18 +228,6 @@ int ensure_split_buffers(rabitq_index* ix, int64_t nq, int nprobe, int k) {
   const ScanPlan plan = plan_for(ix, nq, nprobe, k, false, group);
   update_seg_cache(ix, plan.tseg, plan.segmax);
   int64_t items = item_bound(ix, nq, nprobe, plan.qw);
-  if (group && split_wanted(ix, nq, nprobe)) {
-    // A smaller batch, or one with another k, may be split instead, and the last part of this one or a later
-    // rabitq_search_noalloc is such a batch: room for it as well.  Its items are bounded by segments of the least length, so that
-    // a smaller search by groups never needs more than this one.
-    const ScanPlan finest = plan_for(ix, 1, 1, k, false);
-    const int64_t blocks = split_mask_blocks(ix, nq, nprobe), segs = seg_count(ix->max_tiles, finest.tseg, finest.segmax);
-    const int64_t split_items = ix->n_tiles / finest.tseg + ix->nlist + (nq * nprobe * segs + QW - 1) / QW + 8;
-    if (blocks < ((int64_t)1 << 32) && split_items <= 0x7fffffff) {
-      need = blocks;
-      items = std::max(items, split_items);
-    }
-  }
   if (need <= ix->surv_mask_blocks && items <= ix->item_desc_cap) return RABITQ_OK;
   if (need >= ((int64_t)1 << 32) || items > 0x7fffffff) return RABITQ_OK;  // beyond 32-bit offsets: the search is not split
   RQ_HIP(hipDeviceSynchronize());
