@@ -93,7 +93,7 @@ def kernel_source_hash():
     return h.hexdigest()[:16]
 
 
-def stored_traffic(workload, nprobe, split=False):
+def stored_traffic(workload, nprobe, form=""):
     """Fabric traffic per scan launch (bytes) from the rocprofv3 --pmc summary under profiles/, if that summary was
     taken with the kernel sources as they are now; else None."""
     path = os.path.join(ROOT, "profiles", f"scan_kernel_{workload}_traffic.txt")
@@ -104,7 +104,7 @@ def stored_traffic(workload, nprobe, split=False):
         f = line.split()
         if len(f) >= 2 and f[0] == "kernel_source_hash":
             src = f[1]
-        if len(f) >= 2 and f[0] == f"nprobe_{nprobe}" + ("_split" if split else ""):
+        if len(f) >= 2 and f[0] == f"nprobe_{nprobe}{form}":
             val = int(f[1])
     if val is None:
         return None, "no counter reading for this nprobe"
@@ -217,7 +217,7 @@ def measure_point(gi, Qd, gt, w, bits, args, label):
     sec = timed(nprobe, args.steps, args.warmup, profile=True)
     timed_ms = gi.stage_ms()[0]
     scan_ms, est_ms = timed_ms["scan"], timed_ms["scan_estimate"]
-    split = bool(gi.index_info("last_scan_split"))
+    split, group = bool(gi.index_info("last_scan_split")), bool(gi.index_info("last_scan_group"))
     r_op = recall(out_ids, gt)
     gi.set_option("profile_stages", 0x3ff)
     timed(nprobe, min(args.steps, 20), 0, profile=True)
@@ -230,7 +230,7 @@ def measure_point(gi, Qd, gt, w, bits, args, label):
     r_unpruned = recall(out_ids, gt)
     gi.set_option("prune", 1)
     return dict(total_bits=bits, nprobe=nprobe, recall_at_k=round(r_op, 4), recall_at_k_unpruned=round(r_unpruned, 4),
-                qps=w.nq / sec, ms_per_step=sec * 1e3, scan_ms=scan_ms, scan_split=split, scan_estimate_ms=est_ms,
+                qps=w.nq / sec, ms_per_step=sec * 1e3, scan_ms=scan_ms, scan_split=split, scan_group=group, scan_estimate_ms=est_ms,
                 nprobe_sweep=sweep,
                 stage_ms={k_: round(v, 4) for k_, v in stage_ms.items()}, stage_ms_calls=calls)
 
@@ -247,7 +247,7 @@ def scan_roofline(gi, Qd, w, pt, cluster_sizes, args):
     alu_ops = qv * (8 * (w.dim // 32) + 6)
     alu_achieved = alu_ops / (scan_ms * 1e-3) / 1e12
     split = pt.get("scan_split", False)
-    traffic, traffic_note = (stored_traffic(w.name, pt["nprobe"], split)
+    traffic, traffic_note = (stored_traffic(w.name, pt["nprobe"], "_group" if pt.get("scan_group") else "_split" if split else "")
                              if impl == 0 and pt["total_bits"] == w.total_bits
                              else (None, "no counter summary for this variant"))
     roofline = {"bound": "alu", "achieved": alu_achieved, "peak": ALU_PEAK_TOPS, "unit": "TOP/s (integer lane-operations)",
@@ -257,7 +257,7 @@ def scan_roofline(gi, Qd, w, pt, cluster_sizes, args):
                 "hbm_view": {"algorithmic_bytes_per_launch": alg_bytes, "achieved_gbs": achieved, "peak_gbs": HBM_PEAK_GBS,
                              "frac": achieved / HBM_PEAK_GBS,
                              "note": "above 1 when the launch is cache-served; the HBM-bound regime is roofline.stream"}}
-    if split and pt["scan_estimate_ms"] <= 0:
+    if pt.get("scan_group"):
         # Scan by groups: one kernel estimates (matrix cores) and refines for 16 pairs of a list per wavefront
         roofline["kernel"] = "scan_group_kernel"
     elif split:
